@@ -34,7 +34,7 @@ constexpr int32_t D_EMPTY = -2;  // destination = a new singleton cluster
 
 // Degree buckets (upper bounds, inclusive).  Buckets 0-3 are handled by sub-wave groups of 4/8/16/32 lanes
 // (one neighbour per lane), 4-5 by one wavefront per vertex, 6-7 by one workgroup per vertex.  The local-move
-// kernels aggregate neighbour clusters with register shuffles (0-3), an LDS hash (4-6) or a global-memory
+// kernels sum neighbour clusters in registers (0-1), by leader lanes (2-4), in an LDS hash (5-6) or a global-memory
 // hash inside the edge arena (7).  BUCKET_CAP holds the largest row each of buckets 0-6 can serve (the lane
 // count of its group, half the slots of its LDS hash); a tuning may set lower bounds, never higher ones, and
 // every setting gives the same results.
@@ -42,7 +42,6 @@ constexpr int64_t BUCKET_CAP[NBUCKET - 1] = {4, 8, 16, 32, 128, 1024, 8192};
 // default bounds: every row up to 8192 entries is aggregated in LDS (bucket 6's rows above B6_SPLIT take the
 // 16384-slot table), longer ones in the hub chunks
 constexpr int64_t BUCKET_DEFAULT[NBUCKET - 1] = {4, 8, 16, 32, 128, 1024, 8192};
-constexpr int LDS_SLOTS_B4 = 256;
 constexpr int LDS_SLOTS_B5 = 2048;
 constexpr int LDS_SLOTS_B6 = 8192;    // bucket 6 rows up to 4096 (512 threads)
 constexpr int LDS_SLOTS_B6X = 16384;  // bucket 6 rows 4097-8192 (1024 threads, 128 KB of LDS)

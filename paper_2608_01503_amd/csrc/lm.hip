@@ -11,15 +11,16 @@
 // score).  Sums whose final value fits but whose partial sums need not (the change of the sum of squared
 // cluster weights) are accumulated modulo 2^64, which leaves the final value exact.
 //
-// Work decomposition per degree bucket (see common.h): groups of G lanes (G = 4..32, one neighbour per lane,
-// neighbour clusters aggregated by register shuffles), one wavefront per vertex with an LDS open-addressing
-// hash (degree <= 128), one workgroup per vertex with an LDS hash (degree <= 1024: 128 threads, <= 4096: 512
+// Work decomposition per degree bucket (see common.h): groups of G lanes (G = 4..32, one neighbour per lane) and
+// one wavefront per vertex (degree <= 128, two neighbours per lane), clusters summed by a register sweep (G <= 8) or
+// by leader lanes elected in LDS (rows.h), one workgroup per vertex with an LDS hash (degree <= 1024: 128 threads, <= 4096: 512
 // threads), and hub vertices split into 2048-edge chunks processed by independent workgroups with a global-memory hash in the edge arena.
 #include <algorithm>
 #include <initializer_list>
 #include <utility>
 
 #include "common.h"
+#include "rows.h"
 
 namespace lcc {
 
@@ -31,131 +32,6 @@ constexpr int HUB_BLOCK = 256;
 constexpr int BIG_BLOCK = 256;
 
 __host__ __device__ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
-
-// ---------------------------------------------------------------------------------------------------------
-// reductions over a group of G lanes (G <= 64: shuffles; G == BLOCK-sized: shuffles + LDS)
-// ---------------------------------------------------------------------------------------------------------
-__device__ __forceinline__ bool better(int64_t s2, int32_t c2, int64_t s, int32_t c) {
-  return s2 > s || (s2 == s && c2 < c);
-}
-
-// Partner of butterfly step K (K = 0, 1, ...) inside aligned groups of G lanes.  Groups of at most 16 lanes
-// use DPP lane moves (register to register, no LDS): two quad permutations (lane ^ 1, lane ^ 2), the row half
-// mirror (lane i of an 8-lane half-row <-> lane 7 - i) and the row mirror (i <-> 15 - i).  The mirror partners
-// are not xor partners, but each step pairs every lane with one in the other half of its 2^(K+1)-lane block,
-// whose lanes all hold the same value after the earlier steps: an all-reduction of a commutative and
-// associative operation gets the same result.  Wider groups use shuffles.
-constexpr int DPP_GROUP_STEP[4] = {0xB1, 0x4E, 0x141, 0x140};
-
-template <int G, int K>
-__device__ __forceinline__ int32_t gx32(int32_t x) {
-  if constexpr (G <= 16) return __builtin_amdgcn_update_dpp(0, x, DPP_GROUP_STEP[K], 0xf, 0xf, false);
-  else return __shfl_xor(x, 1 << K, G);
-}
-template <int G, int K>
-__device__ __forceinline__ int64_t gx64(int64_t x) {
-  if constexpr (G <= 16) {
-    const int32_t lo = gx32<G, K>((int32_t)(uint32_t)(uint64_t)x);
-    const int32_t hi = gx32<G, K>((int32_t)((uint64_t)x >> 32));
-    return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo);
-  } else {
-    return __shfl_xor(x, 1 << K, G);
-  }
-}
-
-// Lane K of every aligned group of G lanes (G = 4: quad permutation; 8 and 16: row broadcasts; else shuffle).
-template <int G, int K>
-__device__ __forceinline__ int32_t gbcast32(int32_t x) {
-  if constexpr (G == 4) {
-    return __builtin_amdgcn_update_dpp(0, x, K | (K << 2) | (K << 4) | (K << 6), 0xf, 0xf, false);
-  } else if constexpr (G == 8) {
-    const int32_t lo = __builtin_amdgcn_update_dpp(0, x, 0x150 + K, 0xf, 0xf, false);      // row_newbcast:K
-    const int32_t hi = __builtin_amdgcn_update_dpp(0, x, 0x150 + K + 8, 0xf, 0xf, false);  // row_newbcast:K+8
-    return (threadIdx.x & 8) ? hi : lo;
-  } else if constexpr (G == 16) {
-    return __builtin_amdgcn_update_dpp(0, x, 0x150 + K, 0xf, 0xf, false);
-  } else {
-    return __shfl(x, K, G);
-  }
-}
-
-template <int G, int K = 0>
-__device__ __forceinline__ void argmax_steps(int64_t& s, int32_t& c) {
-  if constexpr ((1 << K) < G) {
-    const int64_t s2 = gx64<G, K>(s);
-    const int32_t c2 = gx32<G, K>(c);
-    if (better(s2, c2, s, c)) { s = s2; c = c2; }
-    argmax_steps<G, K + 1>(s, c);
-  }
-}
-template <int G, int K = 0>
-__device__ __forceinline__ int64_t sum_steps(int64_t x) {
-  if constexpr ((1 << K) < G) return sum_steps<G, K + 1>(x + gx64<G, K>(x));
-  else return x;
-}
-
-template <int G>
-__device__ __forceinline__ void argmax_reduce(int64_t& s, int32_t& c) {
-  if constexpr (G <= WAVE) {
-    argmax_steps<G>(s, c);
-  } else {
-    __shared__ int64_t ss[G / WAVE];
-    __shared__ int32_t cc[G / WAVE];
-    argmax_reduce<WAVE>(s, c);
-    int wv = threadIdx.x / WAVE;
-    if ((threadIdx.x & (WAVE - 1)) == 0) { ss[wv] = s; cc[wv] = c; }
-    __syncthreads();
-    s = ss[0]; c = cc[0];
-#pragma unroll
-    for (int k = 1; k < G / WAVE; ++k)
-      if (better(ss[k], cc[k], s, c)) { s = ss[k]; c = cc[k]; }
-    __syncthreads();
-  }
-}
-
-template <int G>
-__device__ __forceinline__ int64_t sum_reduce(int64_t x) {
-  if constexpr (G <= WAVE) {
-    return sum_steps<G>(x);
-  } else {
-    __shared__ int64_t ss[G / WAVE];
-    x = sum_reduce<WAVE>(x);
-    int wv = threadIdx.x / WAVE;
-    if ((threadIdx.x & (WAVE - 1)) == 0) ss[wv] = x;
-    __syncthreads();
-    int64_t t = 0;
-#pragma unroll
-    for (int k = 0; k < G / WAVE; ++k) t += ss[k];
-    __syncthreads();
-    return t;
-  }
-}
-
-// Destination and candidacy of one vertex from its own score and its best neighbouring cluster
-// (Alg. 2: argmax, the empty-cluster rule, the temperature rule w'(v,D) >= (1 - phi) w'(v,C[v])).
-// strict != 0 replaces the temperature rule by "the move strictly improves" (node optimality, Sec. V-A).
-struct Verdict {
-  int32_t d;
-  int64_t delta;
-  bool cand;
-};
-__device__ __forceinline__ Verdict decide(int64_t scur, int64_t sbest, int32_t cbest, uint32_t pa, uint32_t pb,
-                                          int strict) {
-  int32_t d;
-  int64_t sd;
-  if (scur < 0 && (cbest == INT32_MAX || sbest < 0)) {
-    d = D_EMPTY;
-    sd = 0;
-  } else if (cbest == INT32_MAX) {
-    return {D_NONE, 0, false};
-  } else {
-    d = cbest;
-    sd = sbest;
-  }
-  int64_t delta = sd - scur;
-  bool cand = strict ? (delta > 0) : ((__int128)pb * sd >= (__int128)(pb - pa) * scur);
-  return {cand ? d : D_NONE, cand ? delta : 0, cand};
-}
 
 // this workgroup's stripe of the counter partials (see NSTRIPE)
 __device__ __forceinline__ unsigned long long* stripe(int64_t* S, int ct) {
@@ -259,26 +135,6 @@ __device__ __forceinline__ void finish_vertex(int32_t v, int32_t cv, int64_t wv,
 // cluster: 12 bytes per entry), its own state (56 bytes) and one cluster weight per other cluster (8 bytes each).
 __device__ __forceinline__ int64_t enum_bytes(int64_t deg, int64_t np) { return 12 * deg + 56 + 8 * np; }
 
-__device__ __forceinline__ uint32_t hslot(int32_t c, int bits) {
-  return ((uint32_t)c * 2654435761u) >> (32 - bits);
-}
-
-__device__ __forceinline__ int ceil_log2(int64_t x) {
-  int b = 0;
-  while (((int64_t)1 << b) < x) ++b;
-  return b;
-}
-
-// log2 of the LDS hash capacity for a row of degree d: pow2ceil(2 d) << shift slots (at least 2), at most the
-// kernel's table of `slots`; the bucket bounds keep 2 d <= slots, so the load factor never exceeds 1/2
-__device__ __forceinline__ int table_bits(int64_t d, int shift, int slots) {
-  int bits = ceil_log2(2 * d);
-  if (bits < 1) bits = 1;
-  bits += shift;
-  const int cap = ceil_log2(slots);
-  return bits < cap ? bits : cap;
-}
-
 __device__ __forceinline__ int find_chunk_owner(const int32_t* chunk_off, int64_t n7, int64_t blk) {
   int64_t lo = 0, hi = n7;
   while (hi - lo > 1) {
@@ -295,30 +151,6 @@ __device__ __forceinline__ int find_chunk_owner(const int32_t* chunk_off, int64_
 // forming a serial chain.
 // ---------------------------------------------------------------------------------------------------------
 constexpr int U = 4;
-
-// Sum of x over the 64 lanes of a fully active wavefront, returned to every lane.  A row-local Hillis-Steele
-// scan by DPP row shifts (1, 2, 4, 8), then the two row broadcasts carry rows 0-2 into rows 1-3, so lane 63
-// holds the total: register-to-register moves only, no LDS round trips.
-__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
-  int v = (int)x;
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
-  return (uint32_t)__builtin_amdgcn_readlane(v, 63);
-}
-
-__device__ __forceinline__ void lds_insert(int32_t* hk, uint32_t* hv, int bits, int32_t c, uint32_t wt) {
-  const uint32_t mask = (1u << bits) - 1;
-  uint32_t h = hslot(c, bits);
-  for (uint32_t probe = 0; probe <= mask; ++probe) {  // the table has room for every distinct key
-    int32_t prev = atomicCAS(&hk[h], -1, c);
-    if (prev == -1 || prev == c) { atomicAdd(&hv[h], wt); return; }
-    h = (h + 1) & mask;
-  }
-}
 
 // a(v, c) for the edges b + t, b + t + S, ... < e into the LDS table; edges into v's own cluster cv are
 // summed in registers (returned) instead.  Many lanes of a wavefront often carry the same cluster id (clusters
@@ -376,15 +208,6 @@ __device__ __forceinline__ int64_t insert_row(const DevGraph& g, const int32_t* 
   return own;
 }
 
-struct Best {
-  int64_t s;
-  int32_t c;
-  int64_t own;
-  int64_t np;
-};
-
-__device__ __forceinline__ Best best_init() { return Best{INT64_MIN, INT32_MAX, 0, 0}; }
-
 // slots t, t + S, ... < cap: best other cluster, weight to the own cluster, number of other clusters
 __device__ __forceinline__ void scan_table(const int32_t* hk, const uint32_t* hv, int cap, int t, int S, int32_t cv,
                                            int64_t wv, const int64_t* W, const Score& sc, Best& r) {
@@ -411,38 +234,6 @@ __device__ __forceinline__ void scan_table(const int32_t* hk, const uint32_t* hv
       ++r.np;
       int64_t val = sc.q * as[k] - sc.p * wv * Ws[k];
       if (better(val, ks[k], r.s, r.c)) { r.s = val; r.c = ks[k]; }
-    }
-  }
-}
-
-// reduction of Best over G lanes (G <= 64) or a block of G threads; the result is valid in lane / thread 0
-template <int G, int K = 0>
-__device__ __forceinline__ void best_steps(Best& r) {
-  if constexpr ((1 << K) < G) {
-    const int64_t s2 = gx64<G, K>(r.s);
-    const int32_t c2 = gx32<G, K>(r.c);
-    r.own += gx64<G, K>(r.own);
-    r.np += gx64<G, K>(r.np);
-    if (better(s2, c2, r.s, r.c)) { r.s = s2; r.c = c2; }
-    best_steps<G, K + 1>(r);
-  }
-}
-
-template <int G>
-__device__ __forceinline__ void best_reduce(Best& r) {
-  constexpr int WD = G < WAVE ? G : WAVE;
-  best_steps<WD>(r);
-  if constexpr (G > WAVE) {
-    __shared__ Best sb[G / WAVE];
-    if ((threadIdx.x & (WAVE - 1)) == 0) sb[threadIdx.x / WAVE] = r;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-#pragma unroll
-      for (int k = 1; k < G / WAVE; ++k) {
-        r.own += sb[k].own;
-        r.np += sb[k].np;
-        if (better(sb[k].s, sb[k].c, r.s, r.c)) { r.s = sb[k].s; r.c = sb[k].c; }
-      }
     }
   }
 }
@@ -634,28 +425,13 @@ __global__ __launch_bounds__(HUB_BLOCK) void k_single_hub(const int32_t* hubs, c
 // General pass: enumerate neighbour clusters and take the argmax (Alg. 2 with DS = Enumerate(G, C))
 // ---------------------------------------------------------------------------------------------------------
 
-// Every lane of the group sees every lane's (cluster, weight) in turn and sums the weights of its own cluster;
-// a lane stays leader when no earlier lane holds its cluster.
-template <int G, int K = 0>
-__device__ __forceinline__ void pair_sweep(int32_t c, int32_t wt, bool has, int gl, int64_t& acc, bool& leader) {
-  if constexpr (K < G) {
-    const int32_t ck = gbcast32<G, K>(c);
-    const int32_t wk = gbcast32<G, K>(wt);
-    if (has && ck == c) {
-      acc += wk;
-      if (K < gl) leader = false;
-    }
-    pair_sweep<G, K + 1>(c, wt, has, gl, acc, leader);
-  }
-}
-
 // degree <= G: lane l holds neighbour l; clusters aggregated by an all-pairs sweep of the group.  Workgroup
 // bid of nblk walks the list.
 template <int G>
 __device__ __forceinline__ void enum_grp_blocks(const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk,
                                                 const DevGraph& g, const int32_t* C, const int64_t* W,
                                                 const ScoreSrc& ss, uint32_t pa, uint32_t pb, int strict,
-                                                VState* vs, VtxAcc& va) {
+                                                VState* vs, VtxAcc& va, LeaderLds<1>* ll) {
   const int gl = threadIdx.x % G;
   for (int64_t gid = (int64_t)bid * (BLOCK / G) + threadIdx.x / G; gid < cnt; gid += (int64_t)nblk * (BLOCK / G)) {
     const int32_t v = list[gid];
@@ -670,7 +446,17 @@ __device__ __forceinline__ void enum_grp_blocks(const int32_t* list, int64_t cnt
     const int32_t wt = has ? g.w[b + gl] : 0;
     int64_t acc = 0;
     bool leader = has;
-    pair_sweep<G>(c, wt, has, gl, acc, leader);
+    if constexpr (G <= 8) {
+      pair_sweep<G>(c, wt, has, gl, acc, leader);
+    } else {
+      const int32_t ks[1] = {c};
+      uint32_t as[1] = {(uint32_t)wt};
+      const bool hs[1] = {has};
+      bool ls[1];
+      leader_sum<G, 1>(ll[threadIdx.x / WAVE], threadIdx.x & (WAVE - 1), ks, as, hs, ls);
+      acc = as[0];
+      leader = ls[0];
+    }
     int64_t own = (leader && c == cv) ? acc : 0;
     int64_t bs = INT64_MIN;
     int32_t bcl = INT32_MAX;
@@ -693,9 +479,10 @@ __global__ __launch_bounds__(BLOCK) void k_enum_grp(const int32_t* list, int64_t
                                                     const int32_t* C, const int64_t* W, ScoreSrc ss, uint32_t pa,
                                                     uint32_t pb, int strict, VState* vs, LMSlot* slot, int pass,
                                                     int64_t* S, int ct_own, int ct_pairs) {
+  __shared__ LeaderLds<1> ll[BLOCK / WAVE];
   VtxAcc va;
   if (slot && slot->skip[pass]) return;
-  enum_grp_blocks<G>(list, cnt, blockIdx.x, gridDim.x, g, C, W, ss, pa, pb, strict, vs, va);
+  enum_grp_blocks<G>(list, cnt, blockIdx.x, gridDim.x, g, C, W, ss, pa, pb, strict, vs, va, ll);
   acc_flush<BLOCK>(va, S, slot ? CT_NCAND : -1, ct_own, ct_pairs);
 }
 
@@ -719,62 +506,71 @@ __device__ __forceinline__ int grp_set_bucket(const GrpSet& q, unsigned& bid) {
 __global__ __launch_bounds__(BLOCK) void k_enum_grps(GrpSet q, DevGraph g, const int32_t* C, const int64_t* W,
                                                      ScoreSrc ss, uint32_t pa, uint32_t pb, int strict, VState* vs,
                                                      LMSlot* slot, int pass, int64_t* S, int ct_own, int ct_pairs0) {
+  __shared__ LeaderLds<1> ll[BLOCK / WAVE];
   VtxAcc va;
   if (slot && slot->skip[pass]) return;
   unsigned bid;
   const int k = grp_set_bucket(q, bid);  // uniform over the workgroup
-  if (k == 0) enum_grp_blocks<4>(q.list[0], q.cnt[0], bid, q.nb[0], g, C, W, ss, pa, pb, strict, vs, va);
-  else if (k == 1) enum_grp_blocks<8>(q.list[1], q.cnt[1], bid, q.nb[1], g, C, W, ss, pa, pb, strict, vs, va);
-  else enum_grp_blocks<16>(q.list[2], q.cnt[2], bid, q.nb[2], g, C, W, ss, pa, pb, strict, vs, va);
+  if (k == 0) enum_grp_blocks<4>(q.list[0], q.cnt[0], bid, q.nb[0], g, C, W, ss, pa, pb, strict, vs, va, ll);
+  else if (k == 1) enum_grp_blocks<8>(q.list[1], q.cnt[1], bid, q.nb[1], g, C, W, ss, pa, pb, strict, vs, va, ll);
+  else enum_grp_blocks<16>(q.list[2], q.cnt[2], bid, q.nb[2], g, C, W, ss, pa, pb, strict, vs, va, ll);
   acc_flush<BLOCK>(va, S, slot ? CT_NCAND : -1, ct_own, ct_pairs0 >= 0 ? ct_pairs0 + k : -1);
 }
 
-// Orders a wavefront's own LDS accesses around a phase change of its private table: every LDS operation of
-// the wavefront has completed (lgkmcnt 0) and the compiler moves no memory access across.  No other wavefront
-// is involved, so no workgroup barrier.
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0), vmcnt and expcnt left at their maximum
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// One wavefront per vertex, LDS open-addressing hash of capacity pow2ceil(2 d) <= SLOTS.  Every wavefront owns
-// its table and walks its own vertices: the wavefronts of a workgroup never wait for each other.
-template <int SLOTS>
-__global__ __launch_bounds__(BLOCK) void k_enum_wave(const int32_t* list, int64_t cnt, DevGraph g,
-                                                     const int32_t* C, const int64_t* W, ScoreSrc ss, uint32_t pa,
-                                                     uint32_t pb, int strict, VState* vs, LMSlot* slot,
-                                                     int pass, int64_t* S, int ct_own, int ct_pairs,
-                                                     int hshift) {
-  __shared__ int32_t hk[BLOCK / WAVE][SLOTS];
-  __shared__ uint32_t hv[BLOCK / WAVE][SLOTS];
+// Rows of at most 128 entries, one wavefront per vertex, two entries per lane summed by leaders (rows.h).  The
+// wavefronts of a workgroup never wait for each other.  Bound by instructions and LDS operations per row: with a
+// hash of 256 slots per wavefront (cleared, filled by compare-and-swap, scanned) it took 157 us a launch on R-MAT
+// scale 22, now 108 us; the 32-lane groups, by an all-pairs sweep before, 52 us on 96 kNN graphs, now 26 us.
+__global__ __launch_bounds__(BLOCK) void k_enum_wave(const int32_t* list, int64_t cnt, DevGraph g, const int32_t* C,
+                                                     const int64_t* W, ScoreSrc ss, uint32_t pa, uint32_t pb,
+                                                     int strict, VState* vs, LMSlot* slot, int pass, int64_t* S,
+                                                     int ct_own, int ct_pairs) {
+  __shared__ LeaderLds<2> ll[BLOCK / WAVE];
   VtxAcc va;
   if (slot && slot->skip[pass]) return;
   const int wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
-  int32_t* tk = hk[wv];
-  uint32_t* tv = hv[wv];
   for (int64_t gid = (int64_t)blockIdx.x * (BLOCK / WAVE) + wv; gid < cnt;
        gid += (int64_t)gridDim.x * (BLOCK / WAVE)) {
     const int32_t v = list[gid];
-    const int64_t b = g.off[v], e = g.off[v + 1];
+    const int64_t b = g.off[v];
+    const int d = (int)(g.off[v + 1] - b);
     const int32_t cv = C[v];
     const int64_t wvt = g.vw[v];
-    const int bits = table_bits(e - b, hshift, SLOTS);
-    for (int sl = lane; sl < (1 << bits); sl += WAVE) { tk[sl] = -1; tv[sl] = 0; }
-    wave_lds_sync();
-    const int64_t own_reg = insert_row(g, C, b, e, lane, WAVE, cv, tk, tv, bits, ss.cons, ss.con(v));
-    wave_lds_sync();
     const Score sc = ss.at(v);
+    const int32_t bv = ss.con(v);
+    int32_t cs[2];
+    uint32_t as[2];
+    bool has[2], lead[2];
     Best r = best_init();
-    scan_table(tk, tv, 1 << bits, lane, WAVE, cv, wvt, W, sc, r);
-    r.own += own_reg;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int j = lane + k * WAVE;
+      has[k] = j < d;
+      cs[k] = g.idx[b + (has[k] ? j : 0)];  // lanes past the end read the row's first entry (d > 0)
+      as[k] = (uint32_t)g.w[b + (has[k] ? j : 0)];
+      if (ss.cons && ss.cons[cs[k]] != bv) has[k] = false;
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      cs[k] = C[cs[k]];
+      if (has[k] && cs[k] == cv) { r.own += as[k]; has[k] = false; }
+    }
+    leader_sum<WAVE, 2>(ll[wv], lane, cs, as, has, lead);
+    int64_t Ws[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) Ws[k] = lead[k] ? W[cs[k]] : 0;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      if (!lead[k]) continue;
+      ++r.np;
+      const int64_t val = sc.q * (int64_t)as[k] - sc.p * wvt * Ws[k];
+      if (better(val, cs[k], r.s, r.c)) { r.s = val; r.c = cs[k]; }
+    }
     best_reduce<WAVE>(r);
     if (lane == 0) {
       finish_vertex(v, cv, wvt, r.own, r.s, r.c, sc, W, pa, pb, strict, vs, va, ss.ownv);
-      va.bytes += enum_bytes(e - b, r.np);
+      va.bytes += enum_bytes(d, r.np);
     }
-    wave_lds_sync();  // the scan's reads are done before the next vertex clears the table
   }
   acc_flush<BLOCK>(va, S, slot ? CT_NCAND : -1, ct_own, ct_pairs);
 }
@@ -947,36 +743,6 @@ __global__ void k_hub_final(const int32_t* hubs, const int32_t* chunk_off, int64
 // by +-q w'(u,v); v is kept when the adjusted delta is >= 0.  Order: larger delta first; deltas within the
 // tie window are ordered by the splitmix64 hash of the vertex id.
 // ---------------------------------------------------------------------------------------------------------
-// u and v are graph-local ids (the level id minus the graph's first id in a union of graphs).
-__device__ __forceinline__ bool before(int32_t u, int64_t du, int32_t v, int64_t dv, int64_t tie) {
-  const __int128 diff = (__int128)du - dv;  // two deltas below 2^63 each: their difference needs 65 bits
-  const __int128 ad = diff < 0 ? -diff : diff;
-  if (ad <= tie) return fmix64((uint64_t)(uint32_t)u) < fmix64((uint64_t)(uint32_t)v);
-  return diff > 0;
-}
-
-__device__ __forceinline__ int64_t ab_adjust(int32_t cv, int32_t dv, int32_t cu, int32_t du, int64_t wq) {
-  int64_t a = 0;
-  if (cv == cu) a += wq;
-  else if (dv == cu) a -= wq;
-  if (du != D_EMPTY) {
-    if (cv == du) a -= wq;
-    else if (dv == du) a += wq;
-  }
-  return a;
-}
-
-__device__ __forceinline__ int ab_pattern(int32_t cv, int32_t dv, int32_t cu, int32_t du) {
-  int a = 0;
-  if (cv == cu) a += 1;
-  else if (dv == cu) a -= 1;
-  if (du != D_EMPTY) {
-    if (cv == du) a -= 1;
-    else if (dv == du) a += 1;
-  }
-  return a;
-}
-
 // sum of the adjustments of candidate v over the edges b + t, b + t + S, ... < e
 template <int UU = U>
 __device__ __forceinline__ int64_t ab_row(const DevGraph& g, const VState* vs, const Score& sc, int32_t base,
@@ -2110,7 +1876,7 @@ static void launch_destinations(const DevGraph& g, const Buckets& b, const Score
     }
   }
   LCC_ENUM(3, (k_enum_grp<32><<<grp_blocks(b, b.count[3], 32), BLOCK, 0, st>>>(L + b.off[3], b.count[3], g, C, W, sc, pa, pb, strict, vs, slot, pass, S, co, cp(3))))
-  LCC_ENUM(4, (k_enum_wave<LDS_SLOTS_B4><<<grp_blocks(b, b.count[4], WAVE), BLOCK, 0, st>>>(L + b.off[4], b.count[4], g, C, W, sc, pa, pb, strict, vs, slot, pass, S, co, cp(4), b.hash_shift)))
+  LCC_ENUM(4, (k_enum_wave<<<grp_blocks(b, b.count[4], WAVE), BLOCK, 0, st>>>(L + b.off[4], b.count[4], g, C, W, sc, pa, pb, strict, vs, slot, pass, S, co, cp(4))))
   LCC_ENUM(5, (k_enum_blk<128, LDS_SLOTS_B5><<<vtx_blocks(b, b.count[5]), 128, 0, st>>>(L + b.off[5], b.count[5], g, C, W, sc, pa, pb, strict, vs, slot, pass, S, co, cp(5), b.hash_shift)))
   // bucket 6: rows up to B6_SPLIT on 512 threads and an 8192-slot table; when a tuning raises the bucket's
   // bound, the longer rows (the tail of the bucket's list) on 1024 threads and a 16384-slot table
