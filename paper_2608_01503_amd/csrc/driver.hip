@@ -21,6 +21,7 @@
 
 #include "../../include/lcc.h"
 #include "common.h"
+#include "team.h"
 
 using namespace lcc;
 
@@ -80,6 +81,7 @@ struct WS {
   int64_t *seg0, *seg1;  // contraction: entries per coarse row (then the rows' cursors) and the rows' starts
   Tagged tg;      // free-id marks and single-pass scan state (zeroed when the workspace is allocated)
   int64_t* stripes;  // per-workgroup counter partials (zeroed when the workspace is allocated)
+  TeamHost team;     // control blocks of the team launches (zeroed when the workspace is allocated)
   void* scan_temp;
 };
 
@@ -125,6 +127,8 @@ size_t carve(WS& w, char* base, int64_t n, int64_t nnz) {
   w.tg.status = c.take<unsigned long long>(w.tg.status_cap);
   w.tg.ticket = c.take<uint32_t>(1);
   w.stripes = c.take<int64_t>((int64_t)NSTRIPE * STRIPE_W);
+  w.team = TeamHost{};
+  w.team.ctl = c.take<TeamCtl>(TEAM_SLOTS);
   w.scan_temp = c.take<char>((int64_t)scan_temp_bytes(M + 1));
   return c.off;
 }
@@ -273,6 +277,7 @@ struct lcc_ctx {
     hip_check(hipMemsetAsync(w.tg.status, 0, (size_t)w.tg.status_cap * sizeof(unsigned long long), st), "workspace");
     hip_check(hipMemsetAsync(w.tg.ticket, 0, sizeof(uint32_t), st), "workspace");
     hip_check(hipMemsetAsync(w.stripes, 0, (size_t)NSTRIPE * STRIPE_W * sizeof(int64_t), st), "workspace");
+    hip_check(hipMemsetAsync(w.team.ctl, 0, TEAM_SLOTS * sizeof(TeamCtl), st), "workspace");
     hip_check(hipStreamSynchronize(st), "workspace");
     // tags are result-neutral; LCC_TAG_BASE starts their sequence elsewhere (tests use it to reach the
     // wrap-around, which otherwise takes billions of passes)
@@ -344,6 +349,7 @@ void prof_end(int family, double bytes, hipStream_t st) {
   c->prof_recs.push_back({family, c->prof_open[family], e, bytes});
   c->prof_open[family] = nullptr;
 }
+bool prof_on() { return g_prof_ctx != nullptr; }
 void device_check(hipError_t e, const char* what) { hip_check(e, what); }
 }  // namespace lcc
 
@@ -555,22 +561,33 @@ struct Run {
     return P;
   }
 
+  // a level small enough for the team launches (single graphs; kernel timing measures the bucket kernels)
+  bool small(const Level& L) const { return !G && team_level(L.g.n, L.g.nnz) && !prof_on(); }
+
   // LocalMovePasses on level l from L.C (or singletons); result in L.C.  Returns the slot used.
+  // A single graph's labels are also ranked (w.rank), their number stored in the slot.
   int local_move_level(int l, bool singleton, int phase, const Buckets* only = nullptr) {
     Level& L = lv[l];
     if (nslot >= NSLOT) fail(LCC_ERR_INVALID, "too many local-move calls");
     int s = nslot++;
     rec(-1, l, phase, 0, s, 0, 0, 0);  // marker: the pass records of slot s go here
     LMBuffers B = bufs();
+    if (small(L)) {
+      team_local_move_launch(L.g, L.b, lm_params(L, phase == 0), singleton, B, L.C, w.used, w.rank, w.team, w.slots + s, st);
+      return s;
+    }
     if (!singleton) copy_i32(w.C, L.C, L.g.n, st);
     local_move(L.g, only ? *only : L.b, lm_params(L, phase == 0), singleton, B, w.slots + s, w.ctrl, st);
     copy_i32(L.C, w.Cout, L.g.n, st);
+    if (!G) rank_labels(L.C, L.g.n, &w.slots[s].nlab);
     return s;
   }
 
-  LMSlot read_slot(int s) {
+  // statistics of slot s, a local move on a level of n vertices (its label count must be possible)
+  LMSlot read_slot(int s, int64_t n) {
     hip_check(hipMemcpyAsync(ctx->h_slots + s, w.slots + s, sizeof(LMSlot), hipMemcpyDeviceToHost, st), "slot");
     sync("slot");
+    if (ctx->h_slots[s].nlab < 1 || ctx->h_slots[s].nlab > n) fail(LCC_ERR_DEVICE, "internal: a local move left no clustering");
     return ctx->h_slots[s];
   }
 
@@ -708,8 +725,7 @@ struct Run {
     for (;;) {
       int s = local_move_level(l, !(l == 0 && init), 0);
       Level& L = lv[l];
-      rank_labels(L.C, L.g.n, &w.slots[s].nlab);
-      LMSlot S = read_slot(s);
+      LMSlot S = read_slot(s, L.g.n);
       const int64_t nc = S.nlab;
       rec(2, l, 0, 0, L.g.n, L.g.nnz, nc, S.Nbest);
       if (nc == L.g.n) break;
@@ -723,8 +739,7 @@ struct Run {
       launch_project(lv[k + 1].C, L.map, L.g.n, L.C, st);
       if (plus) {
         int s = local_move_level(k, false, 1);
-        rank_labels(L.C, L.g.n, &w.slots[s].nlab);
-        LMSlot S = read_slot(s);
+        LMSlot S = read_slot(s, L.g.n);
         const int64_t nc = S.nlab;
         rec(2, k, 1, 0, L.g.n, L.g.nnz, nc, S.Nbest);
       }
@@ -808,9 +823,8 @@ struct Run {
       const int64_t n = L.g.n;
       int s = local_move_level(l, singleton, 0);
       singleton = false;
-      rank_labels(L.C, n, &w.slots[s].nlab);  // the count of C_l, unless the alternate move below changes it
-      LMSlot S = read_slot(s);
-      int64_t nc = S.nlab;
+      LMSlot S = read_slot(s, n);
+      int64_t nc = S.nlab;  // the count of C_l, unless the alternate move below changes it
       int64_t N = S.Nbest;
       if (S.Nbest == S.N0) {
         // C_l unchanged by the local move: the alternate local move (Sec. V-A) from C_l
@@ -871,8 +885,7 @@ struct Run {
       launch_project(lv[k + 1].C, L.map, L.g.n, L.C, st);
       if (plus) {
         int s = local_move_level(k, false, 1);
-        rank_labels(L.C, L.g.n, &w.slots[s].nlab);
-        LMSlot S = read_slot(s);
+        LMSlot S = read_slot(s, L.g.n);
         const int64_t nc = S.nlab;
         rec(2, k, 1, 0, L.g.n, L.g.nnz, nc, S.Nbest);
       }
@@ -1309,6 +1322,7 @@ lcc_status cluster_impl(lcc_ctx* ctx, const lcc_graph* g, lcc_lambda lam, lcc_va
     zero_bytes(w.tg.status, (size_t)w.tg.status_cap * sizeof(unsigned long long), st);
     zero_bytes(w.tg.ticket, sizeof(uint32_t), st);
     zero_bytes(w.stripes, (size_t)NSTRIPE * STRIPE_W * sizeof(int64_t), st);
+    zero_bytes(w.team.ctl, TEAM_SLOTS * sizeof(TeamCtl), st);
     w.tg.last = 0;
   }
   ctx->pool_reset();

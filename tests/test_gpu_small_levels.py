@@ -1,0 +1,54 @@
+"""Small levels run in one launch of a team of workgroups; with kernel timing on, the same calls take the per-bucket
+launches.  Labels, exact objective, levels, flags and the whole trace must be the same on both routes: every row
+length around the edges of the team's row kernels, the smallest graphs, and entry counts around the size limit."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import graphgen as gg
+import oracle as O
+from tests import gpu_util as U
+
+pytestmark = pytest.mark.gpu
+MOD, CPM = ((1, 1, True), O.VW_WEIGHTED_DEGREE), ((1, 20, False), O.VW_UNIT)
+
+
+def _rows(lengths, n, seed):
+    """A graph with one row of each given length (more or less) over sparse random edges."""
+    rng = np.random.default_rng(seed)
+    pairs = [np.stack([np.full(d, i), rng.choice(np.arange(len(lengths), n), size=d, replace=False)], axis=1)
+             for i, d in enumerate(lengths)]
+    pairs.append(rng.integers(0, n, size=(2 * n, 2)))
+    P = np.concatenate(pairs)
+    return gg.from_pairs(n, P, rng.integers(1, 50, size=len(P)), name="rows")
+
+
+GRAPHS = {
+    "rows": lambda: _rows([3, 4, 5, 8, 9, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 511, 512, 513, 1024, 1025], 3000, 1),
+    "long rows": lambda: _rows([4096, 4097, 8191, 8192, 8193, 9500], 40000, 2),
+    "pair": lambda: gg.from_pairs(2, [(0, 1)]),
+    "star": lambda: gg.from_pairs(1026, [(0, i) for i in range(1, 1026)]),
+    "limit": lambda: gg.random_gnp(1500, 0.1165, 3, w_max=3),  # about 2^18 entries
+    "above limit": lambda: gg.random_gnp(1500, 0.119, 3, w_max=3),
+}
+
+
+@pytest.mark.parametrize("name", GRAPHS)
+@pytest.mark.parametrize("variant", [O.PLOUVAIN, O.PLEIDEN, O.PLEIDEN_PLUS, O.LOUVAIN])
+def test_team_equals_bucket_launches(name, variant):
+    import paper_2608_01503_amd as L
+    g = GRAPHS[name]()
+    buckets = L.Context(0)
+    buckets.profile_enable(["single"])
+    team = L.Context(0)
+    opts = [{}, dict(pass_limit=3), dict(symmetry=2, phases=((0, 1, 6),)), dict(pass_limit=0)]
+    for (lam, mode), kw in [(MOD, opts[0]), (CPM, opts[0]), (CPM, opts[1]), (MOD, opts[2]), (MOD, opts[3])]:
+        dev = U.device_graph(g, mode)
+        got = [c.cluster(dev, lam, variant, L.lcc_default_options(**kw), trace_capacity=1 << 14) for c in (buckets, team)]
+        (la, a), (lb, b) = got
+        assert np.array_equal(la.cpu().numpy(), lb.cpu().numpy()), (name, lam, kw)
+        assert (a.N, a.num_clusters, a.levels, a.flags) == (b.N, b.num_clusters, b.levels, b.flags)
+        assert np.array_equal(a.trace, b.trace)
+    buckets.close()
+    team.close()
