@@ -91,6 +91,9 @@ struct LMSlot {
   int64_t Nbest;                // objective numerator of C_out
   int64_t N0;                   // objective numerator of the starting clustering
   int64_t nlab;                 // distinct labels of the clustering the driver ranked after the call
+  // a team launch that went on to the next level (team.h)
+  int64_t refined, refine_n, refine_U, refine_m, cycle;
+  int64_t coarse, coarse_nnz, coarse_w2, coarse_boff[NBUCKET + 1];
 };
 
 // Scalars shared by the driver and the kernels.
@@ -481,10 +484,8 @@ struct TeamHost {
 // 470,000 entries (kNN, 20,000 vertices) 0.72 against 0.35 ms.
 constexpr int64_t TEAM_ENTRIES = (int64_t)1 << 18;
 inline bool team_level(int64_t n, int64_t nnz) { return nnz <= TEAM_ENTRIES && n <= TEAM_ENTRIES / 4; }
-// local_move, from the clustering in C (or from singletons) and back into C, with its labels ranked (rank, and
-// their number in slot->nlab).
-void team_local_move_launch(const DevGraph& g, const Buckets& b, const LMParams& prm, bool singleton, LMBuffers& bufs,
-                            int32_t* C, uint8_t* used, int32_t* rank, TeamHost& th, LMSlot* slot, hipStream_t st);
+struct TeamArgs;
+void team_launch(TeamArgs& a, TeamHost& h, hipStream_t st);
 
 // contract.hip
 // used flags of labels -> rank (compact map) : rank[c] for c in [0, n), count at rank[n].

@@ -397,6 +397,8 @@ struct Level {
   int64_t* sumw2g = nullptr;
   // constraint clustering of the level's vertices (constrained Louvain+ coarsening), or null
   int32_t* B = nullptr;
+  bool staged = false;  // built by a team launch and still in the stage; the next one puts it in place
+  bool hubs = true;     // the hub chunks of b are there
 };
 
 __global__ void k_reset_level_counters(Ctrl* c) {
@@ -564,18 +566,96 @@ struct Run {
   // a level small enough for the team launches (single graphs; kernel timing measures the bucket kernels)
   bool small(const Level& L) const { return !G && team_level(L.g.n, L.g.nnz) && !prof_on(); }
 
-  // LocalMovePasses on level l from L.C (or singletons); result in L.C.  Returns the slot used.
-  // A single graph's labels are also ranked (w.rank), their number stored in the slot.
-  int local_move_level(int l, bool singleton, int phase, const Buckets* only = nullptr) {
+  // A team launch on level l.  With TEAM_CONTRACT it leaves the next level in the stage (arrays of the workspace that
+  // no later phase before the next launch uses) and the sizes in the slot, for adopt().
+  void team(int l, int32_t steps, bool singleton, bool constrained, int s) {
+    Level& L = lv[l];
+    const LMParams P = lm_params(L, constrained);
+    TeamArgs a{};
+    if (L.staged) steps |= TEAM_PLACE;
+    a.steps = steps;
+    a.n = (int32_t)L.g.n;
+    a.off = const_cast<int64_t*>(L.g.off); a.idx = const_cast<int32_t*>(L.g.idx); a.w = const_cast<int32_t*>(L.g.w);
+    a.vw = const_cast<int64_t*>(L.g.vw);
+    a.list = const_cast<int32_t*>(L.b.list);
+    for (int k = 0; k <= NBUCKET; ++k) a.boff[k] = (int32_t)L.b.off[k];
+    a.hash_shift = L.b.hash_shift;
+    a.bounds = ctx->bounds();
+    a.sc = sc;
+    a.cons = P.cons;
+    a.C = w.C; a.Cout = L.C; a.W = w.W; a.cnt = w.scan_a; a.vs = w.vs; a.empty = w.empty;
+    a.freelist = w.freelist; a.movers = w.scan_b;
+    a.sum_w2 = L.sum_w2;
+    a.singleton = singleton ? 1 : 0;
+    a.pass_limit = P.pass_limit;
+    a.symmetry = P.symmetry;
+    for (int i = 0; i <= MAX_PASSES; ++i) { a.phi_num[i] = P.phi_num[i]; a.phi_den[i] = P.phi_den[i]; }
+    a.slot = w.slots + s;
+    a.used = w.used; a.rank = w.rank;
+    if (steps & TEAM_PROJECT) a.up_C = lv[l + 1].C;
+    a.map = L.map;
+    a.B = L.B;
+    a.st.raw = w.k0; a.st.seg = w.k1; a.st.end = w.cnt; a.st.start = (int32_t*)w.v0; a.st.cnt = (int32_t*)w.v1;
+    a.st.off = w.ux; a.st.list = w.fail; a.st.rows = w.alt_list; a.st.map = w.uid; a.st.B = w.tsz; a.st.C = w.H;
+    a.st.vw = w.seg0;
+    if (steps & TEAM_PLACE) {
+      a.n_fine = (int32_t)lv[l - 1].g.n;
+      a.map_place = lv[l - 1].map;
+      a.B_place = L.B;
+    }
+    a.seed = seed_stream(o.seed, refine_calls);
+    a.WB = w.WB; a.aB = w.aB; a.aX = w.aX; a.inU = w.inU; a.flip = w.flip; a.has_child = w.has_child;
+    a.H = w.H; a.par = w.par; a.par2 = w.pos_of; a.root = w.root; a.rel = w.fail; a.tsz = w.tsz; a.toff = w.tree_sz;
+    a.trees = w.alt_list; a.R = w.in_labels; a.rankR = w.scan_b;
+    a.keys = w.k0;
+    team_launch(a, w.team, st);
+    L.staged = false;
+  }
+
+  // Level l + 1 of nc vertices, which a team launch on level l has left in the stage.
+  void adopt(int l, const LMSlot& S, int64_t nc) {
+    Level N;
+    lv[l].map = take<int32_t>(ctx, lv[l].g.n);
+    if (lv[l].B) N.B = take<int32_t>(ctx, nc);
+    level_begin(l + 1);
+    N.g.n = nc;
+    N.g.nnz = S.coarse_nnz;
+    N.g.off = level_take<int64_t>(nc + 1);
+    N.g.vw = level_take<int64_t>(nc);
+    N.g.idx = level_take<int32_t>(N.g.nnz);
+    N.g.w = level_take<int32_t>(N.g.nnz);
+    N.C = take<int32_t>(ctx, nc);
+    N.sum_w2 = S.coarse_w2;
+    N.b.list = level_take<int32_t>(nc);
+    N.b.hub_chunk_off = level_take<int32_t>(nc + 1);
+    for (int k = 0; k <= NBUCKET; ++k) N.b.off[k] = S.coarse_boff[k];
+    N.b.hash_shift = ctx->tune.hash_shift;
+    N.staged = true;
+    N.hubs = false;
+    lv.push_back(N);
+  }
+
+  // the whole bucket description of a level that a team launch has built, for the launches per bucket
+  void full_buckets(Level& L) {
+    if (L.hubs) return;
+    prepare(L, const_cast<int32_t*>(L.b.list), const_cast<int32_t*>(L.b.hub_chunk_off));
+    L.hubs = true;
+  }
+
+  // LocalMovePasses on level l from L.C (or singletons, or with TEAM_PROJECT in `more` from the next level's
+  // clustering); result in L.C.  Returns the slot used.  A single graph's labels are also ranked (w.rank), their
+  // number stored in the slot.  `more`: what a team launch does besides.
+  int local_move_level(int l, bool singleton, int phase, const Buckets* only = nullptr, int32_t more = 0) {
     Level& L = lv[l];
     if (nslot >= NSLOT) fail(LCC_ERR_INVALID, "too many local-move calls");
     int s = nslot++;
     rec(-1, l, phase, 0, s, 0, 0, 0);  // marker: the pass records of slot s go here
-    LMBuffers B = bufs();
     if (small(L)) {
-      team_local_move_launch(L.g, L.b, lm_params(L, phase == 0), singleton, B, L.C, w.used, w.rank, w.team, w.slots + s, st);
+      team(l, TEAM_MOVE | more, singleton, phase == 0, s);
       return s;
     }
+    if (more & TEAM_PROJECT) launch_project(lv[l + 1].C, L.map, L.g.n, L.C, st);
+    LMBuffers B = bufs();
     if (!singleton) copy_i32(w.C, L.C, L.g.n, st);
     local_move(L.g, only ? *only : L.b, lm_params(L, phase == 0), singleton, B, w.slots + s, w.ctrl, st);
     copy_i32(L.C, w.Cout, L.g.n, st);
@@ -723,28 +803,34 @@ struct Run {
     int l = 0;
     if (init) copy_i32(lv[0].C, init, lv[0].g.n, st);
     for (;;) {
-      int s = local_move_level(l, !(l == 0 && init), 0);
+      const bool cap = l + 1 >= o.max_levels;
+      int s = local_move_level(l, !(l == 0 && init), 0, nullptr, cap ? 0 : TEAM_CONTRACT);
       Level& L = lv[l];
       LMSlot S = read_slot(s, L.g.n);
       const int64_t nc = S.nlab;
       rec(2, l, 0, 0, L.g.n, L.g.nnz, nc, S.Nbest);
       if (nc == L.g.n) break;
-      if (l + 1 >= o.max_levels) { flags |= LCC_FLAG_LEVEL_CAP; break; }
-      contract(l, lv[l].C, nc);
+      if (cap) { flags |= LCC_FLAG_LEVEL_CAP; break; }
+      if (S.coarse) adopt(l, S, nc);
+      else contract(l, lv[l].C, nc);
       ++l;
     }
-    int top = l;
+    uncoarsen(l, plus);
+    return l;
+  }
+
+  // From the clustering of level `top` back to level 0, with a local move on every level in the + variants (their
+  // records are filled in once the slots are read).
+  void uncoarsen(int top, bool plus) {
     for (int k = top - 1; k >= 0; --k) {
       Level& L = lv[k];
-      launch_project(lv[k + 1].C, L.map, L.g.n, L.C, st);
-      if (plus) {
-        int s = local_move_level(k, false, 1);
-        LMSlot S = read_slot(s, L.g.n);
-        const int64_t nc = S.nlab;
-        rec(2, k, 1, 0, L.g.n, L.g.nnz, nc, S.Nbest);
+      if (!plus) {
+        launch_project(lv[k + 1].C, L.map, L.g.n, L.C, st);
+        continue;
       }
+      const int s = local_move_level(k, false, 1, nullptr, TEAM_PROJECT);
+      rec(-2, k, 1, 0, L.g.n, L.g.nnz, s, 0);
     }
-    return top;
   }
 
   // ---------------------------------------------------------------------------------------------------
@@ -821,13 +907,15 @@ struct Run {
     for (;;) {
       Level& L = lv[l];
       const int64_t n = L.g.n;
-      int s = local_move_level(l, singleton, 0);
+      const bool cap = l + 1 >= o.max_levels;
+      int s = local_move_level(l, singleton, 0, nullptr, cap ? 0 : TEAM_REFINE | TEAM_CONTRACT);
       singleton = false;
       LMSlot S = read_slot(s, n);
       int64_t nc = S.nlab;  // the count of C_l, unless the alternate move below changes it
       int64_t N = S.Nbest;
       if (S.Nbest == S.N0) {
         // C_l unchanged by the local move: the alternate local move (Sec. V-A) from C_l
+        full_buckets(L);
         LMBuffers B = bufs();
         copy_i32(w.C, L.C, n, st);
         launch_cluster_weights(w.C, L.g.vw, n, w.W, st);
@@ -846,32 +934,45 @@ struct Run {
         ctx->pool_release(mark);
         N = q * ctx->h_ctrl->obj_I - p * (ctx->h_ctrl->obj_SW2 - L.sum_w2);
         rec(3, l, 0, 0, ctx->h_ctrl->lmalt_k, ctx->h_ctrl->lmalt_best_k, N, 0);
+        if (small(L) && nc < n && !cap) {
+          team(l, TEAM_REFINE | TEAM_CONTRACT, false, false, s2);
+          S = read_slot(s2, n);
+        }
       }
       rec(2, l, 0, 0, n, L.g.nnz, nc, N);
       if (nc == n) break;
-      if (l + 1 >= o.max_levels) { flags |= LCC_FLAG_LEVEL_CAP; break; }
+      if (cap) { flags |= LCC_FLAG_LEVEL_CAP; break; }
       // refinement R of B = C_l; compaction of B for the downsampled clustering
       int32_t* R = w.in_labels;
-      RefineBuffers rb = rbufs();
-      {
+      int64_t nR, nU, nT;
+      if (S.refined) {
+        nR = S.refine_n; nU = S.refine_U; nT = S.refine_m;
+        if (S.cycle) fail(LCC_ERR_DEVICE, "refinement produced a parent cycle");
+      } else {
+        RefineBuffers rb = rbufs();
         const auto mk = ctx->pool_mark();  // the refinement's sort scratch is released right after
         RefSrc rs;
         rs.s = sc;
         rs.st = seed_stream(o.seed, refine_calls);
         refine(L.g, L.b, rs, L.C, R, rb, w.ctrl, [&](size_t by) { return ctx->pool_take(by); }, st);
         ctx->pool_release(mk);
+        rank_labels(R, n, &w.ctrl->nlab);
+        read_ctrl("refine");
+        nR = ctx->h_ctrl->nlab; nU = ctx->h_ctrl->refine_U; nT = ctx->h_ctrl->refine_m;
+        if (ctx->h_ctrl->err_bits & ERRB_INTERNAL) fail(LCC_ERR_DEVICE, "refinement produced a parent cycle");
       }
-      rank_labels(R, n, &w.ctrl->nlab);
-      read_ctrl("refine");
-      const int64_t nR = ctx->h_ctrl->nlab;
-      if (ctx->h_ctrl->err_bits & ERRB_INTERNAL) fail(LCC_ERR_DEVICE, "refinement produced a parent cycle");
-      rec(4, l, 0, 0, nR, (int64_t)refine_calls, ctx->h_ctrl->refine_U, ctx->h_ctrl->refine_m);
+      rec(4, l, 0, 0, nR, (int64_t)refine_calls, nU, nT);
       ++refine_calls;
       if (nR == n) {
         if (++noprog >= 3) { flags |= LCC_FLAG_REFINE_NO_PROGRESS; break; }
         continue;  // the same level again with the next refinement seed
       }
       noprog = 0;
+      if (S.coarse) {
+        adopt(l, S, nR);  // with C_{l+1}
+        ++l;
+        continue;
+      }
       contract(l, R, nR);
       // Downsample: C_{l+1}[x] = compact(C_l)[C_l[v]] for any v in x
       Level& L2 = lv[l];
@@ -879,18 +980,8 @@ struct Run {
       launch_downsample(L2.C, w.rank, L2.map, n, lv[l + 1].C, st);
       ++l;
     }
-    int top = l;
-    for (int k = top - 1; k >= 0; --k) {
-      Level& L = lv[k];
-      launch_project(lv[k + 1].C, L.map, L.g.n, L.C, st);
-      if (plus) {
-        int s = local_move_level(k, false, 1);
-        LMSlot S = read_slot(s, L.g.n);
-        const int64_t nc = S.nlab;
-        rec(2, k, 1, 0, L.g.n, L.g.nnz, nc, S.Nbest);
-      }
-    }
-    return top;
+    uncoarsen(l, plus);
+    return l;
   }
 
   // ---------------------------------------------------------------------------------------------------
@@ -1382,6 +1473,12 @@ lcc_status cluster_impl(lcc_ctx* ctx, const lcc_graph* g, lcc_lambda lam, lcc_va
     R.emit_pass_records();
     std::vector<int64_t> out;
     for (size_t r = 0; r + 8 <= R.trace.size(); r += 8) {
+      if (R.trace[r] == -2) {  // level record of an uncoarsening local move
+        const LMSlot& S = ctx->h_slots[R.trace[r + 6]];
+        int64_t rr[8] = {2, R.trace[r + 1], 1, 0, R.trace[r + 4], R.trace[r + 5], S.nlab, S.Nbest};
+        out.insert(out.end(), rr, rr + 8);
+        continue;
+      }
       if (R.trace[r] != -1) {
         out.insert(out.end(), R.trace.begin() + r, R.trace.begin() + r + 8);
         continue;

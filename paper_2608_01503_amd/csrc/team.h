@@ -25,7 +25,7 @@ constexpr int TEAM_WAVES = TEAM_BLOCK / WAVE;
 constexpr int TEAM_MAX = 32;                // members: the CUs of an XCD
 constexpr int TEAM_GRID = 8 * TEAM_MAX;     // workgroups launched (they spread over the XCDs in turn)
 constexpr unsigned long long TEAM_WAIT = 300;  // 3 us of the 100 MHz clock
-constexpr int TEAM_VALS = 4;                // values summed at one boundary
+constexpr int TEAM_VALS = 6;                // values summed at one boundary
 constexpr int TEAM_SLOTS = 2;               // control blocks: a launch uses one and clears the next launch's
 
 // One launch's control block (zero when the launch starts).
@@ -39,6 +39,66 @@ struct TeamCtl {
   alignas(128) uint64_t word[2][TEAM_MAX][2 * TEAM_VALS];
 };
 constexpr uint32_t TEAM_CLOSED = 0x80000000u;
+
+// What a launch does, in this order.
+enum : int32_t {
+  TEAM_PLACE = 1,     // put the coarse level that an earlier launch left in the stage into the level's arrays
+  TEAM_PROJECT = 2,   // start from the next level's clustering
+  TEAM_MOVE = 4,      // LocalMovePasses
+  TEAM_REFINE = 8,    // refinement; the contraction goes by it
+  TEAM_CONTRACT = 16  // build the next level in the stage
+};
+
+// Arguments of a team launch on one level.
+struct TeamArgs {
+  TeamCtl* ctl;
+  TeamCtl* next;
+  int32_t steps;
+  int32_t n;
+  int64_t* off;                 // the level's graph; a launch that places it fills the arrays
+  int32_t* idx;
+  int32_t* w;
+  int64_t* vw;
+  int32_t* list;                // vertices by degree bucket, bucket b at [boff[b], boff[b + 1])
+  int32_t boff[NBUCKET + 1];
+  int32_t hash_shift;
+  BucketBounds bounds;
+  Score sc;
+  const int32_t* cons;          // constraint of the local move
+  int32_t* C;
+  int32_t* Cout;
+  int64_t* W;
+  int32_t* cnt;                 // members of every cluster id
+  VState* vs;
+  uint8_t* empty;
+  int32_t *freelist, *movers;
+  int64_t sum_w2;
+  int32_t singleton, pass_limit, symmetry;
+  uint32_t phi_num[MAX_PASSES + 1], phi_den[MAX_PASSES + 1];
+  LMSlot* slot;
+  uint8_t* used;
+  int32_t* rank;                // of the labels in Cout
+  // uncoarsening: the next level's clustering, Cout[v] = up_C[map[v]]
+  const int32_t* up_C;
+  // next level
+  const int32_t* map;
+  const int32_t* B;             // inherited by the coarse vertices
+  // the stage, and where a placed level's map from the finer level (of n_fine vertices) and constraint go
+  struct {
+    uint64_t *raw, *seg;        // entries (neighbour << 32 | weight) as collected, and summed ascending
+    int32_t *end, *start;       // row x: collected at [start[x], end[x])
+    int32_t *cnt, *off, *list, *rows, *map, *B, *C;
+    int64_t* vw;
+  } st;
+  int32_t n_fine;
+  int32_t *map_place, *B_place;
+  // refinement
+  uint64_t seed;                // s_t
+  int64_t *WB, *aB, *aX;
+  uint8_t *inU, *flip, *has_child;
+  int32_t *H, *par, *par2, *root, *rel, *tsz, *toff, *trees, *R, *rankR;
+  uint64_t* keys;
+};
 
 #ifndef TEAM_KERNARG
 #define TEAM_KERNARG __attribute__((address_space(4)))
@@ -66,24 +126,48 @@ __device__ __forceinline__ int64_t uniform64(int64_t x) {
   return (int64_t)((uint64_t)hi << 32 | lo);
 }
 
-// Sum over the 64 lanes of a fully active wavefront, returned to every lane: the row scan and row broadcasts of
-// wave_sum_u32 on both halves, no LDS round trips.
+// The row scan and row broadcasts of wave_sum_u32 on both halves, no LDS round trips.
 template <int CTRL, int ROWS>
 __device__ __forceinline__ int64_t dpp64(int64_t x) {
   const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(uint64_t)x, CTRL, ROWS, 0xf, false);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)((uint64_t)x >> 32), CTRL, ROWS, 0xf, false);
   return (int64_t)((uint64_t)hi << 32 | lo);
 }
-__device__ __forceinline__ int64_t wave_sum64(int64_t x) {
+// Inclusive sums over the lanes of groups of G = 16 or 64 (the whole, fully active wavefront).
+template <int G>
+__device__ __forceinline__ int64_t scan64(int64_t x) {
   x += dpp64<0x111, 0xf>(x);
   x += dpp64<0x112, 0xf>(x);
   x += dpp64<0x114, 0xf>(x);
   x += dpp64<0x118, 0xf>(x);
-  x += dpp64<0x142, 0xa>(x);
-  x += dpp64<0x143, 0xc>(x);
+  if constexpr (G == WAVE) {
+    x += dpp64<0x142, 0xa>(x);
+    x += dpp64<0x143, 0xc>(x);
+  }
+  return x;
+}
+__device__ __forceinline__ uint32_t wave_scan32(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);
+  return x;
+}
+__device__ __forceinline__ int64_t wave_sum64(int64_t x) {
+  x = scan64<WAVE>(x);
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(uint64_t)x, 63);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)x >> 32), 63);
   return (int64_t)((uint64_t)hi << 32 | lo);
+}
+
+// This thread's number within its workgroup, recomputed in every phase (values derived from it are not kept
+// across phases).
+__device__ __forceinline__ int team_tx() {
+  int x = threadIdx.x;
+  asm volatile("" : "+v"(x));
+  return x;
 }
 
 struct TeamShared {
@@ -92,12 +176,15 @@ struct TeamShared {
   int64_t pre[TEAM_VALS];
   uint32_t wsum[TEAM_WAVES];
   uint32_t rank, n;
+  int32_t cursor[9];   // lists by class: this member's next place in every class
+  int32_t first[10];   // class c at [first[c], first[c + 1])
 };
 __shared__ TeamShared team_sh;
 
 struct Sum1 { int64_t a; };
 struct Sum2 { int64_t a, b; };
 struct Sum3 { int64_t a, b, c; };
+struct Sum6 { int64_t a, b, c, d, e, f; };
 
 struct Team {
   TeamCtl* c;
@@ -141,7 +228,7 @@ struct Team {
   // member's; got[k] = word k of member `lane`.
   template <int K>
   __device__ __forceinline__ void exchange(uint32_t mine, uint32_t (&got)[K]) {
-    const int lane = threadIdx.x;
+    const int lane = team_tx();
     uint64_t(*w)[2 * TEAM_VALS] = c->word[epoch & 1];
     if (lane < K) ast(&w[rank][lane], (uint64_t)epoch << 32 | mine);
     const int from = lane < n ? lane : 0;
@@ -162,7 +249,7 @@ struct Team {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     ++epoch;
-    if (threadIdx.x < WAVE) {
+    if (team_tx() < WAVE) {
       uint32_t got[1];
       exchange<1>(0, got);
     }
@@ -180,15 +267,16 @@ struct Team {
   template <int K>
   __device__ __forceinline__ void put(int64_t x) {
     const int64_t s = wave_sum64(x);
-    if ((threadIdx.x & (WAVE - 1)) == 0) team_sh.red[K][threadIdx.x / WAVE] = s;
+    const int tx = team_tx();
+    if ((tx & (WAVE - 1)) == 0) team_sh.red[K][tx / WAVE] = s;
   }
   template <int K>
   __device__ __forceinline__ void sums() {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     ++epoch;
-    if (threadIdx.x < WAVE) {
-      const int lane = threadIdx.x;
+    if (team_tx() < WAVE) {
+      const int lane = team_tx();
       int64_t s = 0;  // lanes 2k and 2k + 1: this member's sum of value k
       if (lane < 2 * K) {
 #pragma unroll
@@ -229,6 +317,15 @@ struct Team {
     return r;
   }
   // The same, and the sums over the members of lower rank.
+  __device__ __forceinline__ Sum6 sum(int64_t a, int64_t b, int64_t d, int64_t e, int64_t f, int64_t g, Sum6& pre) {
+    put<0>(a); put<1>(b); put<2>(d); put<3>(e); put<4>(f); put<5>(g);
+    sums<6>();
+    const int64_t *s = team_sh.tot, *p = team_sh.pre;
+    Sum6 r{uniform64(s[0]), uniform64(s[1]), uniform64(s[2]), uniform64(s[3]), uniform64(s[4]), uniform64(s[5])};
+    pre = Sum6{uniform64(p[0]), uniform64(p[1]), uniform64(p[2]), uniform64(p[3]), uniform64(p[4]), uniform64(p[5])};
+    __syncthreads();
+    return r;
+  }
   __device__ __forceinline__ Sum1 sum(int64_t a, Sum1& pre) {
     put<0>(a);
     sums<1>();
@@ -249,17 +346,12 @@ struct Team {
 
   // Exclusive prefix of x over the threads of this workgroup; *total = its sum.
   __device__ __forceinline__ uint32_t block_excl(uint32_t x, uint32_t& total) {
-    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
-    uint32_t inc = x;
-#pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) {
-      const uint32_t y = __shfl_up(inc, o, WAVE);
-      if (lane >= o) inc += y;
-    }
+    const int tx = team_tx(), lane = tx & (WAVE - 1), wv = uniform32(tx / WAVE);
+    const uint32_t inc = wave_scan32(x);
     if (lane == WAVE - 1) team_sh.wsum[wv] = inc;
     __syncthreads();
     uint32_t before = 0, tot = 0;
-#pragma unroll
+#pragma unroll 4
     for (int w = 0; w < TEAM_WAVES; ++w) {
       const uint32_t s = team_sh.wsum[w];
       if (w < wv) before += s;
@@ -270,19 +362,69 @@ struct Team {
     return before + inc - x;
   }
 
+  // Lists by class, and offsets: f(i, class, size) gives item i < m its class (0 .. K - 1, -1: none) and size.
+  // off[i] = the sizes of the items before i (off[m] = their sum); list = the items, class after class, class c at
+  // team_sh.first[c].  Returns the sum of the sizes and of `extra`.  The arrays are there after the next boundary.
+  template <int K, typename F>
+  __device__ __forceinline__ Sum2 lists(int m, int32_t* off, int32_t* list, int64_t extra, F f) {
+    static_assert(K <= 9, "counts of 21 bits, three to a word");
+    const int tx = team_tx(), lo = share_lo(m), hi = share_hi(m);
+    int64_t s = 0;
+    uint64_t c0 = 0, c1 = 0, c2 = 0;
+    for (int i = lo + tx; i < hi; i += TEAM_BLOCK) {
+      int cls = -1, size = 0;
+      f(i, cls, size);
+      s += size;
+      if (K > 0 && cls >= 0) {
+        const uint64_t one = 1ull << (21 * (cls % 3));
+        c0 += cls < 3 ? one : 0;
+        c1 += cls >= 3 && cls < 6 ? one : 0;
+        c2 += cls >= 6 ? one : 0;
+      }
+    }
+    Sum6 pre;
+    const Sum6 tot = sum(s, (int64_t)c0, (int64_t)c1, (int64_t)c2, extra, 0, pre);
+    if (K > 0 && tx < K) {
+      int at = 0;
+#pragma unroll
+      for (int c = 0; c < K; ++c) {
+        const int64_t t3 = c < 3 ? tot.b : c < 6 ? tot.c : tot.d, p3 = c < 3 ? pre.b : c < 6 ? pre.c : pre.d;
+        const int num = (int)((uint64_t)t3 >> (21 * (c % 3)) & 0x1FFFFF), low = (int)((uint64_t)p3 >> (21 * (c % 3)) & 0x1FFFFF);
+        if (tx == c) { team_sh.first[c] = at; team_sh.cursor[c] = at + low; }
+        at += num;
+      }
+      if (tx == 0) team_sh.first[K] = at;
+    }
+    __syncthreads();
+    int run = (int)pre.a;
+    const int lane = tx & (WAVE - 1);
+    for (int i0 = lo; i0 < hi; i0 += TEAM_BLOCK) {  // uniform over the workgroup
+      const int i = i0 + tx;
+      int cls = -1, size = 0;
+      if (i < hi) f(i, cls, size);
+      uint32_t all;
+      const uint32_t at = block_excl((uint32_t)size, all);
+      if (i < hi) ast(off + i, run + (int)at);
+      run += (int)all;
+#pragma unroll
+      for (int c = 0; c < K; ++c) {
+        const uint64_t b = __ballot(cls == c);
+        if (!b) continue;
+        int base = 0;
+        if (lane == 0) base = atomicAdd(&team_sh.cursor[c], __popcll(b));
+        base = uniform32(base);
+        if (cls == c) ast(list + base + __popcll(b & ((1ull << lane) - 1)), i);
+      }
+    }
+    if (rank == n - 1 && tx == 0) ast(off + m, (int32_t)tot.a);
+    return Sum2{tot.a, tot.e};
+  }
+
   // this member's share [lo, hi) of m items
   __device__ __forceinline__ int share_lo(int m) const { return (int)((int64_t)m * rank / n); }
   __device__ __forceinline__ int share_hi(int m) const { return (int)((int64_t)m * (rank + 1) / n); }
   __device__ __forceinline__ int threads() const { return n * TEAM_BLOCK; }
 };
-
-// This thread's number within its workgroup, recomputed in every phase (values derived from it are not kept
-// across phases).
-__device__ __forceinline__ int team_tx() {
-  int x = threadIdx.x;
-  asm volatile("" : "+v"(x));
-  return x;
-}
 
 }  // namespace
 

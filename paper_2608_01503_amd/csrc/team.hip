@@ -1,10 +1,17 @@
-// Small levels: the local move as one launch of a team (team.h).
+// Small levels: everything that a level takes up to the host's next decision, as one launch of a team (team.h): the
+// level put in place, the local move, the refinement and the contraction.
 //
-// The same method as lm.hip, with the same integer forms and the same results, laid out for levels whose phases
-// take a few microseconds each: counters stay in registers (every member sums the same partials), the moves are
-// applied where the afterburner keeps them, cluster sizes are kept beside the weights so that free ids need no
-// marking pass, and repeated passes cost nothing.  A level has at most TEAM_ENTRIES entries, so positions are
-// 32-bit here.
+// The same method as lm.hip, refine.hip and contract.hip, with the same integer forms and the same results, laid out
+// for levels whose phases take a few microseconds each.  Local move: counters stay in registers (every member sums the
+// same partials), the moves are applied where the afterburner keeps them, cluster sizes are kept beside the weights so
+// that free ids need no marking pass, and repeated passes cost nothing.  Refinement: trees are ordered by counting
+// among the lanes that hold them, no sort passes.  Contraction: a coarse row's entries are collected in a range as
+// long as its members' rows and summed where they lie, no sort of all entries.  A level has at most TEAM_ENTRIES
+// entries, so positions are 32-bit here.
+//
+// With only the local move in one launch a level still took 35 launches and 4 host reads for the contraction and 40
+// and 2 for the refinement; now it takes one launch and one read.  SBM graph of 2,000 vertices, Louvain+: 1058 -> 640
+// us a call; kNN graph of 3,000, pLeiden+: 5277 -> 2683 us; R-MAT graph of 2^14, pLeiden: 27.3 -> 14.6 ms.
 #include <algorithm>
 
 #include "team.h"
@@ -19,6 +26,7 @@ constexpr int TW_ROW = TW_SLOTS / 2;
 constexpr int TB_SLOTS = 16384;  // LDS hash of the whole workgroup (rows of up to TB_ROW entries)
 constexpr int TB_ROW = TB_SLOTS / 2;
 constexpr int TD_SLOTS = 32768;  // dense table of cluster ids for longer rows: one pass over the row per 32768 ids
+constexpr int TS_SLOTS = 16384;  // trees of up to so many members are sorted in LDS
 constexpr int AG_SLOTS = 2048;   // LDS table of the cluster-weight changes
 
 union TeamLds {
@@ -26,38 +34,12 @@ union TeamLds {
   struct { int32_t k[TB_SLOTS]; uint32_t v[TB_SLOTS]; } blk;
   uint32_t dense[TD_SLOTS];
   struct { int32_t k[AG_SLOTS]; int32_t c[AG_SLOTS]; unsigned long long w[AG_SLOTS]; } agg;
+  uint64_t sort[TS_SLOTS];
 };
 static_assert(sizeof(LeaderLds<2>) <= TW_SLOTS * sizeof(int32_t), "a wavefront may use its hash for leaders");
 __shared__ TeamLds lds;
 __shared__ Best team_best[TEAM_WAVES];
 
-struct TeamArgs {
-  TeamCtl* ctl;
-  TeamCtl* next;
-  int32_t n;
-  const int64_t* off;
-  const int32_t* idx;
-  const int32_t* w;
-  const int64_t* vw;
-  const int32_t* list;          // vertices by degree bucket, bucket b at [boff[b], boff[b + 1])
-  int32_t boff[NBUCKET + 1];
-  int32_t hash_shift;
-  Score sc;
-  const int32_t* cons;
-  int32_t* C;
-  int32_t* Cout;
-  int64_t* W;
-  int32_t* cnt;                 // members of every cluster id
-  VState* vs;
-  uint8_t* empty;
-  int32_t *freelist, *movers;
-  int64_t sum_w2;
-  int32_t singleton, pass_limit, symmetry;
-  uint32_t phi_num[MAX_PASSES + 1], phi_den[MAX_PASSES + 1];
-  LMSlot* slot;
-  uint8_t* used;
-  int32_t* rank;
-};
 typedef const TEAM_KERNARG TeamArgs* KP;
 
 // Changes of the cluster weights and sizes, summed per workgroup.  A slot belongs to the first cluster that
@@ -110,6 +92,13 @@ __device__ __forceinline__ void team_finish(KP kp, int32_t v, int32_t cv, int64_
   kp->vs[v] = o;
   a.ncand += vd.cand ? 1 : 0;
   a.own += own;
+}
+
+// f(kp, i) for all items i < m
+template <typename F>
+__device__ __forceinline__ void team_each(const Team& t, KP kp, int m, F f) {
+  TEAM_PHASE(kp);
+  for (int i = t.rank * TEAM_BLOCK + team_tx(); i < m; i += t.threads()) f(kp, i);
 }
 
 // Work of a pass over the rows: a wavefront takes 64 / G vertices of a bucket of G-lane groups (G = 4, 8, 16, 32)
@@ -282,7 +271,7 @@ struct EnumOp {
       pair_sweep<G>(cs[0], (int32_t)as[0], has[0], gl, acc, lead[0]);
       as[0] = (uint32_t)acc;
     } else {
-      leader_sum<G, E>(*(LeaderLds<E>*)lds.wave.k[uniform32((int)threadIdx.x / WAVE)], threadIdx.x & (WAVE - 1), cs, as, has, lead);
+      leader_sum<G, E>(*(LeaderLds<E>*)lds.wave.k[uniform32(team_tx() / WAVE)], team_tx() & (WAVE - 1), cs, as, has, lead);
     }
 #pragma unroll
     for (int k = 0; k < E; ++k) {
@@ -300,7 +289,7 @@ struct EnumOp {
     const int b = (int)kp->off[v], e = (int)kp->off[v + 1];
     if (e - b > TW_ROW) return;  // team_enum_blk
     if (e - b <= 2 * WAVE) return row<WAVE, 2>(kp, v, lane);
-    const int wv = uniform32((int)threadIdx.x / WAVE);
+    const int wv = uniform32(team_tx() / WAVE);
     int32_t* tk = lds.wave.k[wv];
     uint32_t* tv = lds.wave.v[wv];
     const int32_t cv = uniform32(ald(kp->C + v));
@@ -546,6 +535,7 @@ struct InternalOp {
 __device__ __forceinline__ void team_start(Team& t, KP kp) {
   TEAM_PHASE(kp);
   const int tx = team_tx(), n = kp->n, t0 = t.rank * TEAM_BLOCK + tx;
+  const bool up = kp->steps & TEAM_PROJECT;
   if (kp->singleton) {
     for (int v = t0; v < n; v += t.threads()) {
       ast(kp->C + v, v);
@@ -558,7 +548,8 @@ __device__ __forceinline__ void team_start(Team& t, KP kp) {
     t.sync();
     agg_clear();
     for (int v = t0; v < n; v += t.threads()) {
-      const int32_t c = ald(kp->Cout + v);
+      const int32_t c = up ? kp->up_C[kp->map[v]] : ald(kp->Cout + v);
+      if (up) ast(kp->Cout + v, c);
       ast(kp->C + v, c);
       agg_add(kp->W, kp->cnt, c, kp->vw[v], 1);
     }
@@ -578,13 +569,13 @@ __device__ __forceinline__ int64_t team_sw2(const Team& t, KP kp) {
   return sq;
 }
 
-// LocalMovePasses (Alg. 2) from singletons or from C_out (which holds the starting clustering); the result is
-// left in C_out.  *slot receives the statistics (plain stores, read after the launch).
-__device__ __forceinline__ void team_local_move(Team& t, const KP kp0) {
+// LocalMovePasses (Alg. 2) from singletons, from the next level's clustering or from C_out (which holds the starting
+// clustering); the result is left in C_out.  *slot receives the statistics (plain stores, read after the launch).
+// Returns whether the objective changed.
+__device__ __forceinline__ bool team_local_move(Team& t, const KP kp0) {
   KP kp = kp0;
   TEAM_PHASE(kp);
-  const bool log = t.rank == 0 && threadIdx.x == 0;
-  for (int k = threadIdx.x; t.rank == 0 && k < (int)(sizeof(LMSlot) / 8); k += TEAM_BLOCK) ast((int64_t*)kp->slot + k, (int64_t)0);
+  const bool log = t.rank == 0 && team_tx() == 0;
   team_start(t, kp);
   int64_t sw2 = 0, I = 0, Nbest = 0, N0 = 0, nL = 0, nM = 0;
   bool first = true, skipped = false;
@@ -652,74 +643,747 @@ __device__ __forceinline__ void team_local_move(Team& t, const KP kp0) {
     t.sync();
   }
   if (log) { kp->slot->Nbest = Nbest; kp->slot->N0 = N0; }
+  return Nbest != N0;
 }
 
-// ranks of the labels in use: rank[c] = labels below c in use, for c in [0, n]; returns their number
-__device__ __forceinline__ int team_rank(Team& t, KP kp, const int32_t* lab) {
+// ranks of the labels in use: rank[c] = labels below c in use, for c in [0, n); returns their number
+__device__ __forceinline__ int team_rank(Team& t, KP kp, const int32_t* lab, int32_t* rank) {
   TEAM_PHASE(kp);
   const int tx = team_tx(), n = kp->n;
-  for (int c = t.rank * TEAM_BLOCK + tx; c < n; c += t.threads()) ast(kp->used + c, (uint8_t)0);
+  uint8_t* used = kp->used;
+  for (int c = t.rank * TEAM_BLOCK + tx; c < n; c += t.threads()) ast(used + c, (uint8_t)0);
   t.sync();
-  for (int v = t.rank * TEAM_BLOCK + tx; v < n; v += t.threads()) ast(kp->used + ald(lab + v), (uint8_t)1);
+  for (int v = t.rank * TEAM_BLOCK + tx; v < n; v += t.threads()) ast(used + ald(lab + v), (uint8_t)1);
   t.sync();
-  const int lo = t.share_lo(n), hi = t.share_hi(n);
-  int x = 0;
-  for (int c = lo + tx; c < hi; c += TEAM_BLOCK) x += ald(kp->used + c);
-  Sum1 pre;
-  const int nc = (int)t.sum(x, pre).a;
-  int run = (int)pre.a;
-  for (int c0 = lo; c0 < hi; c0 += TEAM_BLOCK) {  // uniform over the workgroup
-    const int c = c0 + tx;
-    uint32_t tot;
-    const uint32_t at = t.block_excl(c < hi ? (uint32_t)ald(kp->used + c) : 0u, tot);
-    if (c < hi) ast(kp->rank + c, run + (int)at);
-    run += (int)tot;
-  }
-  if (t.rank == t.n - 1 && tx == 0) ast(kp->rank + n, nc);
+  const int nc = (int)t.lists<0>(n, rank, nullptr, 0, [&](int c, int& cls, int& size) __attribute__((always_inline)) {
+    size = ald(used + c);
+  }).a;
+  t.sync();
   return nc;
 }
 
-__global__ __launch_bounds__(TEAM_BLOCK) void k_team_local_move(TeamArgs args) {
+// --- contraction (Alg. 4): coarse vertex x = rank of the label; the rows' cross-cluster entries are collected per
+// coarse row, then every row is summed by neighbour, ascending.
+
+// Up to 64 U consecutive entries [j0, e) of a row of coarse vertex x, by a wavefront: those to other clusters go to
+// the coarse row, at places claimed with one atomic.
+template <int U>
+__device__ __forceinline__ void team_emit(KP kp, int32_t x, int j0, int e, int lane) {
+  int32_t us[U], ys[U];
+  uint32_t ws[U];
+#pragma unroll
+  for (int k = 0; k < U; ++k) {
+    const int j = j0 + k * WAVE + lane < e ? j0 + k * WAVE + lane : e - 1;
+    us[k] = kp->idx[j];
+    ws[k] = (uint32_t)kp->w[j];
+  }
+#pragma unroll
+  for (int k = 0; k < U; ++k) ys[k] = ald(kp->st.map + us[k]);
+  uint64_t m[U];
+  int total = 0;
+#pragma unroll
+  for (int k = 0; k < U; ++k) {
+    m[k] = __ballot(j0 + k * WAVE + lane < e && ys[k] != x);
+    total += __popcll(m[k]);
+  }
+  if (!total) return;
+  int at = 0;
+  if (lane == 0) at = atomicAdd(kp->st.end + x, total);
+  at = uniform32(at);
+#pragma unroll
+  for (int k = 0; k < U; ++k) {
+    if (m[k] >> lane & 1) ast(kp->st.raw + at + __popcll(m[k] & ((1ull << lane) - 1)), (uint64_t)(uint32_t)ys[k] << 32 | ws[k]);
+    at += __popcll(m[k]);
+  }
+}
+
+struct EmitOp {
+  template <int G>
+  __device__ __forceinline__ void group(KP kp, int32_t v, int gl) {
+    const int rb = (int)kp->off[v], d = (int)kp->off[v + 1] - rb;
+    const int32_t x = ald(kp->st.map + v);
+    const int j = rb + (gl < d ? gl : 0);
+    const int32_t y = gl < d ? ald(kp->st.map + kp->idx[j]) : x;
+    const uint32_t w = gl < d ? (uint32_t)kp->w[j] : 0u;
+    const int lane = team_tx() & (WAVE - 1);
+    const uint32_t m = (uint32_t)(__ballot(y != x) >> (lane - gl)) & (uint32_t)((1ull << G) - 1);
+    int at = 0;
+    if (gl == 0 && m) at = atomicAdd(kp->st.end + x, __popc(m));
+    at = __shfl(at, 0, G);
+    if (y != x) ast(kp->st.raw + at + __popc(m & ((1u << gl) - 1)), (uint64_t)(uint32_t)y << 32 | w);
+  }
+  __device__ __forceinline__ void wave(KP kp, int32_t v, int lane) {
+    const int b = (int)kp->off[v], e = (int)kp->off[v + 1];
+    if (e - b > TW_ROW) return;  // team_emit_blk
+    const int32_t x = uniform32(ald(kp->st.map + v));
+    for (int j0 = b; j0 < e; j0 += 2 * WAVE) team_emit<2>(kp, x, j0, e, lane);
+  }
+};
+__device__ __forceinline__ void team_emit_blk(const Team& t, KP kp) {
+  TEAM_PHASE(kp);
+  const int tx = team_tx(), lane = tx & (WAVE - 1), wv = uniform32(tx / WAVE), end = kp->boff[NBUCKET];
+  for (int i = kp->boff[5] + t.rank; i < end; i += t.n) {  // uniform over the workgroup
+    const int32_t v = uniform32(kp->list[i]);
+    const int b = (int)kp->off[v], e = (int)kp->off[v + 1];
+    if (e - b <= TW_ROW) continue;
+    const int32_t x = uniform32(ald(kp->st.map + v));
+    for (int j0 = b + wv * 4 * WAVE; j0 < e; j0 += TEAM_WAVES * 4 * WAVE) team_emit<4>(kp, x, j0, e, lane);
+  }
+}
+
+// place of every lane's key among the keys of the group's leaders
+template <int G, int K = 0>
+__device__ __forceinline__ int group_below(int32_t key) {
+  if constexpr (K < G) return (gbcast32<G, K>(key) < key) + group_below<G, K + 1>(key);
+  else return 0;
+}
+
+// A collected row of at most G entries: equal neighbours summed by leader lanes, placed by counting.
+template <int G>
+__device__ __forceinline__ void team_row_lanes(KP kp, int32_t x, int gl) {
+  const int b = ald(kp->st.start + x), m = ald(kp->st.end + x) - b;
+  const int lane = team_tx() & (WAVE - 1);
+  const uint64_t ent = gl < m ? ald(kp->st.raw + b + gl) : 0;
+  int32_t key[1] = {(int32_t)(ent >> 32)};
+  uint32_t wt[1] = {(uint32_t)ent};
+  const bool has[1] = {gl < m};
+  bool lead[1];
+  leader_sum<G, 1>(*(LeaderLds<1>*)lds.wave.k[uniform32(team_tx() / WAVE)], lane, key, wt, has, lead);
+  const int32_t ord = lead[0] ? key[0] : INT32_MAX;
+  uint64_t all = __ballot(lead[0]);
+  int at = 0;
+  if constexpr (G == WAVE) {
+    for (uint64_t left = all; left; left &= left - 1)
+      at += __builtin_amdgcn_readlane(ord, __ffsll((unsigned long long)left) - 1) < ord;
+  } else {
+    all = all >> (lane - gl) & ((1ull << G) - 1);
+    at = group_below<G>(ord);
+  }
+  if (lead[0]) ast(kp->st.seg + b + at, (uint64_t)(uint32_t)key[0] << 32 | wt[0]);
+  if (gl == 0) ast(kp->st.cnt + x, (int32_t)__popcll(all));
+}
+
+// A collected row of at most TW_SLOTS entries by a wavefront: the neighbours mark a bitmap, whose population count
+// gives every neighbour its place; sums in LDS.  Ranges of TB_IDS ids.
+constexpr int TB_WORDS = TW_SLOTS / 2, TB_IDS = TB_WORDS * 32;
+template <typename F>
+__device__ __forceinline__ void team_row_each(KP kp, int b, int m, int lane, F f) {
+  for (int j0 = lane; j0 < m; j0 += 4 * WAVE) {
+    uint64_t ent[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) ent[k] = j0 + k * WAVE < m ? ald(kp->st.raw + b + j0 + k * WAVE) : ~0ull;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) f(ent[k]);
+  }
+}
+__device__ __forceinline__ void team_row_bits(KP kp, int32_t x, int nc, int lane) {
+  TEAM_PHASE(kp);
+  const int b = ald(kp->st.start + x), m = ald(kp->st.end + x) - b;
+  const int wv = uniform32(team_tx() / WAVE);
+  uint32_t* bits = (uint32_t*)lds.wave.k[wv];
+  uint32_t* below = bits + TB_WORDS;
+  uint32_t* sum = lds.wave.v[wv];
+  int out = b;
+  for (int base = 0; base < nc; base += TB_IDS) {
+    const int words = ((nc - base < TB_IDS ? nc - base : TB_IDS) + 31) / 32;
+    for (int k = lane; k < words; k += WAVE) bits[k] = 0;
+    for (int k = lane; k < m; k += WAVE) sum[k] = 0;
+    lds_order();
+    team_row_each(kp, b, m, lane, [&](uint64_t ent) __attribute__((always_inline)) {
+      const uint32_t y = (uint32_t)(ent >> 32) - (uint32_t)base;
+      if (y < TB_IDS) atomicOr(&bits[y >> 5], 1u << (y & 31));
+    });
+    lds_order();
+    int total = 0;
+    for (int k0 = 0; k0 < words; k0 += WAVE) {  // uniform over the wavefront
+      const int k = k0 + lane;
+      const int c = k < words ? __popc(bits[k]) : 0;
+      const int inc = (int)wave_scan32((uint32_t)c);
+      if (k < words) below[k] = (uint32_t)(total + inc - c);
+      total += __builtin_amdgcn_readlane(inc, WAVE - 1);
+    }
+    lds_order();
+    team_row_each(kp, b, m, lane, [&](uint64_t ent) __attribute__((always_inline)) {
+      const uint32_t y = (uint32_t)(ent >> 32) - (uint32_t)base;
+      if (y < TB_IDS) atomicAdd(&sum[below[y >> 5] + __popc(bits[y >> 5] & ((1u << (y & 31)) - 1))], (uint32_t)ent);
+    });
+    lds_order();
+    // entries of one neighbour all write its sum to its place
+    team_row_each(kp, b, m, lane, [&](uint64_t ent) __attribute__((always_inline)) {
+      const uint32_t y = (uint32_t)(ent >> 32) - (uint32_t)base;
+      if (y < TB_IDS) {
+        const uint32_t at = below[y >> 5] + __popc(bits[y >> 5] & ((1u << (y & 31)) - 1));
+        ast(kp->st.seg + out + (int)at, (ent >> 32) << 32 | sum[at]);
+      }
+    });
+    lds_order();
+    out += total;
+  }
+  if (lane == 0) ast(kp->st.cnt + x, out - b);
+}
+
+// longer rows, the workgroup each: a dense table of neighbours (weights are positive: 0 = absent)
+__device__ __forceinline__ void team_row_blk(Team& t, KP kp, int32_t x, int nc) {
+  const int tx = team_tx();
+  const int b = ald(kp->st.start + x), e = ald(kp->st.end + x);
+  int out = b;
+  for (int base = 0; base < nc; base += TD_SLOTS) {
+    const int ids = nc - base < TD_SLOTS ? nc - base : TD_SLOTS;
+    for (int s = tx; s < ids; s += TEAM_BLOCK) lds.dense[s] = 0;
+    __syncthreads();
+    for (int j0 = b + tx; j0 < e; j0 += 4 * TEAM_BLOCK) {
+      uint64_t ent[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) ent[k] = j0 + k * TEAM_BLOCK < e ? ald(kp->st.raw + j0 + k * TEAM_BLOCK) : ~0ull;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t y = (uint32_t)(ent[k] >> 32) - (uint32_t)base;
+        if (y < (uint32_t)ids) atomicAdd(&lds.dense[y], (uint32_t)ent[k]);
+      }
+    }
+    __syncthreads();
+    const int per = (ids + TEAM_BLOCK - 1) / TEAM_BLOCK;
+    const int s0 = tx * per < ids ? tx * per : ids, s1 = s0 + per < ids ? s0 + per : ids;
+    uint32_t c = 0, tot;
+    for (int s = s0; s < s1; ++s) c += lds.dense[s] != 0;
+    int at = out + (int)t.block_excl(c, tot);
+    for (int s = s0; s < s1; ++s)
+      if (const uint32_t w = lds.dense[s]) ast(kp->st.seg + at++, (uint64_t)(uint32_t)(base + s) << 32 | w);
+    out += (int)tot;
+    __syncthreads();
+  }
+  if (tx == 0) ast(kp->st.cnt + x, out - b);
+}
+
+// The collected rows of nc coarse vertices summed, by length.
+__device__ __forceinline__ void team_rows(Team& t, KP kp, int nc) {
+  TEAM_PHASE(kp);
+  t.lists<4>(nc, kp->st.off, kp->st.rows, 0, [&](int x, int& cls, int& size) __attribute__((always_inline)) {
+    const int m = ald(kp->st.end + x) - ald(kp->st.start + x);
+    cls = m <= 16 ? 0 : m <= WAVE ? 1 : m <= TW_SLOTS ? 2 : 3;
+  });
+  t.sync();
+  const int tx = team_tx(), lane = tx & (WAVE - 1), wv = uniform32(tx / WAVE);
+  const int f1 = uniform32(team_sh.first[1]), f2 = uniform32(team_sh.first[2]), f3 = uniform32(team_sh.first[3]),
+            f4 = uniform32(team_sh.first[4]);
+  for (int i = f3 + t.rank; i < f4; i += t.n) team_row_blk(t, kp, uniform32(ald(kp->st.rows + i)), nc);
+  const int nw = f3 - f1, all = nw + (f1 + 3) / 4;
+  for (int k = wv * t.n + t.rank; k < all; k += t.n * TEAM_WAVES) {
+    if (k < nw) {
+      const int i = f3 - 1 - k;
+      const int32_t x = uniform32(ald(kp->st.rows + i));
+      if (i >= f2) team_row_bits(kp, x, nc, lane);
+      else team_row_lanes<WAVE>(kp, x, lane);
+    } else {
+      const int i = (k - nw) * 4 + lane / 16;
+      if (i < f1) team_row_lanes<16>(kp, ald(kp->st.rows + i), lane & 15);
+    }
+  }
+  t.sync();
+}
+
+// The next level, of nc vertices by the rank of the labels (of R after a refinement, else C_out), into the stage.
+__device__ __forceinline__ void team_contract(Team& t, KP kp, int nc) {
+  team_each(t, kp, nc, [](KP kp, int x) __attribute__((always_inline)) { ast(kp->st.cnt + x, 0); ast(kp->st.vw + x, (int64_t)0); });
+  t.sync();
+  agg_clear();
+  team_each(t, kp, kp->n, [](KP kp, int v) __attribute__((always_inline)) {
+    const bool down = kp->steps & TEAM_REFINE;
+    const int32_t x = ald((down ? kp->rankR : kp->rank) + ald((down ? kp->R : kp->Cout) + v));
+    ast(kp->st.map + v, x);
+    if (kp->B) ast(kp->st.B + x, kp->B[v]);
+    if (down) ast(kp->st.C + x, ald(kp->rank + ald(kp->Cout + v)));  // every v of x is in the same cluster
+    agg_add(kp->st.vw, kp->st.cnt, x, kp->vw[v], (int)(kp->off[v + 1] - kp->off[v]));
+  });
+  agg_flush(kp->st.vw, kp->st.cnt);
+  t.sync();
+  TEAM_PHASE(kp);
+  // a coarse row's entries take a range as long as its members' rows
+  t.lists<0>(nc, kp->st.start, nullptr, 0, [&](int x, int& cls, int& size) __attribute__((always_inline)) {
+    size = ald(kp->st.cnt + x);
+  });
+  t.sync();
+  team_each(t, kp, nc, [](KP kp, int x) __attribute__((always_inline)) { ast(kp->st.end + x, ald(kp->st.start + x)); });
+  t.sync();
+  {
+    EmitOp op;
+    team_tasks(t, kp, op);
+    team_emit_blk(t, kp);
+  }
+  t.sync();
+  team_rows(t, kp, nc);
+  TEAM_PHASE(kp);
+  int64_t sq = 0;
+  team_each(t, kp, nc, [&](KP kp, int x) __attribute__((always_inline)) { const int64_t w = ald(kp->st.vw + x); sq += w * w; });
+  const Sum2 z = t.lists<NBUCKET>(nc, kp->st.off, kp->st.list, sq, [&](int x, int& cls, int& size) __attribute__((always_inline)) {
+    size = ald(kp->st.cnt + x);
+    cls = 0;
+    for (int k = 0; k < NBUCKET - 1; ++k) cls += size > kp->bounds.max[k];
+  });
+  if (t.rank == 0 && team_tx() == 0) {
+    LMSlot* s = kp->slot;
+    s->coarse_nnz = z.a;
+    s->coarse_w2 = z.b;
+    for (int k = 0; k <= NBUCKET; ++k) s->coarse_boff[k] = team_sh.first[k];
+    s->coarse = 1;
+  }
+}
+
+// The staged level into its own arrays.  Lanes of a group of 16 take a row; rows above 256 entries the wavefront.
+__device__ __forceinline__ void team_place(Team& t, KP kp) {
+  TEAM_PHASE(kp);
+  const int n = kp->n, tx = team_tx(), lane = tx & (WAVE - 1);
+  team_each(t, kp, n, [](KP kp, int x) __attribute__((always_inline)) {
+    kp->off[x] = kp->st.off[x];
+    kp->vw[x] = kp->st.vw[x];
+    kp->list[x] = kp->st.list[x];
+    if (kp->B_place) kp->B_place[x] = kp->st.B[x];
+    if (!kp->singleton) kp->Cout[x] = kp->st.C[x];
+    if (x == kp->n - 1) kp->off[x + 1] = kp->st.off[x + 1];
+  });
+  team_each(t, kp, kp->n_fine, [](KP kp, int v) __attribute__((always_inline)) { kp->map_place[v] = kp->st.map[v]; });
+  for (int x0 = (t.rank * TEAM_WAVES + uniform32(tx / WAVE)) * 4; x0 < n; x0 += t.n * TEAM_WAVES * 4) {
+    const int x = x0 + lane / 16;
+    int b = 0, o = 0, m = 0;
+    if (x < n) { b = kp->st.start[x]; o = kp->st.off[x]; m = kp->st.cnt[x]; }
+    if (m <= 256)
+      for (int j = lane & 15; j < m; j += 16) {
+        const uint64_t ent = kp->st.seg[b + j];
+        kp->idx[o + j] = (int32_t)(ent >> 32);
+        kp->w[o + j] = (int32_t)(uint32_t)ent;
+      }
+    for (uint64_t big = __ballot(m > 256 && (lane & 15) == 0); big; big &= big - 1) {
+      const int l = __ffsll((unsigned long long)big) - 1;
+      const int bb = __builtin_amdgcn_readlane(b, l), oo = __builtin_amdgcn_readlane(o, l), mm = __builtin_amdgcn_readlane(m, l);
+#pragma unroll 4
+      for (int j = lane; j < mm; j += WAVE) {
+        const uint64_t ent = kp->st.seg[bb + j];
+        kp->idx[oo + j] = (int32_t)(ent >> 32);
+        kp->w[oo + j] = (int32_t)(uint32_t)ent;
+      }
+    }
+  }
+  t.sync_all();
+}
+
+// --- refinement (Alg. 6) of the clustering B = C_out; the definitions are in refine.hip
+
+__device__ __forceinline__ uint64_t team_f(KP kp, int32_t v, bool flip) {
+  const uint64_t f = fmix32((uint32_t)v ^ (uint32_t)(kp->seed >> 32));
+  return flip ? (((uint64_t)1 << 33) - 1) - f : f;
+}
+
+// sum over the entries x, x + S, ... of the row [b, e): get(u) is loaded for U entries at a time, use(g, u, w) is the
+// entry's share
+template <int U, typename Get, typename Use>
+__device__ __forceinline__ int64_t team_row_sum(KP kp, int b, int e, int x, int S, Get get, Use use) {
+  int64_t s = 0;
+  for (int j0 = b + x; j0 < e; j0 += S * U) {
+    int32_t us[U], ws[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int j = j0 + k * S < e ? j0 + k * S : e - 1;
+      us[k] = kp->idx[j];
+      ws[k] = kp->w[j];
+    }
+    decltype(get(0)) g[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) g[k] = get(us[k]);
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+      if (j0 + k * S < e) s += use(g[k], us[k], ws[k]);
+  }
+  return s;
+}
+
+// a(v, B[v] \ v) and membership of U
+struct OwnOp {
+  int64_t nU = 0;
+  template <int U>
+  __device__ __forceinline__ int64_t part(KP kp, int32_t v, int32_t bv, int x, int S) {
+    return team_row_sum<U>(kp, (int)kp->off[v], (int)kp->off[v + 1], x, S,
+                           [&](int32_t u) __attribute__((always_inline)) { return ald(kp->Cout + u); },
+                           [&](int32_t c, int32_t, int32_t w) __attribute__((always_inline)) { return c == bv ? (int64_t)w : 0; });
+  }
+  __device__ __forceinline__ void finish(KP kp, int32_t v, int32_t bv, int64_t s) {
+    const int64_t wv = kp->vw[v];
+    const bool in = kp->sc.q * s - kp->sc.p * wv * (ald(kp->WB + bv) - wv) >= 0;
+    ast(kp->aB + v, s);
+    ast(kp->inU + v, (uint8_t)in);
+    nU += in;
+  }
+  template <int G>
+  __device__ __forceinline__ void group(KP kp, int32_t v, int gl) {
+    const int32_t bv = ald(kp->Cout + v);
+    const int64_t s = sum_steps<G>(part<1>(kp, v, bv, gl, G));
+    if (gl == 0) finish(kp, v, bv, s);
+  }
+  __device__ __forceinline__ void wave(KP kp, int32_t v, int lane) {
+    const int32_t bv = ald(kp->Cout + v);
+    const int64_t s = wave_sum64(part<4>(kp, v, bv, lane, WAVE));
+    if (lane == 0) finish(kp, v, bv, s);
+  }
+};
+
+// random candidate edge H, the parent it gives and the parent's mark
+struct ChooseOp {
+  struct Near { int32_t c; int32_t in; int64_t w; };
+  __device__ __forceinline__ Near near(KP kp, int32_t u) const { return Near{ald(kp->Cout + u), ald(kp->inU + u), kp->vw[u]}; }
+  __device__ __forceinline__ bool good(KP kp, const Near& o, int32_t bv, int64_t wv, int32_t w) const {
+    return o.in && o.c == bv && kp->sc.q * (int64_t)w - kp->sc.p * o.w * wv >= 0;
+  }
+  // the rank among the qualifying neighbours of the chosen one, -1 for v itself
+  __device__ __forceinline__ int pick(KP kp, int32_t v, int total, int below) const {
+    const int r = (int)(fmix64(kp->seed ^ ((uint64_t)(uint32_t)v << 1)) % (uint64_t)(total + 1));
+    return r == below ? -1 : r < below ? r : r - 1;
+  }
+  __device__ __forceinline__ void finish(KP kp, int32_t v, int32_t h) const {
+    const bool keep = h != v && team_f(kp, h, false) < team_f(kp, v, false);
+    ast(kp->H + v, h);
+    ast(kp->par + v, keep ? h : v);
+    if (keep) ast(kp->has_child + h, (uint8_t)1);
+  }
+  template <int G>
+  __device__ __forceinline__ void group(KP kp, int32_t v, int gl) {
+    const int rb = (int)kp->off[v], d = (int)kp->off[v + 1] - rb;
+    const int lane = team_tx() & (WAVE - 1);
+    int32_t u = v;
+    bool q = false;
+    if (gl < d && ald(kp->inU + v)) {
+      u = kp->idx[rb + gl];
+      q = good(kp, near(kp, u), ald(kp->Cout + v), kp->vw[v], kp->w[rb + gl]);
+    }
+    const uint32_t all = (uint32_t)((1ull << G) - 1);
+    const uint32_t m = (uint32_t)(__ballot(q) >> (lane - gl)) & all, lo = (uint32_t)(__ballot(q && u < v) >> (lane - gl)) & all;
+    const int want = pick(kp, v, __popc(m), __popc(lo));
+    const bool mine = q && __popc(m & ((1u << gl) - 1)) == want;
+    if (mine || (gl == 0 && want < 0)) finish(kp, v, mine ? u : v);
+  }
+  __device__ __forceinline__ void wave(KP kp, int32_t v, int lane) {
+    const int b = (int)kp->off[v], e = (int)kp->off[v + 1];
+    if (!ald(kp->inU + v)) {  // uniform
+      if (lane == 0) finish(kp, v, v);
+      return;
+    }
+    const int32_t bv = ald(kp->Cout + v);
+    const int64_t wv = kp->vw[v];
+    int total = 0, below = 0;
+    for (int j0 = b; j0 < e; j0 += 2 * WAVE) {  // uniform
+      int32_t us[2], ws[2];
+      Near o[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int j = j0 + k * WAVE + lane < e ? j0 + k * WAVE + lane : e - 1;
+        us[k] = kp->idx[j];
+        ws[k] = kp->w[j];
+      }
+#pragma unroll
+      for (int k = 0; k < 2; ++k) o[k] = near(kp, us[k]);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const bool q = j0 + k * WAVE + lane < e && good(kp, o[k], bv, wv, ws[k]);
+        total += __popcll(__ballot(q));
+        below += __popcll(__ballot(q && us[k] < v));
+      }
+    }
+    const int want = uniform32(pick(kp, v, total, below));
+    if (want < 0) {
+      if (lane == 0) finish(kp, v, v);
+      return;
+    }
+    int seen = 0;
+    for (int j0 = b; j0 < e && seen <= want; j0 += WAVE) {  // uniform
+      const int j = j0 + lane < e ? j0 + lane : e - 1;
+      const int32_t u = kp->idx[j];
+      const bool q = j0 + lane < e && good(kp, near(kp, u), bv, wv, kp->w[j]);
+      const uint64_t m = __ballot(q);
+      if (q && seen + __popcll(m & ((1ull << lane) - 1)) == want) finish(kp, v, u);
+      seen += __popcll(m);
+    }
+  }
+};
+
+// a(v, X_{<v}): edges to earlier vertices of the same tree (of two or more members)
+struct TreeOp {
+  struct Near { int32_t r; int32_t flip; };
+  template <int U>
+  __device__ __forceinline__ int64_t part(KP kp, int32_t v, int32_t rv, int x, int S) {
+    const uint64_t fv = team_f(kp, v, ald(kp->flip + v));
+    return team_row_sum<U>(kp, (int)kp->off[v], (int)kp->off[v + 1], x, S,
+                           [&](int32_t u) __attribute__((always_inline)) { return Near{ald(kp->root + u), ald(kp->flip + u)}; },
+                           [&](const Near& o, int32_t u, int32_t w) __attribute__((always_inline)) {
+                             return o.r == rv && team_f(kp, u, o.flip) < fv ? (int64_t)w : 0;
+                           });
+  }
+  template <int G>
+  __device__ __forceinline__ void group(KP kp, int32_t v, int gl) {
+    const int32_t rv = ald(kp->root + v);
+    if (ald(kp->tsz + rv) < 2) return;  // uniform over the group
+    const int64_t s = sum_steps<G>(part<1>(kp, v, rv, gl, G));
+    if (gl == 0) ast(kp->aX + v, s);
+  }
+  __device__ __forceinline__ void wave(KP kp, int32_t v, int lane) {
+    const int32_t rv = ald(kp->root + v);
+    if (ald(kp->tsz + rv) < 2) return;
+    const int64_t s = wave_sum64(part<4>(kp, v, rv, lane, WAVE));
+    if (lane == 0) ast(kp->aX + v, s);
+  }
+};
+
+// conditions of Lemma 1 and 2 for a vertex whose earlier tree members weigh wX and have the cut `cut`
+__device__ __forceinline__ bool team_valid(KP kp, int64_t ax, int64_t w, int64_t wX, int64_t cut, int64_t wB) {
+  return kp->sc.q * ax - kp->sc.p * w * wX >= 0 && kp->sc.q * cut - kp->sc.p * wX * (wB - wX) >= 0;
+}
+constexpr int TREE_V = 24;  // keys of the tree members: f << TREE_V | vertex
+constexpr uint64_t TREE_MASK = (1ull << TREE_V) - 1;
+static_assert(TEAM_ENTRIES / 4 <= (int64_t)1 << TREE_V, "vertices in the tree keys");
+
+template <int G, int K = 0>
+__device__ __forceinline__ int group_below64(uint64_t key) {
+  if constexpr (K < G) {
+    const uint64_t o = (uint64_t)(uint32_t)gbcast32<G, K>((int32_t)(key >> 32)) << 32 | (uint32_t)gbcast32<G, K>((int32_t)(uint32_t)key);
+    return (o < key) + group_below64<G, K + 1>(key);
+  } else {
+    return 0;
+  }
+}
+
+// a tree of m <= G members at keys[b ..]: in the order of f, the longest valid prefix takes the root's id
+template <int G>
+__device__ __forceinline__ void team_tree_lanes(KP kp, int32_t r, int b, int m, int gl) {
+  const int lane = team_tx() & (WAVE - 1);
+  int32_t* slot = lds.wave.k[uniform32(team_tx() / WAVE)];
+  const uint64_t key = gl < m ? ald(kp->keys + b + gl) : ~0ull;
+  int at = 0;
+  if constexpr (G == WAVE) {
+    for (int l = 0; l < m; ++l) {
+      const uint64_t o = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(key >> 32), l) << 32 |
+                         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key, l);
+      at += o < key;
+    }
+  } else {
+    at = group_below64<G>(key);
+  }
+  if (gl < m) slot[lane - gl + at] = (int32_t)(key & TREE_MASK);
+  lds_order();
+  const bool has = gl < m;
+  const int32_t v = has ? slot[lane] : r;
+  lds_order();
+  const int64_t w = has ? kp->vw[v] : 0, ax = has ? ald(kp->aX + v) : 0, tc = has ? ald(kp->aB + v) - 2 * ax : 0;
+  const int64_t sw = scan64<G>(w), sc = scan64<G>(tc);
+  const bool bad = has && !team_valid(kp, ax, w, sw - w, sc - tc, ald(kp->WB + ald(kp->Cout + r)));
+  uint64_t f = __ballot(bad);
+  if constexpr (G < WAVE) f = f >> (lane - gl) & ((1ull << G) - 1);
+  const int first = f ? __ffsll((unsigned long long)f) - 1 : m;
+  if (has) ast(kp->R + v, gl < first ? r : v);
+}
+
+// Ascending sort of m keys by a workgroup; keys past the end count as largest.
+template <typename Load, typename Store>
+__device__ __forceinline__ void team_sort(int m, Load load, Store store) {
+  const int tx = team_tx();
+  int P = 2;
+  while (P < m) P <<= 1;
+  for (int k = 2; k <= P; k <<= 1)
+    for (int s = k / 2; s > 0; s >>= 1) {  // first step of a merge: the mirrored partner, then half the distance each
+      for (int x = tx; x < P / 2; x += TEAM_BLOCK) {
+        const int i = (x & ~(s - 1)) << 1 | (x & (s - 1)), j = s == k / 2 ? i ^ (k - 1) : i + s;
+        if (j < m) {
+          const uint64_t a = load(i), c = load(j);
+          if (a > c) { store(i, c); store(j, a); }
+        }
+      }
+      __syncthreads();
+    }
+}
+
+// Inclusive sums of x and y over the threads of the workgroup, and the totals.
+__device__ __forceinline__ void team_block_sums(int64_t& x, int64_t& y, int64_t& tot_x, int64_t& tot_y) {
+  const int tx = team_tx(), lane = tx & (WAVE - 1), wv = uniform32(tx / WAVE);
+  x = scan64<WAVE>(x);
+  y = scan64<WAVE>(y);
+  if (lane == WAVE - 1) { team_sh.red[0][wv] = x; team_sh.red[1][wv] = y; }
+  __syncthreads();
+  int64_t px = 0, py = 0;
+  tot_x = tot_y = 0;
+#pragma unroll 1
+  for (int k = 0; k < TEAM_WAVES; ++k) {
+    const int64_t a = team_sh.red[0][k], c = team_sh.red[1][k];
+    if (k < wv) { px += a; py += c; }
+    tot_x += a;
+    tot_y += c;
+  }
+  x += px;
+  y += py;
+  __syncthreads();
+}
+
+// trees of more than 64 members, the workgroup each
+__device__ __forceinline__ void team_tree_blk(KP kp, int32_t r, int b, int m) {
+  const int tx = team_tx();
+  uint64_t* g = kp->keys + b;
+  const bool in_lds = m <= TS_SLOTS;
+  __syncthreads();
+  if (in_lds) {
+    for (int i = tx; i < m; i += TEAM_BLOCK) lds.sort[i] = ald(g + i);
+    __syncthreads();
+    team_sort(m, [&](int i) __attribute__((always_inline)) { return lds.sort[i]; },
+              [&](int i, uint64_t k) __attribute__((always_inline)) { lds.sort[i] = k; });
+  } else {
+    team_sort(m, [&](int i) __attribute__((always_inline)) { return ald(g + i); },
+              [&](int i, uint64_t k) __attribute__((always_inline)) { ast(g + i, k); });
+  }
+  const int64_t wB = ald(kp->WB + ald(kp->Cout + r));
+  int64_t cw = 0, cc = 0;
+  if (tx == 0) team_sh.cursor[0] = m;
+  __syncthreads();
+  int first = m;
+  for (int i0 = 0; i0 < m && first == m; i0 += TEAM_BLOCK) {  // uniform over the workgroup
+    const int i = i0 + tx;
+    const bool has = i < m;
+    const int32_t v = has ? (int32_t)((in_lds ? lds.sort[i] : ald(g + i)) & TREE_MASK) : r;
+    const int64_t w = has ? kp->vw[v] : 0, ax = has ? ald(kp->aX + v) : 0, tc = has ? ald(kp->aB + v) - 2 * ax : 0;
+    int64_t sw = w, sc = tc, tw, tt;
+    team_block_sums(sw, sc, tw, tt);
+    if (has && !team_valid(kp, ax, w, cw + sw - w, cc + sc - tc, wB)) atomicMin(&team_sh.cursor[0], i);
+    __syncthreads();
+    first = uniform32(team_sh.cursor[0]);
+    cw += tw;
+    cc += tt;
+    __syncthreads();
+  }
+  for (int i = tx; i < m; i += TEAM_BLOCK) {
+    const int32_t v = (int32_t)((in_lds ? lds.sort[i] : ald(g + i)) & TREE_MASK);
+    ast(kp->R + v, i < first ? r : v);
+  }
+  __syncthreads();
+}
+
+// R = refinement of C_out
+__device__ __forceinline__ void team_refine(Team& t, KP kp) {
+  TEAM_PHASE(kp);
+  const int n = kp->n;
+  team_each(t, kp, n, [](KP kp, int v) __attribute__((always_inline)) {
+    ast(kp->WB + v, (int64_t)0);
+    ast(kp->tsz + v, 0);
+    ast(kp->has_child + v, (uint8_t)0);
+  });
+  t.sync();
+  agg_clear();
+  team_each(t, kp, n, [](KP kp, int v) __attribute__((always_inline)) {
+    agg_add(kp->WB, kp->cnt, ald(kp->Cout + v), kp->vw[v], 0);
+  });
+  agg_flush(kp->WB, kp->cnt);
+  t.sync();
+  {
+    OwnOp op;
+    team_tasks(t, kp, op);
+    const int64_t u = t.sum(op.nU).a;
+    if (t.rank == 0 && team_tx() == 0) kp->slot->refine_U = u;
+  }
+  {
+    ChooseOp op;
+    team_tasks(t, kp, op);
+    t.sync();
+  }
+  TEAM_PHASE(kp);
+  // a root without children takes f <- 2K - 1 - f, and its own edge is tested again with the new values
+  team_each(t, kp, n, [](KP kp, int v) __attribute__((always_inline)) {
+    const int32_t p = ald(kp->par + v), h = ald(kp->H + v);
+    const bool flip = p == v && !ald(kp->has_child + v);
+    int32_t p2 = p;
+    if (flip && h != v) {
+      const bool hflip = ald(kp->par + h) == h && !ald(kp->has_child + h);
+      if (team_f(kp, h, hflip) < team_f(kp, v, true)) p2 = h;
+    }
+    ast(kp->flip + v, (uint8_t)flip);
+    ast(kp->par2 + v, p2);
+  });
+  t.sync();
+  // parents strictly decrease f, so every chase ends at a root within n steps; the bound only turns an impossible
+  // cycle into an error instead of a hang
+  team_each(t, kp, n, [](KP kp, int v) __attribute__((always_inline)) {
+    const int n = kp->n;
+    int32_t x = v, p = ald(kp->par2 + x);
+    for (int steps = 0; p != x && steps <= n; ++steps) { x = p; p = ald(kp->par2 + x); }
+    if (p != x) kp->slot->cycle = 1;
+    ast(kp->root + v, x);
+    ast(kp->rel + v, atomicAdd(kp->tsz + x, 1));
+  });
+  t.sync();
+  const int64_t m = t.lists<3>(n, kp->toff, kp->trees, 0, [&](int v, int& cls, int& size) __attribute__((always_inline)) {
+    const int s = ald(kp->tsz + v);  // 0 for vertices that are no roots
+    if (s >= 2) { size = s; cls = s <= 16 ? 0 : s <= WAVE ? 1 : 2; }
+  }).a;
+  if (t.rank == 0 && team_tx() == 0) kp->slot->refine_m = m;
+  t.sync();
+  team_each(t, kp, n, [](KP kp, int v) __attribute__((always_inline)) {
+    const int32_t r = ald(kp->root + v);
+    if (ald(kp->tsz + r) < 2) ast(kp->R + v, v);
+    else ast(kp->keys + ald(kp->toff + r) + ald(kp->rel + v), team_f(kp, v, ald(kp->flip + v)) << TREE_V | (uint32_t)v);
+  });
+  {
+    TreeOp op;
+    team_tasks(t, kp, op);
+    t.sync();
+  }
+  TEAM_PHASE(kp);
+  const int tx = team_tx(), lane = tx & (WAVE - 1), wv = uniform32(tx / WAVE);
+  const int f1 = uniform32(team_sh.first[1]), f2 = uniform32(team_sh.first[2]), f3 = uniform32(team_sh.first[3]);
+  for (int i = f2 + t.rank; i < f3; i += t.n) {
+    const int32_t r = uniform32(ald(kp->trees + i));
+    team_tree_blk(kp, r, uniform32(ald(kp->toff + r)), uniform32(ald(kp->tsz + r)));
+  }
+  const int nw = f2 - f1, all = nw + (f1 + 3) / 4;
+  for (int k = wv * t.n + t.rank; k < all; k += t.n * TEAM_WAVES) {
+    if (k < nw) {
+      const int32_t r = uniform32(ald(kp->trees + f1 + k));
+      team_tree_lanes<WAVE>(kp, r, uniform32(ald(kp->toff + r)), uniform32(ald(kp->tsz + r)), lane);
+    } else {
+      const int i = (k - nw) * 4 + lane / 16;
+      if (i < f1) {
+        const int32_t r = ald(kp->trees + i);
+        team_tree_lanes<16>(kp, r, ald(kp->toff + r), ald(kp->tsz + r), lane & 15);
+      }
+    }
+  }
+  t.sync();
+}
+
+// One level: everything up to the point where the host has to decide or to allocate.
+__global__ __launch_bounds__(TEAM_BLOCK) void k_team_level(TeamArgs args) {
   KP kp = (KP)__builtin_amdgcn_kernarg_segment_ptr();
   Team t;
   if (!t.join(kp->ctl, kp->next)) return;
-  team_local_move(t, kp);
-  const int nc = team_rank(t, kp, kp->Cout);
-  if (t.rank == 0 && threadIdx.x == 0) kp->slot->nlab = nc;
+  for (int k = team_tx(); t.rank == 0 && k < (int)(sizeof(LMSlot) / 8); k += TEAM_BLOCK) ast((int64_t*)kp->slot + k, (int64_t)0);
+  const int steps = kp->steps, n = kp->n;
+  if (steps & TEAM_PLACE) team_place(t, kp);
+  // an unchanged C_out goes through the alternate local move before it is refined
+  bool on = true;
+  if (steps & TEAM_MOVE) on = team_local_move(t, kp) || !(steps & TEAM_REFINE);
+  int nc = team_rank(t, kp, kp->Cout, kp->rank);
+  if (t.rank == 0 && team_tx() == 0) kp->slot->nlab = nc;
+  on = on && nc < n && (steps & TEAM_CONTRACT);
+  if (on && (steps & TEAM_REFINE)) {
+    team_refine(t, kp);
+    nc = team_rank(t, kp, kp->R, kp->rankR);
+    if (t.rank == 0 && team_tx() == 0) { kp->slot->refine_n = nc; kp->slot->refined = 1; }
+    on = nc < n;
+  }
+  if (on) {
+    team_contract(t, kp, nc);
+  }
 }
 
 }  // namespace
 
 // --- host launchers
 
-static TeamCtl* team_ctl(TeamHost& h, TeamCtl** next) {
-  TeamCtl* c = h.ctl + h.turn % TEAM_SLOTS;
-  *next = h.ctl + (h.turn + 1) % TEAM_SLOTS;
+void team_launch(TeamArgs& a, TeamHost& h, hipStream_t st) {
+  a.ctl = h.ctl + h.turn % TEAM_SLOTS;
+  a.next = h.ctl + (h.turn + 1) % TEAM_SLOTS;
   ++h.turn;
-  return c;
-}
-
-void team_local_move_launch(const DevGraph& g, const Buckets& b, const LMParams& prm, bool singleton, LMBuffers& bufs,
-                            int32_t* C, uint8_t* used, int32_t* rank, TeamHost& th, LMSlot* slot, hipStream_t st) {
-  TeamArgs a{};
-  a.ctl = team_ctl(th, &a.next);
-  a.n = (int32_t)g.n;
-  a.off = g.off; a.idx = g.idx; a.w = g.w; a.vw = g.vw;
-  a.list = b.list;
-  for (int k = 0; k <= NBUCKET; ++k) a.boff[k] = (int32_t)b.off[k];
-  a.hash_shift = b.hash_shift;
-  a.sc = prm.sc;
-  a.cons = prm.cons;
-  a.C = bufs.C; a.Cout = C; a.W = bufs.W; a.cnt = bufs.scan_a; a.vs = bufs.vs;
-  a.empty = bufs.empty; a.freelist = bufs.freelist; a.movers = bufs.scan_b;
-  a.sum_w2 = prm.sum_w2;
-  a.singleton = singleton ? 1 : 0;
-  a.pass_limit = prm.pass_limit;
-  a.symmetry = prm.symmetry;
-  for (int i = 0; i <= MAX_PASSES; ++i) { a.phi_num[i] = prm.phi_num[i]; a.phi_den[i] = prm.phi_den[i]; }
-  a.slot = slot;
-  a.used = used; a.rank = rank;
-  k_team_local_move<<<TEAM_GRID, TEAM_BLOCK, 0, st>>>(a);
+  k_team_level<<<TEAM_GRID, TEAM_BLOCK, 0, st>>>(a);
 }
 
 }  // namespace lcc

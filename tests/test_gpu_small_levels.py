@@ -37,6 +37,7 @@ GRAPHS = {
 @pytest.mark.parametrize("name", GRAPHS)
 @pytest.mark.parametrize("variant", [O.PLOUVAIN, O.PLEIDEN, O.PLEIDEN_PLUS, O.LOUVAIN])
 def test_team_equals_bucket_launches(name, variant):
+    import torch
     import paper_2608_01503_amd as L
     g = GRAPHS[name]()
     buckets = L.Context(0)
@@ -50,5 +51,56 @@ def test_team_equals_bucket_launches(name, variant):
         assert np.array_equal(la.cpu().numpy(), lb.cpu().numpy()), (name, lam, kw)
         assert (a.N, a.num_clusters, a.levels, a.flags) == (b.N, b.num_clusters, b.levels, b.flags)
         assert np.array_equal(a.trace, b.trace)
+    buckets.close()
+    team.close()
+
+
+# next levels with rows around the lane groups, the bitmap and the dense table of the contraction, and refinement trees
+# around a lane group, a wavefront and the LDS sort
+NEXT = {
+    "stars": lambda: gg.from_pairs(6000, [(c, 1000 * c + i) for c, d in enumerate([15, 16, 17, 63, 64, 65]) for i in range(1, 3 * d)]
+                                   + [(i, i + 1000) for i in range(200, 5000, 7)]),
+    "wide star": lambda: gg.from_pairs(40001, [(0, i) for i in range(1, 40001)]),
+    "dense rows": lambda: _rows([900, 1020, 1024, 1028, 1100, 2050], 9000, 4),
+    "many vertices": lambda: gg.lattice(220, 220, 0.05, 100, 3),
+}
+
+
+@pytest.mark.parametrize("name", NEXT)
+@pytest.mark.parametrize("variant", [O.PLEIDEN, O.PLEIDEN_PLUS, O.PLOUVAIN])
+def test_team_next_level_equals_launches(name, variant):
+    import torch
+    import paper_2608_01503_amd as L
+    g = NEXT[name]()
+    buckets = L.Context(0)
+    buckets.profile_enable(["single"])
+    team = L.Context(0)
+    rng = np.random.default_rng(3)
+    init = rng.integers(0, g.n // 40, g.n).astype(np.int32)
+    for lam, mode, lab in [(*MOD, None), (*CPM, None), ((0, 1, False), O.VW_UNIT, None), (*CPM, init)]:
+        dev = U.device_graph(g, mode)
+        kw = {} if lab is None else dict(init=torch.from_numpy(lab).cuda())
+        got = [c.cluster(dev, lam, variant, L.lcc_default_options(seed=5), trace_capacity=1 << 14, **kw) for c in (buckets, team)]
+        (la, a), (lb, b) = got
+        assert np.array_equal(la.cpu().numpy(), lb.cpu().numpy()), (name, lam)
+        assert (a.N, a.num_clusters, a.levels, a.flags) == (b.N, b.num_clusters, b.levels, b.flags)
+        assert np.array_equal(a.trace, b.trace)
+    buckets.close()
+    team.close()
+
+
+@pytest.mark.parametrize("name", ["rows", "limit"])
+def test_team_constrained_equals_launches(name):
+    import torch
+    import paper_2608_01503_amd as L
+    g = GRAPHS[name]()
+    buckets = L.Context(0)
+    buckets.profile_enable(["single"])
+    team = L.Context(0)
+    B = torch.from_numpy(np.random.default_rng(4).integers(0, 30, g.n).astype(np.int32)).cuda()
+    dev = U.device_graph(g, CPM[1])
+    (la, a), (lb, b) = [c.cluster(dev, CPM[0], O.PLOUVAIN, L.lcc_default_options(), trace_capacity=1 << 14, constraint=B) for c in (buckets, team)]
+    assert np.array_equal(la.cpu().numpy(), lb.cpu().numpy()) and (a.N, a.levels, a.flags) == (b.N, b.levels, b.flags)
+    assert np.array_equal(a.trace, b.trace)
     buckets.close()
     team.close()
