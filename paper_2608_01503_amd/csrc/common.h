@@ -92,6 +92,7 @@ struct LMSlot {
   int64_t N0;                   // objective numerator of the starting clustering
   int64_t nlab;                 // distinct labels of the clustering the driver ranked after the call
   // a team launch that went on to the next level (team.h)
+  int64_t alt, alt_k, alt_best_k, alt_N;  // the alternate local move's movers, committed prefix and objective
   int64_t refined, refine_n, refine_U, refine_m, cycle;
   int64_t coarse, coarse_nnz, coarse_w2, coarse_boff[NBUCKET + 1];
 };

@@ -81,6 +81,7 @@ struct WS {
   int64_t *seg0, *seg1;  // contraction: entries per coarse row (then the rows' cursors) and the rows' starts
   Tagged tg;      // free-id marks and single-pass scan state (zeroed when the workspace is allocated)
   int64_t* stripes;  // per-workgroup counter partials (zeroed when the workspace is allocated)
+  int64_t* team_best;  // 2 words per member of a team
   TeamHost team;     // control blocks of the team launches (zeroed when the workspace is allocated)
   void* scan_temp;
 };
@@ -127,6 +128,7 @@ size_t carve(WS& w, char* base, int64_t n, int64_t nnz) {
   w.tg.status = c.take<unsigned long long>(w.tg.status_cap);
   w.tg.ticket = c.take<uint32_t>(1);
   w.stripes = c.take<int64_t>((int64_t)NSTRIPE * STRIPE_W);
+  w.team_best = c.take<int64_t>(2 * TEAM_MAX);
   w.team = TeamHost{};
   w.team.ctl = c.take<TeamCtl>(TEAM_SLOTS);
   w.scan_temp = c.take<char>((int64_t)scan_temp_bytes(M + 1));
@@ -398,7 +400,6 @@ struct Level {
   // constraint clustering of the level's vertices (constrained Louvain+ coarsening), or null
   int32_t* B = nullptr;
   bool staged = false;  // built by a team launch and still in the stage; the next one puts it in place
-  bool hubs = true;     // the hub chunks of b are there
 };
 
 __global__ void k_reset_level_counters(Ctrl* c) {
@@ -607,7 +608,9 @@ struct Run {
     a.WB = w.WB; a.aB = w.aB; a.aX = w.aX; a.inU = w.inU; a.flip = w.flip; a.has_child = w.has_child;
     a.H = w.H; a.par = w.par; a.par2 = w.pos_of; a.root = w.root; a.rel = w.fail; a.tsz = w.tsz; a.toff = w.tree_sz;
     a.trees = w.alt_list; a.R = w.in_labels; a.rankR = w.scan_b;
-    a.keys = w.k0;
+    a.keys = w.k0;  // and on into k1, which follows it
+    a.pos = w.pos_of; a.relD = w.par; a.flowC = w.pw; a.flowD = w.pc; a.adj = w.t64a;
+    a.best = (decltype(a.best))w.team_best;
     team_launch(a, w.team, st);
     L.staged = false;
   }
@@ -627,19 +630,10 @@ struct Run {
     N.C = take<int32_t>(ctx, nc);
     N.sum_w2 = S.coarse_w2;
     N.b.list = level_take<int32_t>(nc);
-    N.b.hub_chunk_off = level_take<int32_t>(nc + 1);
     for (int k = 0; k <= NBUCKET; ++k) N.b.off[k] = S.coarse_boff[k];
     N.b.hash_shift = ctx->tune.hash_shift;
     N.staged = true;
-    N.hubs = false;
     lv.push_back(N);
-  }
-
-  // the whole bucket description of a level that a team launch has built, for the launches per bucket
-  void full_buckets(Level& L) {
-    if (L.hubs) return;
-    prepare(L, const_cast<int32_t*>(L.b.list), const_cast<int32_t*>(L.b.hub_chunk_off));
-    L.hubs = true;
   }
 
   // LocalMovePasses on level l from L.C (or singletons, or with TEAM_PROJECT in `more` from the next level's
@@ -908,14 +902,18 @@ struct Run {
       Level& L = lv[l];
       const int64_t n = L.g.n;
       const bool cap = l + 1 >= o.max_levels;
-      int s = local_move_level(l, singleton, 0, nullptr, cap ? 0 : TEAM_REFINE | TEAM_CONTRACT);
+      int s = local_move_level(l, singleton, 0, nullptr, TEAM_ALTERNATE | (cap ? 0 : TEAM_REFINE | TEAM_CONTRACT));
       singleton = false;
       LMSlot S = read_slot(s, n);
       int64_t nc = S.nlab;  // the count of C_l, unless the alternate move below changes it
       int64_t N = S.Nbest;
-      if (S.Nbest == S.N0) {
+      if (S.alt) {
+        if (nslot >= NSLOT) fail(LCC_ERR_INVALID, "too many local-move calls");
+        ++nslot;  // as when the alternate move is a launch sequence of its own
+        N = S.alt_N;
+        rec(3, l, 0, 0, S.alt_k, S.alt_best_k, N, 0);
+      } else if (S.Nbest == S.N0) {
         // C_l unchanged by the local move: the alternate local move (Sec. V-A) from C_l
-        full_buckets(L);
         LMBuffers B = bufs();
         copy_i32(w.C, L.C, n, st);
         launch_cluster_weights(w.C, L.g.vw, n, w.W, st);
@@ -934,10 +932,6 @@ struct Run {
         ctx->pool_release(mark);
         N = q * ctx->h_ctrl->obj_I - p * (ctx->h_ctrl->obj_SW2 - L.sum_w2);
         rec(3, l, 0, 0, ctx->h_ctrl->lmalt_k, ctx->h_ctrl->lmalt_best_k, N, 0);
-        if (small(L) && nc < n && !cap) {
-          team(l, TEAM_REFINE | TEAM_CONTRACT, false, false, s2);
-          S = read_slot(s2, n);
-        }
       }
       rec(2, l, 0, 0, n, L.g.nnz, nc, N);
       if (nc == n) break;

@@ -45,8 +45,9 @@ enum : int32_t {
   TEAM_PLACE = 1,     // put the coarse level that an earlier launch left in the stage into the level's arrays
   TEAM_PROJECT = 2,   // start from the next level's clustering
   TEAM_MOVE = 4,      // LocalMovePasses
-  TEAM_REFINE = 8,    // refinement; the contraction goes by it
-  TEAM_CONTRACT = 16  // build the next level in the stage
+  TEAM_ALTERNATE = 8, // the alternate local move, if the objective is unchanged
+  TEAM_REFINE = 16,   // refinement; the contraction goes by it
+  TEAM_CONTRACT = 32  // build the next level in the stage
 };
 
 // Arguments of a team launch on one level.
@@ -97,7 +98,12 @@ struct TeamArgs {
   int64_t *WB, *aB, *aX;
   uint8_t *inU, *flip, *has_child;
   int32_t *H, *par, *par2, *root, *rel, *tsz, *toff, *trees, *R, *rankR;
-  uint64_t* keys;
+  uint64_t* keys;               // 2 n
+  // alternate local move: movers in ascending order, the flow into a mover's own cluster and into its destination
+  // before it, the adjacent part of its gain; every member's best prefix
+  int32_t *pos, *relD;
+  int64_t *flowC, *flowD, *adj;
+  struct { int64_t v; int64_t i; }* best;
 };
 
 #ifndef TEAM_KERNARG

@@ -1,7 +1,7 @@
 // Small levels: everything that a level takes up to the host's next decision, as one launch of a team (team.h): the
-// level put in place, the local move, the refinement and the contraction.
+// level put in place, the local move and the alternate one, the refinement and the contraction.
 //
-// The same method as lm.hip, refine.hip and contract.hip, with the same integer forms and the same results, laid out
+// The same method as lm.hip, lmalt.hip, refine.hip and contract.hip, with the same integer forms and the same results, laid out
 // for levels whose phases take a few microseconds each.  Local move: counters stay in registers (every member sums the
 // same partials), the moves are applied where the afterburner keeps them, cluster sizes are kept beside the weights so
 // that free ids need no marking pass, and repeated passes cost nothing.  Refinement: trees are ordered by counting
@@ -11,7 +11,8 @@
 //
 // With only the local move in one launch a level still took 35 launches and 4 host reads for the contraction and 40
 // and 2 for the refinement; now it takes one launch and one read.  SBM graph of 2,000 vertices, Louvain+: 1058 -> 640
-// us a call; kNN graph of 3,000, pLeiden+: 5277 -> 2683 us; R-MAT graph of 2^14, pLeiden: 27.3 -> 14.6 ms.
+// us a call; kNN graph of 3,000, pLeiden+: 5277 -> 2683 us; R-MAT graph of 2^14, pLeiden: 27.3 -> 14.6 ms.  The
+// alternate local move, about 30 launches and 2 reads where it is taken, joined them: 2683 -> 1594 us and 14.6 -> 11.5 ms.
 #include <algorithm>
 
 #include "team.h"
@@ -79,12 +80,13 @@ __device__ __forceinline__ uint64_t agg_flush(int64_t* W, int32_t* cnt) {
 struct TeamAcc {
   int32_t ncand = 0;
   int64_t own = 0;
+  int strict = 0;  // a move has to improve strictly
 };
 
 __device__ __forceinline__ void team_finish(KP kp, int32_t v, int32_t cv, int64_t wv, int64_t own, int64_t sbest,
                                             int32_t cbest, int64_t wcv, uint32_t pa, uint32_t pb, TeamAcc& a) {
   const int64_t scur = kp->sc.q * own - kp->sc.p * wv * (wcv - wv);
-  const Verdict vd = decide(scur, sbest, cbest, pa, pb, 0);
+  const Verdict vd = decide(scur, sbest, cbest, pa, pb, a.strict);
   VState o;
   o.c = cv;
   o.d = vd.d;
@@ -532,11 +534,10 @@ struct InternalOp {
 };
 
 // The starting state: cluster weights and sizes of C_out (or singletons), C = C_out.
-__device__ __forceinline__ void team_start(Team& t, KP kp) {
+__device__ __forceinline__ void team_start(Team& t, KP kp, bool single, bool up) {
   TEAM_PHASE(kp);
   const int tx = team_tx(), n = kp->n, t0 = t.rank * TEAM_BLOCK + tx;
-  const bool up = kp->steps & TEAM_PROJECT;
-  if (kp->singleton) {
+  if (single) {
     for (int v = t0; v < n; v += t.threads()) {
       ast(kp->C + v, v);
       ast(kp->Cout + v, v);
@@ -576,7 +577,7 @@ __device__ __forceinline__ bool team_local_move(Team& t, const KP kp0) {
   KP kp = kp0;
   TEAM_PHASE(kp);
   const bool log = t.rank == 0 && team_tx() == 0;
-  team_start(t, kp);
+  team_start(t, kp, kp->singleton, kp->steps & TEAM_PROJECT);
   int64_t sw2 = 0, I = 0, Nbest = 0, N0 = 0, nL = 0, nM = 0;
   bool first = true, skipped = false;
   const int limit = kp->pass_limit;
@@ -1148,12 +1149,11 @@ __device__ __forceinline__ int group_below64(uint64_t key) {
   }
 }
 
-// a tree of m <= G members at keys[b ..]: in the order of f, the longest valid prefix takes the root's id
+// The m <= G keys of a group of lanes in ascending order (the group's lanes from m on: any key).
 template <int G>
-__device__ __forceinline__ void team_tree_lanes(KP kp, int32_t r, int b, int m, int gl) {
-  const int lane = team_tx() & (WAVE - 1);
-  int32_t* slot = lds.wave.k[uniform32(team_tx() / WAVE)];
-  const uint64_t key = gl < m ? ald(kp->keys + b + gl) : ~0ull;
+__device__ __forceinline__ uint64_t team_order(uint64_t key, int m, int gl) {
+  const int tx = team_tx(), lane = tx & (WAVE - 1);
+  uint64_t* slot = (uint64_t*)lds.wave.k[uniform32(tx / WAVE)];
   int at = 0;
   if constexpr (G == WAVE) {
     for (int l = 0; l < m; ++l) {
@@ -1162,13 +1162,22 @@ __device__ __forceinline__ void team_tree_lanes(KP kp, int32_t r, int b, int m, 
       at += o < key;
     }
   } else {
-    at = group_below64<G>(key);
+    at = group_below64<G>(gl < m ? key : ~0ull);
   }
-  if (gl < m) slot[lane - gl + at] = (int32_t)(key & TREE_MASK);
+  if (gl < m) slot[lane - gl + at] = key;
   lds_order();
+  const uint64_t r = slot[lane];
+  lds_order();
+  return r;
+}
+
+// a tree of m <= G members at keys[b ..]: in the order of f, the longest valid prefix takes the root's id
+template <int G>
+__device__ __forceinline__ void team_tree_lanes(KP kp, int32_t r, int b, int m, int gl) {
+  const int lane = team_tx() & (WAVE - 1);
   const bool has = gl < m;
-  const int32_t v = has ? slot[lane] : r;
-  lds_order();
+  const uint64_t key = team_order<G>(has ? ald(kp->keys + b + gl) : ~0ull, m, gl);
+  const int32_t v = has ? (int32_t)(key & TREE_MASK) : r;
   const int64_t w = has ? kp->vw[v] : 0, ax = has ? ald(kp->aX + v) : 0, tc = has ? ald(kp->aB + v) - 2 * ax : 0;
   const int64_t sw = scan64<G>(w), sc = scan64<G>(tc);
   const bool bad = has && !team_valid(kp, ax, w, sw - w, sc - tc, ald(kp->WB + ald(kp->Cout + r)));
@@ -1218,21 +1227,27 @@ __device__ __forceinline__ void team_block_sums(int64_t& x, int64_t& y, int64_t&
   __syncthreads();
 }
 
+// The m keys at g sorted by the workgroup, in LDS (returned true: they are in lds.sort then) or where they are.
+__device__ __forceinline__ bool team_sort_keys(uint64_t* g, int m) {
+  const int tx = team_tx();
+  __syncthreads();
+  if (m > TS_SLOTS) {
+    team_sort(m, [&](int i) __attribute__((always_inline)) { return ald(g + i); },
+              [&](int i, uint64_t k) __attribute__((always_inline)) { ast(g + i, k); });
+    return false;
+  }
+  for (int i = tx; i < m; i += TEAM_BLOCK) lds.sort[i] = ald(g + i);
+  __syncthreads();
+  team_sort(m, [&](int i) __attribute__((always_inline)) { return lds.sort[i]; },
+            [&](int i, uint64_t k) __attribute__((always_inline)) { lds.sort[i] = k; });
+  return true;
+}
+
 // trees of more than 64 members, the workgroup each
 __device__ __forceinline__ void team_tree_blk(KP kp, int32_t r, int b, int m) {
   const int tx = team_tx();
   uint64_t* g = kp->keys + b;
-  const bool in_lds = m <= TS_SLOTS;
-  __syncthreads();
-  if (in_lds) {
-    for (int i = tx; i < m; i += TEAM_BLOCK) lds.sort[i] = ald(g + i);
-    __syncthreads();
-    team_sort(m, [&](int i) __attribute__((always_inline)) { return lds.sort[i]; },
-              [&](int i, uint64_t k) __attribute__((always_inline)) { lds.sort[i] = k; });
-  } else {
-    team_sort(m, [&](int i) __attribute__((always_inline)) { return ald(g + i); },
-              [&](int i, uint64_t k) __attribute__((always_inline)) { ast(g + i, k); });
-  }
+  const bool in_lds = team_sort_keys(g, m);
   const int64_t wB = ald(kp->WB + ald(kp->Cout + r));
   int64_t cw = 0, cc = 0;
   if (tx == 0) team_sh.cursor[0] = m;
@@ -1257,6 +1272,227 @@ __device__ __forceinline__ void team_tree_blk(KP kp, int32_t r, int b, int m) {
     ast(kp->R + v, i < first ? r : v);
   }
   __syncthreads();
+}
+
+// --- alternate local move (Sec. V-A) from C_out; the gains are defined in lmalt.hip.  Mover i is the i-th vertex that
+// is not node optimal.  Every mover has an event in its own cluster (its weight leaves) and one in its destination, if
+// that is a cluster (its weight enters); the flow before a mover into either is the sum of the earlier events there, so
+// the events of a cluster are put in mover order and scanned.
+
+// adjacent part of the gain: earlier movers are those of smaller id
+struct AdjOp {
+  template <int U>
+  __device__ __forceinline__ int64_t part(KP kp, int32_t v, const VState& me, int x, int S) {
+    return team_row_sum<U>(kp, (int)kp->off[v], (int)kp->off[v + 1], x, S,
+                           [&](int32_t u) __attribute__((always_inline)) { return ald((const uint64_t*)&kp->vs[u]); },
+                           [&](uint64_t cd, int32_t u, int32_t w) __attribute__((always_inline)) {
+                             const int32_t c = (int32_t)(uint32_t)cd, d = (int32_t)(cd >> 32);
+                             return u < v && d != D_NONE ? (int64_t)ab_pattern(me.c, me.d, c, d) * w : 0;
+                           });
+  }
+  template <int G>
+  __device__ __forceinline__ void group(KP kp, int32_t v, int gl) {
+    const VState me = ald_state(kp->vs, v);
+    if (me.d == D_NONE) return;  // uniform over the group
+    const int64_t s = sum_steps<G>(part<1>(kp, v, me, gl, G));
+    if (gl == 0) ast(kp->adj + v, s);
+  }
+  __device__ __forceinline__ void wave(KP kp, int32_t v, int lane) {
+    const VState me = ald_state(kp->vs, v);
+    if (me.d == D_NONE) return;
+    const int64_t s = wave_sum64(part<2>(kp, v, me, lane, WAVE));
+    if (lane == 0) ast(kp->adj + v, s);
+  }
+};
+
+// key of an event: mover's vertex << 1 | 1 when its weight enters
+__device__ __forceinline__ int64_t team_event(KP kp, uint64_t key) {
+  const int64_t w = kp->vw[key >> 1];
+  return key & 1 ? w : -w;
+}
+__device__ __forceinline__ void team_flow(KP kp, uint64_t key, int64_t before) {
+  ast((key & 1 ? kp->flowD : kp->flowC) + (key >> 1), before);
+}
+template <int G>
+__device__ __forceinline__ void team_flow_lanes(KP kp, int b, int m, int gl) {
+  const bool has = gl < m;
+  const uint64_t key = team_order<G>(has ? ald(kp->keys + b + gl) : ~0ull, m, gl);
+  const int64_t x = has ? team_event(kp, key) : 0;
+  const int64_t s = scan64<G>(x);
+  if (has) team_flow(kp, key, s - x);
+}
+__device__ __forceinline__ void team_flow_blk(KP kp, int b, int m) {
+  const int tx = team_tx();
+  uint64_t* g = kp->keys + b;
+  const bool in_lds = team_sort_keys(g, m);
+  int64_t run = 0;
+  for (int i0 = 0; i0 < m; i0 += TEAM_BLOCK) {  // uniform over the workgroup
+    const int i = i0 + tx;
+    const uint64_t key = i < m ? (in_lds ? lds.sort[i] : ald(g + i)) : 0;
+    const int64_t x = i < m ? team_event(kp, key) : 0;
+    int64_t s = x, zero = 0, tot, none;
+    team_block_sums(s, zero, tot, none);
+    if (i < m) team_flow(kp, key, run + s - x);
+    run += tot;
+  }
+  __syncthreads();
+}
+
+// better prefix: the larger sum, then the shorter prefix
+__device__ __forceinline__ bool team_longer(int64_t v, int64_t i, int64_t bv, int64_t bi) { return v > bv || (v == bv && i < bi); }
+
+// The alternate move from C_out.
+__device__ __forceinline__ void team_alternate(Team& t, KP kp) {
+  team_start(t, kp, false, false);
+  TEAM_PHASE(kp);
+  const int n = kp->n;
+  int64_t sw2 = team_sw2(t, kp);
+  {
+    TeamAcc a;
+    a.strict = 1;
+    EnumOp op{1, 1, a};
+    team_tasks(t, kp, op);
+    a = op.a;
+    team_enum_blk(t, kp, 1, 1, a);
+    team_each(t, kp, n, [](KP kp, int c) __attribute__((always_inline)) { ast(kp->tsz + c, 0); });
+    const Sum3 x = t.sum(a.ncand, a.own, sw2);
+    sw2 = x.c;
+    if (t.rank == 0 && team_tx() == 0) {
+      kp->slot->alt = 1;
+      kp->slot->alt_k = x.a;
+      kp->slot->alt_N = kp->sc.q * x.b - kp->sc.p * (sw2 - kp->sum_w2);
+    }
+    if (!x.a) return;
+  }
+  team_each(t, kp, n, [](KP kp, int v) __attribute__((always_inline)) {
+    const uint64_t cd = ald((const uint64_t*)&kp->vs[v]);
+    const int32_t c = (int32_t)(uint32_t)cd, d = (int32_t)(cd >> 32);
+    if (d == D_NONE) return;
+    ast(kp->rel + v, atomicAdd(kp->tsz + c, 1));
+    if (d != D_EMPTY) ast(kp->relD + v, atomicAdd(kp->tsz + d, 1));
+  });
+  {
+    AdjOp op;
+    team_tasks(t, kp, op);
+  }
+  t.sync();
+  TEAM_PHASE(kp);
+  t.lists<3>(n, kp->toff, kp->trees, 0, [&](int c, int& cls, int& size) __attribute__((always_inline)) {
+    size = ald(kp->tsz + c);
+    if (size) cls = size <= 16 ? 0 : size <= WAVE ? 1 : 2;
+  });
+  t.sync();
+  team_each(t, kp, n, [](KP kp, int v) __attribute__((always_inline)) {
+    const uint64_t cd = ald((const uint64_t*)&kp->vs[v]);
+    const int32_t c = (int32_t)(uint32_t)cd, d = (int32_t)(cd >> 32);
+    if (d == D_NONE) return;
+    ast(kp->keys + ald(kp->toff + c) + ald(kp->rel + v), (uint64_t)(uint32_t)v << 1);
+    if (d != D_EMPTY) ast(kp->keys + ald(kp->toff + d) + ald(kp->relD + v), (uint64_t)(uint32_t)v << 1 | 1);
+  });
+  t.sync();
+  TEAM_PHASE(kp);
+  {
+    const int tx = team_tx(), lane = tx & (WAVE - 1), wv = uniform32(tx / WAVE);
+    const int f1 = uniform32(team_sh.first[1]), f2 = uniform32(team_sh.first[2]), f3 = uniform32(team_sh.first[3]);
+    for (int i = f2 + t.rank; i < f3; i += t.n) {
+      const int32_t c = uniform32(ald(kp->trees + i));
+      team_flow_blk(kp, uniform32(ald(kp->toff + c)), uniform32(ald(kp->tsz + c)));
+    }
+    const int nw = f2 - f1, all = nw + (f1 + 3) / 4;
+    for (int x = wv * t.n + t.rank; x < all; x += t.n * TEAM_WAVES) {
+      if (x < nw) {
+        const int32_t c = uniform32(ald(kp->trees + f1 + x));
+        team_flow_lanes<WAVE>(kp, uniform32(ald(kp->toff + c)), uniform32(ald(kp->tsz + c)), lane);
+      } else {
+        const int i = (x - nw) * 4 + lane / 16;
+        if (i < f1) {
+          const int32_t c = ald(kp->trees + i);
+          team_flow_lanes<16>(kp, ald(kp->toff + c), ald(kp->tsz + c), lane & 15);
+        }
+      }
+    }
+  }
+  t.sync();
+  // gains in mover order, their running sums, and the shortest prefix with the largest one; every member scans its
+  // share of the vertices
+  TEAM_PHASE(kp);
+  const auto gain = [&](int v, int32_t& mover) __attribute__((always_inline)) {
+    const VState me = ald_state(kp->vs, v);
+    mover = me.d != D_NONE;
+    if (!mover) return (int64_t)0;
+    const int64_t fB = me.d == D_EMPTY ? 0 : ald(kp->flowD + v);
+    // half the exact objective change of the move (below 2^62): its terms are summed modulo 2^64
+    return (int64_t)((uint64_t)me.delta + (uint64_t)(kp->sc.q * ald(kp->adj + v)) -
+                     (uint64_t)(kp->sc.p * kp->vw[v] * (fB - ald(kp->flowC + v))));
+  };
+  const int lo = t.share_lo(n), hi = t.share_hi(n);
+  int64_t s = 0;
+  int32_t c = 0;
+  for (int v = lo + team_tx(); v < hi; v += TEAM_BLOCK) {
+    int32_t mover;
+    s += gain(v, mover);
+    c += mover;
+  }
+  Sum2 pre;
+  t.sum(s, c, pre);
+  int64_t bv = 0, bi = INT64_MAX;  // no prefix yet; a prefix must beat 0
+  for (int v0 = lo; v0 < hi; v0 += TEAM_BLOCK) {  // uniform over the workgroup
+    const int v = v0 + team_tx();
+    int32_t mover = 0;
+    int64_t g = 0, ts, tc;
+    if (v < hi) g = gain(v, mover);
+    int64_t num = mover;
+    team_block_sums(g, num, ts, tc);
+    const int64_t sum = pre.a + g, at = pre.b + num - 1;
+    if (v < hi) ast(kp->pos + v, (int32_t)at);  // for movers
+    if (mover && sum > 0 && team_longer(sum, at, bv, bi)) { bv = sum; bi = at; }
+    pre.a += ts;
+    pre.b += tc;
+  }
+#pragma unroll
+  for (int o = 1; o < WAVE; o <<= 1) {
+    const int64_t ov = __shfl_xor(bv, o, WAVE), oi = __shfl_xor(bi, o, WAVE);
+    if (team_longer(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+  }
+  {
+    const int tx = team_tx();
+    if ((tx & (WAVE - 1)) == 0) { team_sh.red[0][tx / WAVE] = bv; team_sh.red[1][tx / WAVE] = bi; }
+    __syncthreads();
+    if (tx == 0) {
+      for (int x = 1; x < TEAM_WAVES; ++x)
+        if (team_longer(team_sh.red[0][x], team_sh.red[1][x], bv, bi)) { bv = team_sh.red[0][x]; bi = team_sh.red[1][x]; }
+      ast(&kp->best[t.rank].v, bv);
+      ast(&kp->best[t.rank].i, bi);
+    }
+  }
+  t.sync();
+  bv = 0;
+  bi = INT64_MAX;
+  for (int r = 0; r < t.n; ++r) {
+    const int64_t ov = uniform64(ald(&kp->best[r].v)), oi = uniform64(ald(&kp->best[r].i));
+    if (team_longer(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+  }
+  const int kb = bv > 0 ? (int)bi + 1 : 0;
+  // the movers of the prefix move
+  agg_clear();
+  TeamKeep kk;
+  team_each(t, kp, n, [&](KP kp, int v) __attribute__((always_inline)) {
+    const VState me = ald_state(kp->vs, v);
+    team_apply(kp, v, me, me.d != D_NONE && ald(kp->pos + v) < kb, false, kk);
+  });
+  kk.dsq += agg_flush(kp->W, kp->cnt);
+  const Sum2 y = t.sum(kk.ne, (int64_t)kk.dsq);
+  sw2 = (int64_t)((uint64_t)sw2 + (uint64_t)y.b);
+  if (y.a) team_empty(t, kp, (int)y.a, sw2);
+  TEAM_PHASE(kp);
+  InternalOp op{kp->C, 0};
+  team_tasks(t, kp, op);
+  team_each(t, kp, n, [](KP kp, int v) __attribute__((always_inline)) { ast(kp->Cout + v, ald(kp->C + v)); });
+  const int64_t I = t.sum(op.s).a;
+  if (t.rank == 0 && team_tx() == 0) {
+    kp->slot->alt_best_k = kb;
+    kp->slot->alt_N = kp->sc.q * I - kp->sc.p * (sw2 - kp->sum_w2);
+  }
 }
 
 // R = refinement of C_out
@@ -1358,12 +1594,13 @@ __global__ __launch_bounds__(TEAM_BLOCK) void k_team_level(TeamArgs args) {
   for (int k = team_tx(); t.rank == 0 && k < (int)(sizeof(LMSlot) / 8); k += TEAM_BLOCK) ast((int64_t*)kp->slot + k, (int64_t)0);
   const int steps = kp->steps, n = kp->n;
   if (steps & TEAM_PLACE) team_place(t, kp);
-  // an unchanged C_out goes through the alternate local move before it is refined
-  bool on = true;
-  if (steps & TEAM_MOVE) on = team_local_move(t, kp) || !(steps & TEAM_REFINE);
+  if (steps & TEAM_MOVE) {
+    // C_out unchanged: the alternate local move
+    if (!team_local_move(t, kp) && (steps & TEAM_ALTERNATE)) team_alternate(t, kp);
+  }
   int nc = team_rank(t, kp, kp->Cout, kp->rank);
   if (t.rank == 0 && team_tx() == 0) kp->slot->nlab = nc;
-  on = on && nc < n && (steps & TEAM_CONTRACT);
+  bool on = nc < n && (steps & TEAM_CONTRACT);
   if (on && (steps & TEAM_REFINE)) {
     team_refine(t, kp);
     nc = team_rank(t, kp, kp->R, kp->rankR);

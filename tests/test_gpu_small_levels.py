@@ -77,10 +77,13 @@ def test_team_next_level_equals_launches(name, variant):
     team = L.Context(0)
     rng = np.random.default_rng(3)
     init = rng.integers(0, g.n // 40, g.n).astype(np.int32)
-    for lam, mode, lab in [(*MOD, None), (*CPM, None), ((0, 1, False), O.VW_UNIT, None), (*CPM, init)]:
+    # without passes the alternate move decides: from three clusters its events fill a workgroup's sort and more
+    few = rng.integers(0, 3, g.n).astype(np.int32)
+    for lam, mode, lab, opt in [(*MOD, None, {}), (*CPM, None, {}), ((0, 1, False), O.VW_UNIT, None, {}), (*CPM, init, {}),
+                                (*CPM, init, dict(pass_limit=0)), (*CPM, few, dict(pass_limit=0)), (*MOD, few, dict(pass_limit=0))]:
         dev = U.device_graph(g, mode)
         kw = {} if lab is None else dict(init=torch.from_numpy(lab).cuda())
-        got = [c.cluster(dev, lam, variant, L.lcc_default_options(seed=5), trace_capacity=1 << 14, **kw) for c in (buckets, team)]
+        got = [c.cluster(dev, lam, variant, L.lcc_default_options(seed=5, **opt), trace_capacity=1 << 14, **kw) for c in (buckets, team)]
         (la, a), (lb, b) = got
         assert np.array_equal(la.cpu().numpy(), lb.cpu().numpy()), (name, lam)
         assert (a.N, a.num_clusters, a.levels, a.flags) == (b.N, b.num_clusters, b.levels, b.flags)
