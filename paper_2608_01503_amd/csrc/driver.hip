@@ -580,6 +580,7 @@ struct Run {
     a.vw = const_cast<int64_t*>(L.g.vw);
     a.list = const_cast<int32_t*>(L.b.list);
     for (int k = 0; k <= NBUCKET; ++k) a.boff[k] = (int32_t)L.b.off[k];
+    a.rows = (uint64_t*)w.hub_ps;
     a.hash_shift = L.b.hash_shift;
     a.bounds = ctx->bounds();
     a.sc = sc;

@@ -25,7 +25,7 @@ constexpr int TEAM_WAVES = TEAM_BLOCK / WAVE;
 constexpr int TEAM_MAX = 32;                // members: the CUs of an XCD
 constexpr int TEAM_GRID = 8 * TEAM_MAX;     // workgroups launched (they spread over the XCDs in turn)
 constexpr unsigned long long TEAM_WAIT = 300;  // 3 us of the 100 MHz clock
-constexpr int TEAM_VALS = 6;                // values summed at one boundary
+constexpr int TEAM_VALS = 5;                // values summed at one boundary
 constexpr int TEAM_SLOTS = 2;               // control blocks: a launch uses one and clears the next launch's
 
 // One launch's control block (zero when the launch starts).
@@ -62,6 +62,7 @@ struct TeamArgs {
   int64_t* vw;
   int32_t* list;                // vertices by degree bucket, bucket b at [boff[b], boff[b + 1])
   int32_t boff[NBUCKET + 1];
+  uint64_t* rows;               // the list with the rows' places: row_of(v, first entry, length)
   int32_t hash_shift;
   BucketBounds bounds;
   Score sc;
@@ -190,7 +191,6 @@ __shared__ TeamShared team_sh;
 struct Sum1 { int64_t a; };
 struct Sum2 { int64_t a, b; };
 struct Sum3 { int64_t a, b, c; };
-struct Sum6 { int64_t a, b, c, d, e, f; };
 
 struct Team {
   TeamCtl* c;
@@ -262,11 +262,13 @@ struct Team {
     asm volatile("" ::: "memory");
     __syncthreads();
   }
-  // The same, and plain loads see it too (the CU's L1 is emptied): before reading arrays the team has built with
-  // ordinary loads.
+  // The same, and plain loads see it too: before reading arrays the team has built with ordinary loads.  The members
+  // share their L2, so emptying the CU's L1 is enough (the invalidation of workgroup scope; that of an agent-scope
+  // fence goes on to the L2 and took 27 us).  Use: arrays whose every byte is stored once and that nothing has loaded
+  // before in the launch, so that an L1 holds at most what its own CU stored.
   __device__ __forceinline__ void sync_all() {
     sync();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    asm volatile("buffer_inv sc0\n\ts_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
   }
 
@@ -323,15 +325,6 @@ struct Team {
     return r;
   }
   // The same, and the sums over the members of lower rank.
-  __device__ __forceinline__ Sum6 sum(int64_t a, int64_t b, int64_t d, int64_t e, int64_t f, int64_t g, Sum6& pre) {
-    put<0>(a); put<1>(b); put<2>(d); put<3>(e); put<4>(f); put<5>(g);
-    sums<6>();
-    const int64_t *s = team_sh.tot, *p = team_sh.pre;
-    Sum6 r{uniform64(s[0]), uniform64(s[1]), uniform64(s[2]), uniform64(s[3]), uniform64(s[4]), uniform64(s[5])};
-    pre = Sum6{uniform64(p[0]), uniform64(p[1]), uniform64(p[2]), uniform64(p[3]), uniform64(p[4]), uniform64(p[5])};
-    __syncthreads();
-    return r;
-  }
   __device__ __forceinline__ Sum1 sum(int64_t a, Sum1& pre) {
     put<0>(a);
     sums<1>();
@@ -388,13 +381,19 @@ struct Team {
         c2 += cls >= 6 ? one : 0;
       }
     }
-    Sum6 pre;
-    const Sum6 tot = sum(s, (int64_t)c0, (int64_t)c1, (int64_t)c2, extra, 0, pre);
+    put<0>(s);
+    put<1>(extra);
+    if constexpr (K > 0) put<2>((int64_t)c0);
+    if constexpr (K > 3) put<3>((int64_t)c1);
+    if constexpr (K > 6) put<4>((int64_t)c2);
+    sums<2 + (K + 2) / 3>();
+    const Sum2 tot{uniform64(team_sh.tot[0]), uniform64(team_sh.tot[1])};
+    int run = uniform32((int)team_sh.pre[0]);
     if (K > 0 && tx < K) {
       int at = 0;
 #pragma unroll
       for (int c = 0; c < K; ++c) {
-        const int64_t t3 = c < 3 ? tot.b : c < 6 ? tot.c : tot.d, p3 = c < 3 ? pre.b : c < 6 ? pre.c : pre.d;
+        const int64_t t3 = team_sh.tot[2 + c / 3], p3 = team_sh.pre[2 + c / 3];
         const int num = (int)((uint64_t)t3 >> (21 * (c % 3)) & 0x1FFFFF), low = (int)((uint64_t)p3 >> (21 * (c % 3)) & 0x1FFFFF);
         if (tx == c) { team_sh.first[c] = at; team_sh.cursor[c] = at + low; }
         at += num;
@@ -402,7 +401,6 @@ struct Team {
       if (tx == 0) team_sh.first[K] = at;
     }
     __syncthreads();
-    int run = (int)pre.a;
     const int lane = tx & (WAVE - 1);
     for (int i0 = lo; i0 < hi; i0 += TEAM_BLOCK) {  // uniform over the workgroup
       const int i = i0 + tx;
@@ -423,7 +421,7 @@ struct Team {
       }
     }
     if (rank == n - 1 && tx == 0) ast(off + m, (int32_t)tot.a);
-    return Sum2{tot.a, tot.e};
+    return tot;
   }
 
   // this member's share [lo, hi) of m items

@@ -103,10 +103,30 @@ __device__ __forceinline__ void team_each(const Team& t, KP kp, int m, F f) {
   for (int i = t.rank * TEAM_BLOCK + team_tx(); i < m; i += t.threads()) f(kp, i);
 }
 
+// A row in one word, so that a pass finds vertex, first entry and length with one load per row.
+struct TeamRow { int32_t v; int b, d; };
+constexpr int ROW_V = 20, ROW_B = 22;
+static_assert(TEAM_ENTRIES / 4 < (int64_t)1 << ROW_V && TEAM_ENTRIES < (int64_t)1 << ROW_B, "row words");
+__device__ __forceinline__ uint64_t row_word(int32_t v, int b, int d) {
+  return (uint64_t)(uint32_t)d << (ROW_V + ROW_B) | (uint64_t)(uint32_t)b << ROW_V | (uint32_t)v;
+}
+__device__ __forceinline__ TeamRow row_of(uint64_t x) {
+  return TeamRow{(int32_t)(x & ((1u << ROW_V) - 1)), (int)(x >> ROW_V & ((1u << ROW_B) - 1)), (int)(x >> (ROW_V + ROW_B))};
+}
+__device__ __forceinline__ TeamRow uniform_row(uint64_t x) { return row_of((uint64_t)uniform64((int64_t)x)); }
+
+__device__ __forceinline__ void team_row_words(const Team& t, KP kp) {
+  team_each(t, kp, kp->n, [](KP kp, int i) __attribute__((always_inline)) {
+    const int32_t v = kp->list[i];
+    ast(kp->rows + i, row_word(v, (int)kp->off[v], (int)(kp->off[v + 1] - kp->off[v])));
+  });
+}
+
 // Work of a pass over the rows: a wavefront takes 64 / G vertices of a bucket of G-lane groups (G = 4, 8, 16, 32)
 // or one longer row at a time.  All buckets form one list of such tasks, the long rows first, dealt to the members
 // in turn: a wavefront goes through one dependent chain of loads per task it gets, not one per bucket (with a loop
-// per bucket a pass over 27,000 entries took 28 us, most of it six such chains one after the other).
+// per bucket a pass over 27,000 entries took 28 us, most of it six such chains one after the other).  The next task's
+// row words are loaded before a task is worked on.
 template <typename Op>
 __device__ __forceinline__ void team_tasks(const Team& t, KP kp, Op& op) {
   TEAM_PHASE(kp);
@@ -114,21 +134,46 @@ __device__ __forceinline__ void team_tasks(const Team& t, KP kp, Op& op) {
   const int e0 = kp->boff[1], e1 = kp->boff[2], e2 = kp->boff[3], e3 = kp->boff[4], e4 = kp->boff[NBUCKET];
   const int n4 = e4 - e3, n3 = n4 + (e3 - e2 + 1) / 2, n2 = n3 + (e2 - e1 + 3) / 4, n1 = n2 + (e1 - e0 + 7) / 8,
             n0 = n1 + (e0 + 15) / 16;
+  const auto word = [&](int k) __attribute__((always_inline)) {  // ~0: no row for this lane
+    int i, end;
+    if (k < n4) i = e4 - 1 - k, end = e4;  // the longest buckets are at the end of the list
+    else if (k < n3) i = e2 + (k - n4) * 2 + lane / 32, end = e3;
+    else if (k < n2) i = e1 + (k - n3) * 4 + lane / 16, end = e2;
+    else if (k < n1) i = e0 + (k - n2) * 8 + lane / 8, end = e1;
+    else i = (k - n1) * 16 + lane / 4, end = k < n0 ? e0 : 0;
+    return i < end ? ald(kp->rows + i) : ~0ull;
+  };
+  uint64_t next = word(wv * t.n + t.rank);
   for (int k = wv * t.n + t.rank; k < n0; k += t.n * TEAM_WAVES) {
+    const uint64_t x = next;
+    next = word(k + t.n * TEAM_WAVES);
     if (k < n4) {
-      op.wave(kp, uniform32(kp->list[e4 - 1 - k]), lane);  // the longest buckets are at the end of the list
+      op.wave(kp, uniform_row(x), lane);
     } else if (k < n3) {
-      const int i = e2 + (k - n4) * 2 + lane / 32;
-      if (i < e3) op.template group<32>(kp, kp->list[i], lane & 31);
+      if (x != ~0ull) op.template group<32>(kp, row_of(x), lane & 31);
     } else if (k < n2) {
-      const int i = e1 + (k - n3) * 4 + lane / 16;
-      if (i < e2) op.template group<16>(kp, kp->list[i], lane & 15);
+      if (x != ~0ull) op.template group<16>(kp, row_of(x), lane & 15);
     } else if (k < n1) {
-      const int i = e0 + (k - n2) * 8 + lane / 8;
-      if (i < e1) op.template group<8>(kp, kp->list[i], lane & 7);
+      if (x != ~0ull) op.template group<8>(kp, row_of(x), lane & 7);
     } else {
-      const int i = (k - n1) * 16 + lane / 4;
-      if (i < e0) op.template group<4>(kp, kp->list[i], lane & 3);
+      if (x != ~0ull) op.template group<4>(kp, row_of(x), lane & 3);
+    }
+  }
+}
+
+// f(row) for this member's rows above `min` entries (min >= 128), by the whole workgroup.  Every wavefront looks at 64
+// of the member's rows at a time.
+template <typename F>
+__device__ __forceinline__ void team_long(const Team& t, KP kp, int min, F f) {
+  TEAM_PHASE(kp);
+  const int lane = team_tx() & (WAVE - 1), end = kp->boff[NBUCKET];
+  for (int i0 = kp->boff[5] + t.rank; i0 < end; i0 += t.n * WAVE) {  // uniform over the workgroup
+    const int i = i0 + lane * t.n;
+    const uint64_t x = i < end ? ald(kp->rows + i) : 0;
+    for (uint64_t m = __ballot(row_of(x).d > min); m; m &= m - 1) {
+      const int l = __ffsll((unsigned long long)m) - 1;
+      const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, l), hi = (uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), l);
+      f(row_of((uint64_t)hi << 32 | lo));
     }
   }
 }
@@ -138,13 +183,14 @@ struct SingleOp {
   uint32_t pa, pb;
   TeamAcc a;
   template <int U, int G>
-  __device__ __forceinline__ void row(KP kp, int32_t v, int gl) {
+  __device__ __forceinline__ void row(KP kp, const TeamRow& r, int gl) {
+    const int32_t v = r.v;
     const int64_t wv = kp->vw[v];
-    const int e = (int)kp->off[v + 1];
+    const int e = r.b + r.d;
     const int32_t bv = kp->cons ? kp->cons[v] : 0;
     int64_t bs = INT64_MIN;
     int32_t bc = INT32_MAX;
-    for (int j0 = (int)kp->off[v] + gl; j0 < e; j0 += U * G) {
+    for (int j0 = r.b + gl; j0 < e; j0 += U * G) {
       int32_t us[U], ws[U];
       int64_t vu[U];
 #pragma unroll
@@ -166,8 +212,8 @@ struct SingleOp {
     if (gl == 0) team_finish(kp, v, v, wv, 0, bs, bc, wv, pa, pb, a);
   }
   template <int G>
-  __device__ __forceinline__ void group(KP kp, int32_t v, int gl) { row<1, G>(kp, v, gl); }
-  __device__ __forceinline__ void wave(KP kp, int32_t v, int lane) { row<4, WAVE>(kp, v, lane); }
+  __device__ __forceinline__ void group(KP kp, const TeamRow& r, int gl) { row<1, G>(kp, r, gl); }
+  __device__ __forceinline__ void wave(KP kp, const TeamRow& r, int lane) { row<4, WAVE>(kp, r, lane); }
 };
 
 // The row [b, e) into an LDS hash, by S lanes of which this is lane x; returns the lane's share of the weight to
@@ -241,8 +287,9 @@ struct EnumOp {
   TeamAcc a;
   // rows of at most G E entries, E per lane: clusters summed by an all-pairs sweep or by leaders
   template <int G, int E>
-  __device__ __forceinline__ void row(KP kp, int32_t v, int gl) {
-    const int rb = (int)kp->off[v], d = (int)kp->off[v + 1] - rb;
+  __device__ __forceinline__ void row(KP kp, const TeamRow& r, int gl) {
+    const int32_t v = r.v;
+    const int rb = r.b, d = r.d;
     const int32_t cv = ald(kp->C + v);
     const int64_t wv = kp->vw[v];
     const int32_t bv = kp->cons ? kp->cons[v] : 0;
@@ -285,12 +332,13 @@ struct EnumOp {
     if (gl == 0) team_finish(kp, v, cv, wv, own, bs, bc, wcv, pa, pb, a);
   }
   template <int G>
-  __device__ __forceinline__ void group(KP kp, int32_t v, int gl) { row<G, 1>(kp, v, gl); }
+  __device__ __forceinline__ void group(KP kp, const TeamRow& r, int gl) { row<G, 1>(kp, r, gl); }
   // longer rows of at most TW_ROW entries: an LDS hash of the wavefront's own
-  __device__ __forceinline__ void wave(KP kp, int32_t v, int lane) {
-    const int b = (int)kp->off[v], e = (int)kp->off[v + 1];
-    if (e - b > TW_ROW) return;  // team_enum_blk
-    if (e - b <= 2 * WAVE) return row<WAVE, 2>(kp, v, lane);
+  __device__ __forceinline__ void wave(KP kp, const TeamRow& rw, int lane) {
+    const int32_t v = rw.v;
+    const int b = rw.b, e = rw.b + rw.d;
+    if (rw.d > TW_ROW) return;  // team_enum_blk
+    if (rw.d <= 2 * WAVE) return row<WAVE, 2>(kp, rw, lane);
     const int wv = uniform32(team_tx() / WAVE);
     int32_t* tk = lds.wave.k[wv];
     uint32_t* tv = lds.wave.v[wv];
@@ -313,12 +361,11 @@ struct EnumOp {
 // longer rows, the workgroup each
 __device__ __forceinline__ void team_enum_blk(const Team& t, KP kp, uint32_t pa, uint32_t pb, TeamAcc& a) {
   TEAM_PHASE(kp);
-  const int tx = team_tx(), lane = tx & (WAVE - 1), wv = tx / WAVE, end = kp->boff[NBUCKET];
   __syncthreads();
-  for (int i = kp->boff[5] + t.rank; i < end; i += t.n) {  // uniform over the workgroup
-    const int32_t v = uniform32(kp->list[i]);
-    const int b = (int)kp->off[v], e = (int)kp->off[v + 1];
-    if (e - b <= TW_ROW) continue;
+  team_long(t, kp, TW_ROW, [&](const TeamRow& rw) __attribute__((always_inline)) {
+    const int tx = team_tx(), lane = tx & (WAVE - 1), wv = tx / WAVE;
+    const int32_t v = rw.v;
+    const int b = rw.b, e = rw.b + rw.d;
     const int32_t cv = uniform32(ald(kp->C + v));
     const int32_t bv = kp->cons ? kp->cons[v] : 0;
     const int64_t wvt = kp->vw[v], wcv = ald(kp->W + cv);
@@ -363,7 +410,7 @@ __device__ __forceinline__ void team_enum_blk(const Team& t, KP kp, uint32_t pa,
       team_finish(kp, v, cv, wvt, r.own, r.s, r.c, wcv, pa, pb, a);
     }
     __syncthreads();
-  }
+  });
 }
 
 __device__ __forceinline__ VState ald_state(const VState* vs, int32_t v) {
@@ -433,20 +480,22 @@ struct KeepOp {
   bool copy;
   TeamKeep k;
   template <int G>
-  __device__ __forceinline__ void group(KP kp, int32_t v, int gl) {
+  __device__ __forceinline__ void group(KP kp, const TeamRow& r, int gl) {
+    const int32_t v = r.v;
     const VState me = ald_state(kp->vs, v);
     bool keep = false;
     if (kp->symmetry) {
       keep = team_rule(me, kp->symmetry, pass);
     } else if (me.d != D_NONE) {
-      const int64_t acc = sum_steps<G>(team_ab_row<1>(kp, (int)kp->off[v], (int)kp->off[v + 1], gl, G, v, me, kp->vw[v]));
+      const int64_t acc = sum_steps<G>(team_ab_row<1>(kp, r.b, r.b + r.d, gl, G, v, me, kp->vw[v]));
       keep = (__int128)me.delta + acc >= 0;
     }
     if (gl == 0) team_apply(kp, v, me, keep, copy, k);
   }
-  __device__ __forceinline__ void wave(KP kp, int32_t v, int lane) {
-    const int b = (int)kp->off[v], e = (int)kp->off[v + 1];
-    if (e - b > TB_ROW) return;  // team_ab_blk
+  __device__ __forceinline__ void wave(KP kp, const TeamRow& r, int lane) {
+    const int32_t v = r.v;
+    const int b = r.b, e = r.b + r.d;
+    if (r.d > TB_ROW) return;  // team_ab_blk
     const VState me = ald_state(kp->vs, v);
     bool keep = false;
     if (kp->symmetry) {
@@ -462,11 +511,10 @@ struct KeepOp {
 // the workgroup per row above TB_ROW entries
 __device__ __forceinline__ void team_ab_blk(const Team& t, KP kp, int pass, bool copy, TeamKeep& kk) {
   TEAM_PHASE(kp);
-  const int tx = team_tx(), lane = tx & (WAVE - 1), end = kp->boff[NBUCKET];
-  for (int i = kp->boff[5] + t.rank; i < end; i += t.n) {  // uniform over the workgroup
-    const int32_t v = uniform32(kp->list[i]);
-    const int b = (int)kp->off[v], e = (int)kp->off[v + 1];
-    if (e - b <= TB_ROW) continue;
+  team_long(t, kp, TB_ROW, [&](const TeamRow& r) __attribute__((always_inline)) {
+    const int tx = team_tx(), lane = tx & (WAVE - 1);
+    const int32_t v = r.v;
+    const int b = r.b, e = r.b + r.d;
     const VState me = ald_state(kp->vs, v);
     int64_t acc = 0;
     if (!kp->symmetry && me.d != D_NONE) acc = team_ab_row<2>(kp, b, e, tx, TEAM_BLOCK, v, me, kp->vw[v]);
@@ -479,7 +527,7 @@ __device__ __forceinline__ void team_ab_blk(const Team& t, KP kp, int pass, bool
       const bool keep = kp->symmetry ? team_rule(me, kp->symmetry, pass) : me.d != D_NONE && (__int128)me.delta + acc >= 0;
       team_apply(kp, v, me, keep, copy, kk);
     }
-  }
+  });
 }
 
 // Movers to a new singleton: the i-th in ascending vertex order takes the i-th id without members.  Every member
@@ -519,18 +567,42 @@ __device__ __forceinline__ void team_empty(Team& t, KP kp, int nm, int64_t& sw2)
   sw2 += t.sum(d).a;
 }
 
-// internal weight of a clustering, this thread's share
-struct InternalOp {
-  const int32_t* C;
-  int64_t s;
-  template <int G>
-  __device__ __forceinline__ void group(KP kp, int32_t v, int gl) {
-    const int32_t cv = ald(C + v);
-    const int e = (int)kp->off[v + 1];
-    for (int j = (int)kp->off[v] + gl; j < e; j += G)
-      if (ald(C + kp->idx[j]) == cv) s += kp->w[j];
+// sum over the entries x, x + S, ... of a row: get(u) is loaded for U entries at a time, use(g, u, w) is the
+// entry's share
+template <int U, typename Get, typename Use>
+__device__ __forceinline__ int64_t team_row_sum(KP kp, const TeamRow& r, int x, int S, Get get, Use use) {
+  int64_t s = 0;
+  const int e = r.b + r.d;
+  for (int j0 = r.b + x; j0 < e; j0 += S * U) {
+    int32_t us[U], ws[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int j = j0 + k * S < e ? j0 + k * S : e - 1;
+      us[k] = kp->idx[j];
+      ws[k] = kp->w[j];
+    }
+    decltype(get(0)) g[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) g[k] = get(us[k]);
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+      if (j0 + k * S < e) s += use(g[k], us[k], ws[k]);
   }
-  __device__ __forceinline__ void wave(KP kp, int32_t v, int lane) { group<WAVE>(kp, v, lane); }
+  return s;
+}
+
+// internal weight of the clustering C, this thread's share
+struct InternalOp {
+  int64_t s = 0;
+  template <int U>
+  __device__ __forceinline__ void part(KP kp, const TeamRow& r, int x, int S) {
+    const int32_t cv = ald(kp->C + r.v);
+    s += team_row_sum<U>(kp, r, x, S, [&](int32_t u) __attribute__((always_inline)) { return ald(kp->C + u); },
+                         [&](int32_t c, int32_t, int32_t w) __attribute__((always_inline)) { return c == cv ? (int64_t)w : 0; });
+  }
+  template <int G>
+  __device__ __forceinline__ void group(KP kp, const TeamRow& r, int gl) { part<1>(kp, r, gl, G); }
+  __device__ __forceinline__ void wave(KP kp, const TeamRow& r, int lane) { part<4>(kp, r, lane, WAVE); }
 };
 
 // The starting state: cluster weights and sizes of C_out (or singletons), C = C_out.
@@ -631,7 +703,7 @@ __device__ __forceinline__ bool team_local_move(Team& t, const KP kp0) {
     N0 = Nbest = -kp->sc.p * (sq - kp->sum_w2);
   } else {
     if (!skipped && nM) {  // the state the last pass left
-      InternalOp op{kp->C, 0};
+      InternalOp op;
       team_tasks(t, kp, op);
       I = t.sum(op.s).a;
       const int64_t N = kp->sc.q * I - kp->sc.p * (sw2 - kp->sum_w2);
@@ -700,9 +772,9 @@ __device__ __forceinline__ void team_emit(KP kp, int32_t x, int j0, int e, int l
 
 struct EmitOp {
   template <int G>
-  __device__ __forceinline__ void group(KP kp, int32_t v, int gl) {
-    const int rb = (int)kp->off[v], d = (int)kp->off[v + 1] - rb;
-    const int32_t x = ald(kp->st.map + v);
+  __device__ __forceinline__ void group(KP kp, const TeamRow& r, int gl) {
+    const int rb = r.b, d = r.d;
+    const int32_t x = ald(kp->st.map + r.v);
     const int j = rb + (gl < d ? gl : 0);
     const int32_t y = gl < d ? ald(kp->st.map + kp->idx[j]) : x;
     const uint32_t w = gl < d ? (uint32_t)kp->w[j] : 0u;
@@ -713,23 +785,19 @@ struct EmitOp {
     at = __shfl(at, 0, G);
     if (y != x) ast(kp->st.raw + at + __popc(m & ((1u << gl) - 1)), (uint64_t)(uint32_t)y << 32 | w);
   }
-  __device__ __forceinline__ void wave(KP kp, int32_t v, int lane) {
-    const int b = (int)kp->off[v], e = (int)kp->off[v + 1];
-    if (e - b > TW_ROW) return;  // team_emit_blk
-    const int32_t x = uniform32(ald(kp->st.map + v));
-    for (int j0 = b; j0 < e; j0 += 2 * WAVE) team_emit<2>(kp, x, j0, e, lane);
+  __device__ __forceinline__ void wave(KP kp, const TeamRow& r, int lane) {
+    const int e = r.b + r.d;
+    if (r.d > TW_ROW) return;  // team_emit_blk
+    const int32_t x = uniform32(ald(kp->st.map + r.v));
+    for (int j0 = r.b; j0 < e; j0 += 2 * WAVE) team_emit<2>(kp, x, j0, e, lane);
   }
 };
 __device__ __forceinline__ void team_emit_blk(const Team& t, KP kp) {
-  TEAM_PHASE(kp);
-  const int tx = team_tx(), lane = tx & (WAVE - 1), wv = uniform32(tx / WAVE), end = kp->boff[NBUCKET];
-  for (int i = kp->boff[5] + t.rank; i < end; i += t.n) {  // uniform over the workgroup
-    const int32_t v = uniform32(kp->list[i]);
-    const int b = (int)kp->off[v], e = (int)kp->off[v + 1];
-    if (e - b <= TW_ROW) continue;
-    const int32_t x = uniform32(ald(kp->st.map + v));
-    for (int j0 = b + wv * 4 * WAVE; j0 < e; j0 += TEAM_WAVES * 4 * WAVE) team_emit<4>(kp, x, j0, e, lane);
-  }
+  team_long(t, kp, TW_ROW, [&](const TeamRow& r) __attribute__((always_inline)) {
+    const int tx = team_tx(), lane = tx & (WAVE - 1), wv = uniform32(tx / WAVE), e = r.b + r.d;
+    const int32_t x = uniform32(ald(kp->st.map + r.v));
+    for (int j0 = r.b + wv * 4 * WAVE; j0 < e; j0 += TEAM_WAVES * 4 * WAVE) team_emit<4>(kp, x, j0, e, lane);
+  });
 }
 
 // place of every lane's key among the keys of the group's leaders
@@ -974,35 +1042,12 @@ __device__ __forceinline__ uint64_t team_f(KP kp, int32_t v, bool flip) {
   return flip ? (((uint64_t)1 << 33) - 1) - f : f;
 }
 
-// sum over the entries x, x + S, ... of the row [b, e): get(u) is loaded for U entries at a time, use(g, u, w) is the
-// entry's share
-template <int U, typename Get, typename Use>
-__device__ __forceinline__ int64_t team_row_sum(KP kp, int b, int e, int x, int S, Get get, Use use) {
-  int64_t s = 0;
-  for (int j0 = b + x; j0 < e; j0 += S * U) {
-    int32_t us[U], ws[U];
-#pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const int j = j0 + k * S < e ? j0 + k * S : e - 1;
-      us[k] = kp->idx[j];
-      ws[k] = kp->w[j];
-    }
-    decltype(get(0)) g[U];
-#pragma unroll
-    for (int k = 0; k < U; ++k) g[k] = get(us[k]);
-#pragma unroll
-    for (int k = 0; k < U; ++k)
-      if (j0 + k * S < e) s += use(g[k], us[k], ws[k]);
-  }
-  return s;
-}
-
 // a(v, B[v] \ v) and membership of U
 struct OwnOp {
   int64_t nU = 0;
   template <int U>
-  __device__ __forceinline__ int64_t part(KP kp, int32_t v, int32_t bv, int x, int S) {
-    return team_row_sum<U>(kp, (int)kp->off[v], (int)kp->off[v + 1], x, S,
+  __device__ __forceinline__ int64_t part(KP kp, const TeamRow& r, int32_t bv, int x, int S) {
+    return team_row_sum<U>(kp, r, x, S,
                            [&](int32_t u) __attribute__((always_inline)) { return ald(kp->Cout + u); },
                            [&](int32_t c, int32_t, int32_t w) __attribute__((always_inline)) { return c == bv ? (int64_t)w : 0; });
   }
@@ -1014,15 +1059,15 @@ struct OwnOp {
     nU += in;
   }
   template <int G>
-  __device__ __forceinline__ void group(KP kp, int32_t v, int gl) {
-    const int32_t bv = ald(kp->Cout + v);
-    const int64_t s = sum_steps<G>(part<1>(kp, v, bv, gl, G));
-    if (gl == 0) finish(kp, v, bv, s);
+  __device__ __forceinline__ void group(KP kp, const TeamRow& r, int gl) {
+    const int32_t bv = ald(kp->Cout + r.v);
+    const int64_t s = sum_steps<G>(part<1>(kp, r, bv, gl, G));
+    if (gl == 0) finish(kp, r.v, bv, s);
   }
-  __device__ __forceinline__ void wave(KP kp, int32_t v, int lane) {
-    const int32_t bv = ald(kp->Cout + v);
-    const int64_t s = wave_sum64(part<4>(kp, v, bv, lane, WAVE));
-    if (lane == 0) finish(kp, v, bv, s);
+  __device__ __forceinline__ void wave(KP kp, const TeamRow& r, int lane) {
+    const int32_t bv = ald(kp->Cout + r.v);
+    const int64_t s = wave_sum64(part<4>(kp, r, bv, lane, WAVE));
+    if (lane == 0) finish(kp, r.v, bv, s);
   }
 };
 
@@ -1045,8 +1090,9 @@ struct ChooseOp {
     if (keep) ast(kp->has_child + h, (uint8_t)1);
   }
   template <int G>
-  __device__ __forceinline__ void group(KP kp, int32_t v, int gl) {
-    const int rb = (int)kp->off[v], d = (int)kp->off[v + 1] - rb;
+  __device__ __forceinline__ void group(KP kp, const TeamRow& r, int gl) {
+    const int32_t v = r.v;
+    const int rb = r.b, d = r.d;
     const int lane = team_tx() & (WAVE - 1);
     int32_t u = v;
     bool q = false;
@@ -1060,8 +1106,28 @@ struct ChooseOp {
     const bool mine = q && __popc(m & ((1u << gl) - 1)) == want;
     if (mine || (gl == 0 && want < 0)) finish(kp, v, mine ? u : v);
   }
-  __device__ __forceinline__ void wave(KP kp, int32_t v, int lane) {
-    const int b = (int)kp->off[v], e = (int)kp->off[v + 1];
+  // 256 entries at a time; the chosen one is looked for among the masks of the last of them, or in a second sweep
+  __device__ __forceinline__ void sweep(KP kp, int j0, int e, int lane, int32_t v, int32_t bv, int64_t wv, uint64_t (&m)[4], int& below) const {
+    int32_t us[4], ws[4];
+    Near o[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int j = j0 + k * WAVE + lane < e ? j0 + k * WAVE + lane : e - 1;
+      us[k] = kp->idx[j];
+      ws[k] = kp->w[j];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) o[k] = near(kp, us[k]);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const bool q = j0 + k * WAVE + lane < e && good(kp, o[k], bv, wv, ws[k]);
+      m[k] = __ballot(q);
+      below += __popcll(__ballot(q && us[k] < v));
+    }
+  }
+  __device__ __forceinline__ void wave(KP kp, const TeamRow& r, int lane) {
+    const int32_t v = r.v;
+    const int b = r.b, e = r.b + r.d;
     if (!ald(kp->inU + v)) {  // uniform
       if (lane == 0) finish(kp, v, v);
       return;
@@ -1069,37 +1135,27 @@ struct ChooseOp {
     const int32_t bv = ald(kp->Cout + v);
     const int64_t wv = kp->vw[v];
     int total = 0, below = 0;
-    for (int j0 = b; j0 < e; j0 += 2 * WAVE) {  // uniform
-      int32_t us[2], ws[2];
-      Near o[2];
+    uint64_t m[4];
+    for (int j0 = b; j0 < e; j0 += 4 * WAVE) {  // uniform
+      sweep(kp, j0, e, lane, v, bv, wv, m, below);
 #pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const int j = j0 + k * WAVE + lane < e ? j0 + k * WAVE + lane : e - 1;
-        us[k] = kp->idx[j];
-        ws[k] = kp->w[j];
-      }
-#pragma unroll
-      for (int k = 0; k < 2; ++k) o[k] = near(kp, us[k]);
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const bool q = j0 + k * WAVE + lane < e && good(kp, o[k], bv, wv, ws[k]);
-        total += __popcll(__ballot(q));
-        below += __popcll(__ballot(q && us[k] < v));
-      }
+      for (int k = 0; k < 4; ++k) total += __popcll(m[k]);
     }
-    const int want = uniform32(pick(kp, v, total, below));
+    int want = uniform32(pick(kp, v, total, below));
     if (want < 0) {
       if (lane == 0) finish(kp, v, v);
       return;
     }
-    int seen = 0;
-    for (int j0 = b; j0 < e && seen <= want; j0 += WAVE) {  // uniform
-      const int j = j0 + lane < e ? j0 + lane : e - 1;
-      const int32_t u = kp->idx[j];
-      const bool q = j0 + lane < e && good(kp, near(kp, u), bv, wv, kp->w[j]);
-      const uint64_t m = __ballot(q);
-      if (q && seen + __popcll(m & ((1ull << lane) - 1)) == want) finish(kp, v, u);
-      seen += __popcll(m);
+    for (int j0 = b;; j0 += 4 * WAVE) {  // uniform; want < total
+      if (r.d > 4 * WAVE) sweep(kp, j0, e, lane, v, bv, wv, m, below);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int c = __popcll(m[k]);
+        if (want >= 0 && want < c && m[k] >> lane & 1 && __popcll(m[k] & ((1ull << lane) - 1)) == want)
+          finish(kp, v, kp->idx[j0 + k * WAVE + lane]);
+        want -= c;
+      }
+      if (want < 0) break;
     }
   }
 };
@@ -1108,26 +1164,26 @@ struct ChooseOp {
 struct TreeOp {
   struct Near { int32_t r; int32_t flip; };
   template <int U>
-  __device__ __forceinline__ int64_t part(KP kp, int32_t v, int32_t rv, int x, int S) {
-    const uint64_t fv = team_f(kp, v, ald(kp->flip + v));
-    return team_row_sum<U>(kp, (int)kp->off[v], (int)kp->off[v + 1], x, S,
+  __device__ __forceinline__ int64_t part(KP kp, const TeamRow& r, int32_t rv, int x, int S) {
+    const uint64_t fv = team_f(kp, r.v, ald(kp->flip + r.v));
+    return team_row_sum<U>(kp, r, x, S,
                            [&](int32_t u) __attribute__((always_inline)) { return Near{ald(kp->root + u), ald(kp->flip + u)}; },
                            [&](const Near& o, int32_t u, int32_t w) __attribute__((always_inline)) {
                              return o.r == rv && team_f(kp, u, o.flip) < fv ? (int64_t)w : 0;
                            });
   }
   template <int G>
-  __device__ __forceinline__ void group(KP kp, int32_t v, int gl) {
-    const int32_t rv = ald(kp->root + v);
+  __device__ __forceinline__ void group(KP kp, const TeamRow& r, int gl) {
+    const int32_t rv = ald(kp->root + r.v);
     if (ald(kp->tsz + rv) < 2) return;  // uniform over the group
-    const int64_t s = sum_steps<G>(part<1>(kp, v, rv, gl, G));
-    if (gl == 0) ast(kp->aX + v, s);
+    const int64_t s = sum_steps<G>(part<1>(kp, r, rv, gl, G));
+    if (gl == 0) ast(kp->aX + r.v, s);
   }
-  __device__ __forceinline__ void wave(KP kp, int32_t v, int lane) {
-    const int32_t rv = ald(kp->root + v);
+  __device__ __forceinline__ void wave(KP kp, const TeamRow& r, int lane) {
+    const int32_t rv = ald(kp->root + r.v);
     if (ald(kp->tsz + rv) < 2) return;
-    const int64_t s = wave_sum64(part<4>(kp, v, rv, lane, WAVE));
-    if (lane == 0) ast(kp->aX + v, s);
+    const int64_t s = wave_sum64(part<4>(kp, r, rv, lane, WAVE));
+    if (lane == 0) ast(kp->aX + r.v, s);
   }
 };
 
@@ -1282,8 +1338,9 @@ __device__ __forceinline__ void team_tree_blk(KP kp, int32_t r, int b, int m) {
 // adjacent part of the gain: earlier movers are those of smaller id
 struct AdjOp {
   template <int U>
-  __device__ __forceinline__ int64_t part(KP kp, int32_t v, const VState& me, int x, int S) {
-    return team_row_sum<U>(kp, (int)kp->off[v], (int)kp->off[v + 1], x, S,
+  __device__ __forceinline__ int64_t part(KP kp, const TeamRow& r, const VState& me, int x, int S) {
+    const int32_t v = r.v;
+    return team_row_sum<U>(kp, r, x, S,
                            [&](int32_t u) __attribute__((always_inline)) { return ald((const uint64_t*)&kp->vs[u]); },
                            [&](uint64_t cd, int32_t u, int32_t w) __attribute__((always_inline)) {
                              const int32_t c = (int32_t)(uint32_t)cd, d = (int32_t)(cd >> 32);
@@ -1291,17 +1348,17 @@ struct AdjOp {
                            });
   }
   template <int G>
-  __device__ __forceinline__ void group(KP kp, int32_t v, int gl) {
-    const VState me = ald_state(kp->vs, v);
+  __device__ __forceinline__ void group(KP kp, const TeamRow& r, int gl) {
+    const VState me = ald_state(kp->vs, r.v);
     if (me.d == D_NONE) return;  // uniform over the group
-    const int64_t s = sum_steps<G>(part<1>(kp, v, me, gl, G));
-    if (gl == 0) ast(kp->adj + v, s);
+    const int64_t s = sum_steps<G>(part<1>(kp, r, me, gl, G));
+    if (gl == 0) ast(kp->adj + r.v, s);
   }
-  __device__ __forceinline__ void wave(KP kp, int32_t v, int lane) {
-    const VState me = ald_state(kp->vs, v);
+  __device__ __forceinline__ void wave(KP kp, const TeamRow& r, int lane) {
+    const VState me = ald_state(kp->vs, r.v);
     if (me.d == D_NONE) return;
-    const int64_t s = wave_sum64(part<2>(kp, v, me, lane, WAVE));
-    if (lane == 0) ast(kp->adj + v, s);
+    const int64_t s = wave_sum64(part<2>(kp, r, me, lane, WAVE));
+    if (lane == 0) ast(kp->adj + r.v, s);
   }
 };
 
@@ -1346,8 +1403,9 @@ __device__ __forceinline__ void team_alternate(Team& t, KP kp) {
   team_start(t, kp, false, false);
   TEAM_PHASE(kp);
   const int n = kp->n;
-  int64_t sw2 = team_sw2(t, kp);
+  int64_t N;
   {
+    const int64_t sw2 = team_sw2(t, kp);
     TeamAcc a;
     a.strict = 1;
     EnumOp op{1, 1, a};
@@ -1356,11 +1414,11 @@ __device__ __forceinline__ void team_alternate(Team& t, KP kp) {
     team_enum_blk(t, kp, 1, 1, a);
     team_each(t, kp, n, [](KP kp, int c) __attribute__((always_inline)) { ast(kp->tsz + c, 0); });
     const Sum3 x = t.sum(a.ncand, a.own, sw2);
-    sw2 = x.c;
+    N = kp->sc.q * x.b - kp->sc.p * (x.c - kp->sum_w2);
     if (t.rank == 0 && team_tx() == 0) {
       kp->slot->alt = 1;
       kp->slot->alt_k = x.a;
-      kp->slot->alt_N = kp->sc.q * x.b - kp->sc.p * (sw2 - kp->sum_w2);
+      kp->slot->alt_N = N;
     }
     if (!x.a) return;
   }
@@ -1466,11 +1524,15 @@ __device__ __forceinline__ void team_alternate(Team& t, KP kp) {
     }
   }
   t.sync();
-  bv = 0;
-  bi = INT64_MAX;
-  for (int r = 0; r < t.n; ++r) {
-    const int64_t ov = uniform64(ald(&kp->best[r].v)), oi = uniform64(ald(&kp->best[r].i));
-    if (team_longer(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+  {
+    const int lane = team_tx() & (WAVE - 1), r = lane < t.n ? lane : 0;
+    bv = ald(&kp->best[r].v);
+    bi = ald(&kp->best[r].i);
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+      const int64_t ov = __shfl_xor(bv, o, WAVE), oi = __shfl_xor(bi, o, WAVE);
+      if (team_longer(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+    }
   }
   const int kb = bv > 0 ? (int)bi + 1 : 0;
   // the movers of the prefix move
@@ -1480,18 +1542,17 @@ __device__ __forceinline__ void team_alternate(Team& t, KP kp) {
     const VState me = ald_state(kp->vs, v);
     team_apply(kp, v, me, me.d != D_NONE && ald(kp->pos + v) < kb, false, kk);
   });
-  kk.dsq += agg_flush(kp->W, kp->cnt);
-  const Sum2 y = t.sum(kk.ne, (int64_t)kk.dsq);
-  sw2 = (int64_t)((uint64_t)sw2 + (uint64_t)y.b);
-  if (y.a) team_empty(t, kp, (int)y.a, sw2);
-  TEAM_PHASE(kp);
-  InternalOp op{kp->C, 0};
-  team_tasks(t, kp, op);
+  agg_flush(kp->W, kp->cnt);
+  const int ne = (int)t.sum(kk.ne).a;
+  if (ne) {
+    int64_t sw2 = 0;
+    team_empty(t, kp, ne, sw2);
+  }
   team_each(t, kp, n, [](KP kp, int v) __attribute__((always_inline)) { ast(kp->Cout + v, ald(kp->C + v)); });
-  const int64_t I = t.sum(op.s).a;
+  t.sync();
   if (t.rank == 0 && team_tx() == 0) {
     kp->slot->alt_best_k = kb;
-    kp->slot->alt_N = kp->sc.q * I - kp->sc.p * (sw2 - kp->sum_w2);
+    kp->slot->alt_N = N + 2 * bv;  // a gain is half the exact change of the objective
   }
 }
 
@@ -1594,6 +1655,7 @@ __global__ __launch_bounds__(TEAM_BLOCK) void k_team_level(TeamArgs args) {
   for (int k = team_tx(); t.rank == 0 && k < (int)(sizeof(LMSlot) / 8); k += TEAM_BLOCK) ast((int64_t*)kp->slot + k, (int64_t)0);
   const int steps = kp->steps, n = kp->n;
   if (steps & TEAM_PLACE) team_place(t, kp);
+  team_row_words(t, kp);  // there after the local move's first boundary
   if (steps & TEAM_MOVE) {
     // C_out unchanged: the alternate local move
     if (!team_local_move(t, kp) && (steps & TEAM_ALTERNATE)) team_alternate(t, kp);
