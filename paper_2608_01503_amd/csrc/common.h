@@ -84,14 +84,17 @@ struct LMSlot {
   int64_t nM[MAX_PASSES + 1];   // kept moves of pass i
   int64_t I[MAX_PASSES + 1];    // ordered internal edge weight of state k
   int64_t SW2[MAX_PASSES + 1];  // sum over clusters of W_c^2 for state k
-  int32_t skip[MAX_PASSES + 2]; // pass i repeats pass i-1 exactly (no move, same temperature)
+  uint8_t skip[MAX_PASSES + 4]; // pass i repeats pass i-1 exactly (no move, same temperature)
   int32_t copy;                 // current best-so-far decision: copy C -> C_out
-  int32_t pad;
   int64_t n_empty;              // movers to a new singleton in the current pass
   int64_t Nbest;                // objective numerator of C_out
   int64_t N0;                   // objective numerator of the starting clustering
   int64_t nlab;                 // distinct labels of the clustering the driver ranked after the call
-  // a team launch that went on to the next level (team.h)
+};
+
+// What a team launch (team.h) leaves for the host's decisions.
+struct TeamOut {
+  int64_t Nbest, N0, nlab;                // as in the slot
   int64_t alt, alt_k, alt_best_k, alt_N;  // the alternate local move's movers, committed prefix and objective
   int64_t refined, refine_n, refine_U, refine_m, cycle;
   int64_t coarse, coarse_nnz, coarse_w2, coarse_boff[NBUCKET + 1];

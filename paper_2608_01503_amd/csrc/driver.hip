@@ -44,6 +44,11 @@ void hip_check(hipError_t e, const char* what) {
 
 constexpr size_t ALIGN = 256;
 constexpr int NSLOT = 4 * 1024 + 16;
+// The slots' part of a workspace, also holding the team launches' blocks.  Its size belongs to the figure that
+// lcc_workspace_bytes reports and no-allocation calls are admitted by.
+constexpr size_t SLOT_BYTES = (size_t)NSLOT * 1232;
+static_assert(NSLOT * sizeof(LMSlot) + 256 + TEAM_SLOTS * sizeof(TeamCtl) + sizeof(TeamOut) + 16 * TEAM_MAX <= SLOT_BYTES,
+              "the slots and the team's blocks share their part");
 
 inline size_t align_up(size_t x) { return (x + ALIGN - 1) & ~(ALIGN - 1); }
 
@@ -82,6 +87,7 @@ struct WS {
   Tagged tg;      // free-id marks and single-pass scan state (zeroed when the workspace is allocated)
   int64_t* stripes;  // per-workgroup counter partials (zeroed when the workspace is allocated)
   int64_t* team_best;  // 2 words per member of a team
+  TeamOut* team_out;
   TeamHost team;     // control blocks of the team launches (zeroed when the workspace is allocated)
   void* scan_temp;
 };
@@ -91,7 +97,14 @@ size_t carve(WS& w, char* base, int64_t n, int64_t nnz) {
   const int64_t M = std::max(n, nnz);
   const int64_t nch = nnz / HUB_CHUNK_EDGES + n + 1;
   w.ctrl = c.take<Ctrl>(1);
-  w.slots = c.take<LMSlot>(NSLOT);
+  char* slots = c.take<char>((int64_t)SLOT_BYTES);
+  w.slots = (LMSlot*)slots;
+  w.team = TeamHost{};
+  if (slots) {
+    w.team.ctl = (TeamCtl*)(slots + align_up(NSLOT * sizeof(LMSlot)));
+    w.team_out = (TeamOut*)(w.team.ctl + TEAM_SLOTS);
+    w.team_best = (int64_t*)(w.team_out + 1);
+  }
   w.in_off = c.take<int64_t>(n + 1);
   w.in_idx = c.take<int32_t>(nnz);
   w.in_w = c.take<int32_t>(nnz);
@@ -128,9 +141,6 @@ size_t carve(WS& w, char* base, int64_t n, int64_t nnz) {
   w.tg.status = c.take<unsigned long long>(w.tg.status_cap);
   w.tg.ticket = c.take<uint32_t>(1);
   w.stripes = c.take<int64_t>((int64_t)NSTRIPE * STRIPE_W);
-  w.team_best = c.take<int64_t>(2 * TEAM_MAX);
-  w.team = TeamHost{};
-  w.team.ctl = c.take<TeamCtl>(TEAM_SLOTS);
   w.scan_temp = c.take<char>((int64_t)scan_temp_bytes(M + 1));
   return c.off;
 }
@@ -593,6 +603,7 @@ struct Run {
     a.symmetry = P.symmetry;
     for (int i = 0; i <= MAX_PASSES; ++i) { a.phi_num[i] = P.phi_num[i]; a.phi_den[i] = P.phi_den[i]; }
     a.slot = w.slots + s;
+    a.out = w.team_out;
     a.used = w.used; a.rank = w.rank;
     if (steps & TEAM_PROJECT) a.up_C = lv[l + 1].C;
     a.map = L.map;
@@ -617,7 +628,7 @@ struct Run {
   }
 
   // Level l + 1 of nc vertices, which a team launch on level l has left in the stage.
-  void adopt(int l, const LMSlot& S, int64_t nc) {
+  void adopt(int l, const TeamOut& S, int64_t nc) {
     Level N;
     lv[l].map = take<int32_t>(ctx, lv[l].g.n);
     if (lv[l].B) N.B = take<int32_t>(ctx, nc);
@@ -658,12 +669,23 @@ struct Run {
     return s;
   }
 
-  // statistics of slot s, a local move on a level of n vertices (its label count must be possible)
-  LMSlot read_slot(int s, int64_t n) {
-    hip_check(hipMemcpyAsync(ctx->h_slots + s, w.slots + s, sizeof(LMSlot), hipMemcpyDeviceToHost, st), "slot");
-    sync("slot");
-    if (ctx->h_slots[s].nlab < 1 || ctx->h_slots[s].nlab > n) fail(LCC_ERR_DEVICE, "internal: a local move left no clustering");
-    return ctx->h_slots[s];
+  // What the local move on level l (statistics in slot s) has left to decide by; its label count must be possible.
+  TeamOut read_level(int l, int s) {
+    const int64_t n = lv[l].g.n;
+    TeamOut r{};
+    if (small(lv[l])) {
+      TeamOut* h = (TeamOut*)ctx->h_slots;  // the mirror's slots are read at the end of the call
+      hip_check(hipMemcpyAsync(h, w.team_out, sizeof(TeamOut), hipMemcpyDeviceToHost, st), "level");
+      sync("level");
+      r = *h;
+    } else {
+      LMSlot* h = ctx->h_slots + s;
+      hip_check(hipMemcpyAsync(h, w.slots + s, sizeof(LMSlot), hipMemcpyDeviceToHost, st), "slot");
+      sync("slot");
+      r.Nbest = h->Nbest; r.N0 = h->N0; r.nlab = h->nlab;
+    }
+    if (r.nlab < 1 || r.nlab > n) fail(LCC_ERR_DEVICE, "internal: a local move left no clustering");
+    return r;
   }
 
   // w.rank = the label rank of `labels`; their count is stored on the device at *dst (a field of a slot or of
@@ -801,7 +823,7 @@ struct Run {
       const bool cap = l + 1 >= o.max_levels;
       int s = local_move_level(l, !(l == 0 && init), 0, nullptr, cap ? 0 : TEAM_CONTRACT);
       Level& L = lv[l];
-      LMSlot S = read_slot(s, L.g.n);
+      const TeamOut S = read_level(l, s);
       const int64_t nc = S.nlab;
       rec(2, l, 0, 0, L.g.n, L.g.nnz, nc, S.Nbest);
       if (nc == L.g.n) break;
@@ -905,7 +927,7 @@ struct Run {
       const bool cap = l + 1 >= o.max_levels;
       int s = local_move_level(l, singleton, 0, nullptr, TEAM_ALTERNATE | (cap ? 0 : TEAM_REFINE | TEAM_CONTRACT));
       singleton = false;
-      LMSlot S = read_slot(s, n);
+      const TeamOut S = read_level(l, s);
       int64_t nc = S.nlab;  // the count of C_l, unless the alternate move below changes it
       int64_t N = S.Nbest;
       if (S.alt) {

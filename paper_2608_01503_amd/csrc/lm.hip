@@ -1147,7 +1147,7 @@ __global__ void k_sw2(const int64_t* W, int64_t n, int64_t* out, const LMSlot* s
 // one total over all rows (counter CT_INT of the stripes S), or per_v[v] per row when per_v is not null
 template <int G>
 __global__ __launch_bounds__(BLOCK) void k_internal_grp(const int32_t* list, int64_t cnt, DevGraph g,
-                                                        const int32_t* C, int64_t* S, const int32_t* skip,
+                                                        const int32_t* C, int64_t* S, const uint8_t* skip,
                                                         int64_t* per_v) {
   if (skip && *skip) return;
   const int gl = threadIdx.x % G;
@@ -1170,7 +1170,7 @@ __global__ __launch_bounds__(BLOCK) void k_internal_grp(const int32_t* list, int
 
 template <int BS>
 __global__ __launch_bounds__(BS) void k_internal_blk(const int32_t* list, int64_t cnt, DevGraph g, const int32_t* C,
-                                                     int64_t* S, const int32_t* skip, int64_t* per_v) {
+                                                     int64_t* S, const uint8_t* skip, int64_t* per_v) {
   if (skip && *skip) return;
   int64_t s = 0;
   for (int64_t vi = blockIdx.x; vi < cnt; vi += gridDim.x) {
@@ -1190,7 +1190,7 @@ __global__ __launch_bounds__(BS) void k_internal_blk(const int32_t* list, int64_
 
 __global__ __launch_bounds__(HUB_BLOCK) void k_internal_hub(const int32_t* hubs, const int32_t* chunk_off,
                                                             int64_t n7, DevGraph g, const int32_t* C, int64_t* S,
-                                                            const int32_t* skip, int64_t* per_v) {
+                                                            const uint8_t* skip, int64_t* per_v) {
   if (skip && *skip) return;
   const int k = find_chunk_owner(chunk_off, n7, blockIdx.x);
   const int32_t v = hubs[k];
@@ -1203,7 +1203,7 @@ __global__ __launch_bounds__(HUB_BLOCK) void k_internal_hub(const int32_t* hubs,
 }
 
 // per_v[hubs[k]] = 0 before the hub chunks add into it
-__global__ void k_zero_listed(const int32_t* list, int64_t cnt, int64_t* per_v, const int32_t* skip) {
+__global__ void k_zero_listed(const int32_t* list, int64_t cnt, int64_t* per_v, const uint8_t* skip) {
   if (skip && *skip) return;
   for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < cnt; k += (int64_t)gridDim.x * blockDim.x)
     per_v[list[k]] = 0;
@@ -1778,7 +1778,7 @@ void launch_cluster_weights(const int32_t* C, const int64_t* vw, int64_t n, int6
 }
 
 static void launch_internal(const DevGraph& g, const Buckets& b, const int32_t* C, int64_t* out,
-                            const int32_t* skip, hipStream_t st, int64_t* per_v = nullptr,
+                            const uint8_t* skip, hipStream_t st, int64_t* per_v = nullptr,
                             FoldDst* pending = nullptr) {
   const int32_t* L = b.list;
   int64_t* S = b.stripes;

@@ -78,6 +78,7 @@ struct TeamArgs {
   int32_t singleton, pass_limit, symmetry;
   uint32_t phi_num[MAX_PASSES + 1], phi_den[MAX_PASSES + 1];
   LMSlot* slot;
+  TeamOut* out;
   uint8_t* used;
   int32_t* rank;                // of the labels in Cout
   // uncoarsening: the next level's clustering, Cout[v] = up_C[map[v]]

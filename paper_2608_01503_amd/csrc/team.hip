@@ -715,7 +715,7 @@ __device__ __forceinline__ bool team_local_move(Team& t, const KP kp0) {
     for (int v = t.rank * TEAM_BLOCK + team_tx(); v < kp->n; v += t.threads()) ast(kp->Cout + v, ald(kp->C + v));
     t.sync();
   }
-  if (log) { kp->slot->Nbest = Nbest; kp->slot->N0 = N0; }
+  if (log) { kp->slot->Nbest = kp->out->Nbest = Nbest; kp->slot->N0 = kp->out->N0 = N0; }
   return Nbest != N0;
 }
 
@@ -990,7 +990,7 @@ __device__ __forceinline__ void team_contract(Team& t, KP kp, int nc) {
     for (int k = 0; k < NBUCKET - 1; ++k) cls += size > kp->bounds.max[k];
   });
   if (t.rank == 0 && team_tx() == 0) {
-    LMSlot* s = kp->slot;
+    TeamOut* s = kp->out;
     s->coarse_nnz = z.a;
     s->coarse_w2 = z.b;
     for (int k = 0; k <= NBUCKET; ++k) s->coarse_boff[k] = team_sh.first[k];
@@ -1416,9 +1416,9 @@ __device__ __forceinline__ void team_alternate(Team& t, KP kp) {
     const Sum3 x = t.sum(a.ncand, a.own, sw2);
     N = kp->sc.q * x.b - kp->sc.p * (x.c - kp->sum_w2);
     if (t.rank == 0 && team_tx() == 0) {
-      kp->slot->alt = 1;
-      kp->slot->alt_k = x.a;
-      kp->slot->alt_N = N;
+      kp->out->alt = 1;
+      kp->out->alt_k = x.a;
+      kp->out->alt_N = N;
     }
     if (!x.a) return;
   }
@@ -1551,8 +1551,8 @@ __device__ __forceinline__ void team_alternate(Team& t, KP kp) {
   team_each(t, kp, n, [](KP kp, int v) __attribute__((always_inline)) { ast(kp->Cout + v, ald(kp->C + v)); });
   t.sync();
   if (t.rank == 0 && team_tx() == 0) {
-    kp->slot->alt_best_k = kb;
-    kp->slot->alt_N = N + 2 * bv;  // a gain is half the exact change of the objective
+    kp->out->alt_best_k = kb;
+    kp->out->alt_N = N + 2 * bv;  // a gain is half the exact change of the objective
   }
 }
 
@@ -1576,7 +1576,7 @@ __device__ __forceinline__ void team_refine(Team& t, KP kp) {
     OwnOp op;
     team_tasks(t, kp, op);
     const int64_t u = t.sum(op.nU).a;
-    if (t.rank == 0 && team_tx() == 0) kp->slot->refine_U = u;
+    if (t.rank == 0 && team_tx() == 0) kp->out->refine_U = u;
   }
   {
     ChooseOp op;
@@ -1603,7 +1603,7 @@ __device__ __forceinline__ void team_refine(Team& t, KP kp) {
     const int n = kp->n;
     int32_t x = v, p = ald(kp->par2 + x);
     for (int steps = 0; p != x && steps <= n; ++steps) { x = p; p = ald(kp->par2 + x); }
-    if (p != x) kp->slot->cycle = 1;
+    if (p != x) kp->out->cycle = 1;
     ast(kp->root + v, x);
     ast(kp->rel + v, atomicAdd(kp->tsz + x, 1));
   });
@@ -1612,7 +1612,7 @@ __device__ __forceinline__ void team_refine(Team& t, KP kp) {
     const int s = ald(kp->tsz + v);  // 0 for vertices that are no roots
     if (s >= 2) { size = s; cls = s <= 16 ? 0 : s <= WAVE ? 1 : 2; }
   }).a;
-  if (t.rank == 0 && team_tx() == 0) kp->slot->refine_m = m;
+  if (t.rank == 0 && team_tx() == 0) kp->out->refine_m = m;
   t.sync();
   team_each(t, kp, n, [](KP kp, int v) __attribute__((always_inline)) {
     const int32_t r = ald(kp->root + v);
@@ -1653,6 +1653,7 @@ __global__ __launch_bounds__(TEAM_BLOCK) void k_team_level(TeamArgs args) {
   Team t;
   if (!t.join(kp->ctl, kp->next)) return;
   for (int k = team_tx(); t.rank == 0 && k < (int)(sizeof(LMSlot) / 8); k += TEAM_BLOCK) ast((int64_t*)kp->slot + k, (int64_t)0);
+  for (int k = team_tx(); t.rank == 0 && k < (int)(sizeof(TeamOut) / 8); k += TEAM_BLOCK) ast((int64_t*)kp->out + k, (int64_t)0);
   const int steps = kp->steps, n = kp->n;
   if (steps & TEAM_PLACE) team_place(t, kp);
   team_row_words(t, kp);  // there after the local move's first boundary
@@ -1661,12 +1662,12 @@ __global__ __launch_bounds__(TEAM_BLOCK) void k_team_level(TeamArgs args) {
     if (!team_local_move(t, kp) && (steps & TEAM_ALTERNATE)) team_alternate(t, kp);
   }
   int nc = team_rank(t, kp, kp->Cout, kp->rank);
-  if (t.rank == 0 && team_tx() == 0) kp->slot->nlab = nc;
+  if (t.rank == 0 && team_tx() == 0) kp->slot->nlab = kp->out->nlab = nc;
   bool on = nc < n && (steps & TEAM_CONTRACT);
   if (on && (steps & TEAM_REFINE)) {
     team_refine(t, kp);
     nc = team_rank(t, kp, kp->R, kp->rankR);
-    if (t.rank == 0 && team_tx() == 0) { kp->slot->refine_n = nc; kp->slot->refined = 1; }
+    if (t.rank == 0 && team_tx() == 0) { kp->out->refine_n = nc; kp->out->refined = 1; }
     on = nc < n;
   }
   if (on) {
