@@ -34,8 +34,8 @@ constexpr int32_t D_EMPTY = -2;  // destination = a new singleton cluster
 
 // Degree buckets (upper bounds, inclusive).  Buckets 0-3 are handled by sub-wave groups of 4/8/16/32 lanes
 // (one neighbour per lane), 4-5 by one wavefront per vertex, 6-7 by one workgroup per vertex.  The local-move
-// kernels sum neighbour clusters in registers (0-1), by leader lanes (2-4), in an LDS hash (5-6) or a global-memory
-// hash inside the edge arena (7).  BUCKET_CAP holds the largest row each of buckets 0-6 can serve (the lane
+// kernels sum neighbour clusters in registers (0-1), by leader lanes (2-4), in an LDS hash (5-6) or in LDS hashes by
+// chunk and by range of clusters (7).  BUCKET_CAP holds the largest row each of buckets 0-6 can serve (the lane
 // count of its group, half the slots of its LDS hash); a tuning may set lower bounds, never higher ones, and
 // every setting gives the same results.
 constexpr int64_t BUCKET_CAP[NBUCKET - 1] = {4, 8, 16, 32, 128, 1024, 8192};
@@ -445,7 +445,7 @@ struct LMBuffers {
   int32_t* scan_a; // n+1
   int32_t* scan_b; // n+1
   int32_t* freelist;
-  uint32_t* arena; // 2 * nnz (key, value) slots for the global-memory hash
+  uint32_t* arena; // 2 * nnz slots of 8 bytes: the hub rows' records by cluster
   void* scan_temp;
   int64_t* enum_bytes;  // per-bucket algorithmic bytes of the enumeration launches (diagnostics), or null
   Tagged* tg;      // free-id marks and single-pass scan state

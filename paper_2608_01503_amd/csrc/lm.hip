@@ -609,111 +609,149 @@ __global__ __launch_bounds__(BS) void k_enum_blk(const int32_t* list, int64_t cn
   acc_flush<BS>(va, S, slot ? CT_NCAND : -1, ct_own, ct_pairs);
 }
 
-// Hubs: global-memory hash of 2 d 64-bit slots (cluster << 32 | weight sum) at slot offset 2 off[v] of the
-// edge arena.  A hub's weight sums stay below 2^32 (the total edge weight does), so adding a weight to a slot
-// never carries into its key.  Chunk k of a hub owns the 2 * HUB_CHUNK slots that start at
-// 2 (off[v] + k HUB_CHUNK) for clearing and scanning; insertions probe the whole table.
-constexpr unsigned long long HUB_EMPTY = 0xFFFFFFFF00000000ull;
+// Hubs, in two steps.  Every chunk of a hub sums its entries by cluster in LDS (a hub's neighbours often share few
+// clusters) and writes the sums, one 8-byte record (cluster << 32 | weight) per cluster, grouped by P = min(chunks,
+// HUB_PARTS) ranges of the cluster's hash; then one workgroup per range sums the records that all chunks have for it,
+// again in LDS, and finds the best cluster of the range.  A range holds about as many clusters as a chunk.
+// Chunk k's records are at 2 off[v] + k HUB_CHUNK of the edge arena (64-bit slots), its ranges' ends as 16-bit numbers
+// from slot 2 off[v] + d on: P + 1 per chunk, less than 8 d bytes for any d.
+// Bound by the latency of the gathers C[u] in the first step.  Sums in a global-memory hash of 2 d slots, which these
+// steps replace, took a compare-and-swap or an add in memory per cluster of a chunk, and clearing the table as it was
+// scanned: 88 us a pass on an R-MAT graph of 2^18 vertices (8 M entries), now 39 us; on one of 2^22 vertices 385 us,
+// now about 95 us.
+constexpr int HUB_PARTS = HUB_BLOCK;
+constexpr int HUB_SLOTS = 1 << HUB_LDS_BITS;
+static_assert(HUB_SLOTS == 2 * HUB_CHUNK, "the LDS table holds 2 slots per chunk edge");
 
-__device__ __forceinline__ uint32_t hub_slot(int32_t c, int64_t cap) {
-  return (uint32_t)(((uint64_t)fmix32((uint32_t)c) * (uint64_t)cap) >> 32);
-}
+struct HubRow {
+  int32_t v;
+  int64_t base, d;
+  int nch, ch, parts;  // chunks of the hub, this workgroup's, ranges
+  __device__ __forceinline__ HubRow(const int32_t* hubs, const int32_t* chunk_off, int64_t n7, const int64_t* off) {
+    const int k = find_chunk_owner(chunk_off, n7, blockIdx.x);
+    v = hubs[k];
+    base = off[v];
+    d = off[v + 1] - base;
+    nch = chunk_off[k + 1] - chunk_off[k];
+    ch = (int)blockIdx.x - chunk_off[k];
+    parts = nch < HUB_PARTS ? nch : HUB_PARTS;
+  }
+  __device__ __forceinline__ uint64_t* records(uint32_t* arena) const { return (uint64_t*)arena + 2 * base; }
+  __device__ __forceinline__ uint16_t* ends(uint32_t* arena) const { return (uint16_t*)(records(arena) + d); }
+};
+__device__ __forceinline__ uint64_t hub_hash(int32_t c, int parts) { return (uint64_t)fmix32((uint32_t)c) * (uint64_t)parts; }
 
-__global__ __launch_bounds__(HUB_BLOCK) void k_hub_clear(const int32_t* hubs, const int32_t* chunk_off,
-                                                         int64_t n7, const int64_t* off, uint32_t* arena,
-                                                         const LMSlot* slot, int pass) {
-  if (slot && pass >= 0 && slot->skip[pass]) return;
-  const int k = find_chunk_owner(chunk_off, n7, blockIdx.x);
-  const int32_t v = hubs[k];
-  const int64_t s0 = 2 * (off[v] + (int64_t)(blockIdx.x - chunk_off[k]) * HUB_CHUNK);
-  const int64_t s1 = min(2 * off[v + 1], s0 + 2 * HUB_CHUNK);
-  unsigned long long* tab = (unsigned long long*)arena;
-  for (int64_t s = s0 + threadIdx.x; s < s1; s += HUB_BLOCK) tab[s] = HUB_EMPTY;
-}
-
-// Each chunk first aggregates its edges by cluster in LDS (a hub's neighbours often share few clusters), then
-// inserts one entry per distinct cluster into the hub's global table.
-__global__ __launch_bounds__(HUB_BLOCK) void k_hub_insert(const int32_t* hubs, const int32_t* chunk_off,
-                                                          int64_t n7, DevGraph g, const int32_t* C,
-                                                          uint32_t* arena, const LMSlot* slot, int pass,
-                                                          const int32_t* cons) {
+__global__ __launch_bounds__(HUB_BLOCK) void k_hub_part(const int32_t* hubs, const int32_t* chunk_off, int64_t n7,
+                                                        DevGraph g, const int32_t* C, uint32_t* arena, int64_t* pown,
+                                                        const LMSlot* slot, int pass, const int32_t* cons) {
   if (slot && slot->skip[pass]) return;
-  constexpr int S = 2 * HUB_CHUNK;
-  static_assert(S == (1 << HUB_LDS_BITS), "the LDS table holds 2 slots per chunk edge");
-  __shared__ int32_t lk[S];
-  __shared__ uint32_t lv[S];
-  const int k = find_chunk_owner(chunk_off, n7, blockIdx.x);
-  const int32_t v = hubs[k];
-  const int64_t base = g.off[v];
-  const int64_t cap = 2 * (g.off[v + 1] - base);
-  const int64_t j0 = base + (int64_t)(blockIdx.x - chunk_off[k]) * HUB_CHUNK;
-  const int64_t j1 = min(g.off[v + 1], j0 + HUB_CHUNK);
-  for (int s = threadIdx.x; s < S; s += HUB_BLOCK) { lk[s] = -1; lv[s] = 0; }
+  __shared__ int32_t lk[HUB_SLOTS];
+  __shared__ uint32_t lv[HUB_SLOTS];
+  __shared__ int32_t at[HUB_PARTS], wsum[HUB_BLOCK / WAVE];
+  const HubRow r(hubs, chunk_off, n7, g.off);
+  const int64_t j0 = r.base + (int64_t)r.ch * HUB_CHUNK, j1 = min(r.base + r.d, j0 + HUB_CHUNK);
+  const int t = threadIdx.x, lane = t & (WAVE - 1);
+  for (int s = t; s < HUB_SLOTS; s += HUB_BLOCK) { lk[s] = -1; lv[s] = 0; }
+  at[t] = 0;
   __syncthreads();
-  // own-cluster edges also go through the table here (the scan reads the hub's own weight from it)
-  const int64_t own = insert_row(g, C, j0, j1, threadIdx.x, HUB_BLOCK, -3, lk, lv, HUB_LDS_BITS, cons, cons ? cons[v] : 0);
-  (void)own;
+  const int64_t own = insert_row(g, C, j0, j1, t, HUB_BLOCK, C[r.v], lk, lv, HUB_LDS_BITS, cons, cons ? cons[r.v] : 0);
   __syncthreads();
-  // one atomic per entry: an add when the slot already holds the key, else a compare-and-swap of the whole
-  // slot from empty (a slot read as empty may be stale; the swap then reports its real content)
-  unsigned long long* tab = (unsigned long long*)arena + 2 * base;
-  for (int s = threadIdx.x; s < S; s += HUB_BLOCK) {
-    int32_t c = lk[s];
-    if (c < 0) continue;
-    const unsigned long long wt = lv[s];
-    const unsigned long long mine = ((unsigned long long)(uint32_t)c << 32) | wt;
-    int64_t h = hub_slot(c, cap);
-    for (int64_t probe = 0; probe < cap; ++probe) {
-      unsigned long long cur = tab[h];
-      if (cur == HUB_EMPTY) {
-        cur = atomicCAS(&tab[h], HUB_EMPTY, mine);
-        if (cur == HUB_EMPTY) break;
+  for (int s = t; s < HUB_SLOTS; s += HUB_BLOCK)
+    if (lk[s] >= 0) atomicAdd(&at[hub_hash(lk[s], r.parts) >> 32], 1);
+  const int64_t own_sum = sum_reduce<HUB_BLOCK>(own);  // with barriers
+  if (t == 0) pown[blockIdx.x] = own_sum;
+  int inc = at[t];
+#pragma unroll
+  for (int o = 1; o < WAVE; o <<= 1) {
+    const int y = __shfl_up(inc, o, WAVE);
+    if (lane >= o) inc += y;
+  }
+  if (lane == WAVE - 1) wsum[t / WAVE] = inc;
+  __syncthreads();
+  for (int w = 0; w < t / WAVE; ++w) inc += wsum[w];
+  const int first = inc - at[t];
+  at[t] = first;
+  uint16_t* ends = r.ends(arena) + (int64_t)r.ch * (r.parts + 1);
+  if (t < r.parts) ends[t] = (uint16_t)first;
+  if (t == r.parts - 1) ends[r.parts] = (uint16_t)inc;
+  __syncthreads();
+  uint64_t* rec = r.records(arena) + (int64_t)r.ch * HUB_CHUNK;
+  for (int s = t; s < HUB_SLOTS; s += HUB_BLOCK)
+    if (lk[s] >= 0) rec[atomicAdd(&at[hub_hash(lk[s], r.parts) >> 32], 1)] = (uint64_t)(uint32_t)lk[s] << 32 | lv[s];
+}
+
+// One range of a hub's clusters: partial best.  Chunks are read by groups of 8 to 64 lanes (a chunk's share of a range
+// is HUB_CHUNK / chunks records on average).  Should the range hold more clusters than the table, it is done again in
+// twice as many sub-ranges of the hash, which is a bijection of the cluster id: enough sub-ranges fit always.
+__global__ __launch_bounds__(HUB_BLOCK) void k_hub_best(const int32_t* hubs, const int32_t* chunk_off, int64_t n7,
+                                                        DevGraph g, const int32_t* C, const int64_t* W, ScoreSrc ss,
+                                                        uint32_t* arena, int64_t* ps, int32_t* pc, const LMSlot* slot,
+                                                        int pass, int64_t* S, int ct_pairs) {
+  if (slot && slot->skip[pass]) return;
+  __shared__ int32_t lk[HUB_SLOTS];
+  __shared__ uint32_t lv[HUB_SLOTS];
+  __shared__ int full;
+  const HubRow r(hubs, chunk_off, n7, g.off);
+  const int t = threadIdx.x;
+  if (r.ch >= r.parts) {
+    if (t == 0) { ps[blockIdx.x] = INT64_MIN; pc[blockIdx.x] = INT32_MAX; }
+    return;
+  }
+  const Score sc = ss.at(r.v);
+  const int64_t wvt = g.vw[r.v];
+  const uint64_t* rec = r.records(arena);
+  const uint16_t* ends = r.ends(arena);
+  const int ls = r.nch <= 4 ? 6 : r.nch <= 8 ? 5 : r.nch <= 16 ? 4 : 3;
+  const int gl = t & ((1 << ls) - 1);
+  Best best = best_init();
+  for (uint64_t sub = 1, q = 0; q < sub;) {  // uniform over the workgroup
+    for (int s = t; s < HUB_SLOTS; s += HUB_BLOCK) { lk[s] = -1; lv[s] = 0; }
+    if (t == 0) full = 0;
+    __syncthreads();
+    for (int ch = t >> ls; ch < r.nch; ch += HUB_BLOCK >> ls) {
+      const int64_t e = (int64_t)ch * (r.parts + 1) + r.ch;
+      const uint64_t* p = rec + (int64_t)ch * HUB_CHUNK;
+      const int j1 = ends[e + 1];
+      for (int j = ends[e] + gl; j < j1; j += 1 << ls) {
+        const uint64_t x = p[j];
+        const int32_t c = (int32_t)(x >> 32);
+        if (sub > 1 && ((hub_hash(c, r.parts) & 0xFFFFFFFFu) * sub) >> 32 != q) continue;
+        uint32_t h = hslot(c, HUB_LDS_BITS);
+        int probe = 0;
+        for (; probe < HUB_SLOTS; ++probe) {
+          const int32_t prev = atomicCAS(&lk[h], -1, c);
+          if (prev == -1 || prev == c) { atomicAdd(&lv[h], (uint32_t)x); break; }
+          h = (h + 1) & (HUB_SLOTS - 1);
+        }
+        if (probe == HUB_SLOTS) full = 1;
       }
-      if ((uint32_t)(cur >> 32) == (uint32_t)c) { atomicAdd(&tab[h], wt); break; }
-      if (++h == cap) h = 0;
     }
+    __syncthreads();
+    if (full) {
+      sub *= 2;
+      q = 0;
+      best = best_init();
+      __syncthreads();
+      continue;
+    }
+    for (int s = t; s < HUB_SLOTS; s += HUB_BLOCK) {
+      const int32_t c = lk[s];
+      if (c < 0) continue;
+      ++best.np;
+      const int64_t x = sc.q * (int64_t)lv[s] - sc.p * wvt * W[c];
+      if (better(x, c, best.s, best.c)) { best.s = x; best.c = c; }
+    }
+    ++q;
+    __syncthreads();
+  }
+  best_reduce<HUB_BLOCK>(best);
+  if (t == 0) {
+    ps[blockIdx.x] = best.s; pc[blockIdx.x] = best.c;
+    if (ct_pairs >= 0 && best.np) atomicAdd(stripe(S, ct_pairs), (unsigned long long)(8 * best.np));
   }
 }
 
-// Scan this chunk's share of the table: partial best and own weight; clears the slots for the next pass.
-__global__ __launch_bounds__(HUB_BLOCK) void k_hub_scan(const int32_t* hubs, const int32_t* chunk_off,
-                                                        int64_t n7, DevGraph g, const int32_t* C,
-                                                        const int64_t* W, ScoreSrc ss, uint32_t* arena,
-                                                        int64_t* ps, int32_t* pc, int64_t* pown,
-                                                        const LMSlot* slot, int pass, int64_t* S,
-                                                        int ct_pairs) {
-  if (slot && slot->skip[pass]) return;
-  const int k = find_chunk_owner(chunk_off, n7, blockIdx.x);
-  const int32_t v = hubs[k];
-  const Score sc = ss.at(v);
-  const int32_t cv = C[v];
-  const int64_t wvt = g.vw[v];
-  const int64_t s0 = 2 * (g.off[v] + (int64_t)(blockIdx.x - chunk_off[k]) * HUB_CHUNK);
-  const int64_t s1 = min(2 * g.off[v + 1], s0 + 2 * HUB_CHUNK);
-  int64_t own = 0, bs = INT64_MIN, np_ = 0;
-  int32_t bcl = INT32_MAX;
-  unsigned long long* tab = (unsigned long long*)arena;
-  for (int64_t s = s0 + threadIdx.x; s < s1; s += HUB_BLOCK) {
-    const unsigned long long e = tab[s];
-    if (e == HUB_EMPTY) continue;
-    tab[s] = HUB_EMPTY;
-    const int32_t c = (int32_t)(uint32_t)(e >> 32);
-    const int64_t a = (int64_t)(uint32_t)e;
-    if (c == cv) { own = a; continue; }
-    ++np_;
-    int64_t sc_ = sc.q * a - sc.p * wvt * W[c];
-    if (better(sc_, c, bs, bcl)) { bs = sc_; bcl = c; }
-  }
-  argmax_reduce<HUB_BLOCK>(bs, bcl);
-  own = sum_reduce<HUB_BLOCK>(own);
-  np_ = sum_reduce<HUB_BLOCK>(np_);
-  if (threadIdx.x == 0) {
-    ps[blockIdx.x] = bs; pc[blockIdx.x] = bcl; pown[blockIdx.x] = own;
-    if (ct_pairs >= 0 && np_) atomicAdd(stripe(S, ct_pairs), (unsigned long long)(8 * np_));
-  }
-}
-
-// Combine the chunks of each hub (pown may be null: singleton pass).  off (the level's offsets) and ct_bytes
+// Combine the chunks of each hub, a wavefront per hub (pown may be null: singleton pass).  off (the level's offsets) and ct_bytes
 // (a counter id, or -1) count the hub rows' algorithmic bytes.
 __global__ void k_hub_final(const int32_t* hubs, const int32_t* chunk_off, int64_t n7, const int64_t* vw,
                             const int32_t* C, const int64_t* W, ScoreSrc ss, uint32_t pa, uint32_t pb, int strict,
@@ -722,15 +760,18 @@ __global__ void k_hub_final(const int32_t* hubs, const int32_t* chunk_off, int64
                             int ct_bytes = -1) {
   VtxAcc va;
   if (slot && slot->skip[pass]) return;
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < n7) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  for (int64_t k = ((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE; k < n7; k += (int64_t)gridDim.x * (BLOCK / WAVE)) {
     int32_t v = hubs[k];
     int64_t bs = INT64_MIN, own = 0;
     int32_t bcl = INT32_MAX;
-    for (int32_t ch = chunk_off[k]; ch < chunk_off[k + 1]; ++ch) {
+    for (int32_t ch = chunk_off[k] + lane; ch < chunk_off[k + 1]; ch += WAVE) {
       if (better(ps[ch], pc[ch], bs, bcl)) { bs = ps[ch]; bcl = pc[ch]; }
       if (pown) own += pown[ch];
     }
+    argmax_reduce<WAVE>(bs, bcl);
+    own = sum_reduce<WAVE>(own);
+    if (lane) continue;
     int32_t cv = C ? C[v] : v;
     finish_vertex(v, cv, vw[v], own, bs, bcl, ss.at(v), C ? W : vw, pa, pb, strict, vs, va, ss.ownv);
     if (off) va.bytes += enum_bytes(off[v + 1] - off[v], 0);
@@ -1815,7 +1856,6 @@ void launch_objective(const DevGraph& g, const Buckets& b, const int32_t* C, con
   k_sw2<<<red_blocks(g.n), BLOCK, 0, st>>>(W, g.n, &ctrl->obj_SW2, nullptr, -1);
 }
 
-static const int32_t* L_hubs(const Buckets& b);
 static HubScratch hub_scratch(const Buckets& b);
 
 // One pass of destinations + candidacy.  singleton: first coarsening pass (C = identity).
@@ -1843,7 +1883,7 @@ static void launch_destinations(const DevGraph& g, const Buckets& b, const Score
     if (b.count[6]) k_single_blk<BIG_BLOCK><<<vtx_blocks(b, b.count[6]), BIG_BLOCK, 0, st>>>(L + b.off[6], b.count[6], g, sc, pa, pb, vs, slot, pass, S);
     if (n7) {
       k_single_hub<<<(unsigned)b.hub_chunks, HUB_BLOCK, 0, st>>>(hubs, b.hub_chunk_off, n7, g, sc, hs.ps, hs.pc);
-      k_hub_final<<<grid_for(n7), BLOCK, 0, st>>>(hubs, b.hub_chunk_off, n7, g.vw, nullptr, nullptr, sc, pa, pb, 0,
+      k_hub_final<<<grp_blocks(b, n7, WAVE), BLOCK, 0, st>>>(hubs, b.hub_chunk_off, n7, g.vw, nullptr, nullptr, sc, pa, pb, 0,
                                                  hs.ps, hs.pc, nullptr, vs, slot, pass, S, -1);
     }
     prof_end(PF_SINGLE, sb, st);
@@ -1895,10 +1935,10 @@ static void launch_destinations(const DevGraph& g, const Buckets& b, const Score
   if (n7) {
     unsigned nc = (unsigned)b.hub_chunks;
     prof_begin(PF_ENUM_B0 + 7, st);
-    k_hub_insert<<<nc, HUB_BLOCK, 0, st>>>(hubs, b.hub_chunk_off, n7, g, C, bufs.arena, slot, pass, sc.cons);
-    k_hub_scan<<<nc, HUB_BLOCK, 0, st>>>(hubs, b.hub_chunk_off, n7, g, C, W, sc, bufs.arena, hs.ps, hs.pc, hs.pown, slot, pass,
-                                         S, cp(7));
-    k_hub_final<<<grid_for(n7), BLOCK, 0, st>>>(hubs, b.hub_chunk_off, n7, g.vw, C, W, sc, pa, pb, strict, hs.ps,
+    k_hub_part<<<nc, HUB_BLOCK, 0, st>>>(hubs, b.hub_chunk_off, n7, g, C, bufs.arena, hs.pown, slot, pass, sc.cons);
+    k_hub_best<<<nc, HUB_BLOCK, 0, st>>>(hubs, b.hub_chunk_off, n7, g, C, W, sc, bufs.arena, hs.ps, hs.pc, slot, pass, S,
+                                         cp(7));
+    k_hub_final<<<grp_blocks(b, n7, WAVE), BLOCK, 0, st>>>(hubs, b.hub_chunk_off, n7, g.vw, C, W, sc, pa, pb, strict, hs.ps,
                                                hs.pc, hs.pown, vs, slot, pass, S, co, g.off, cp(7));
     prof_end(PF_ENUM_B0 + 7, 0.0, st);
   }
@@ -1908,7 +1948,6 @@ static void launch_destinations(const DevGraph& g, const Buckets& b, const Score
            {CT_PAIRS + 7, P ? P + 7 : nullptr}}, st, pending);
 }
 
-static const int32_t* L_hubs(const Buckets& b) { return b.list + b.off[7]; }
 
 static HubScratch hub_scratch(const Buckets& b) {
   HubScratch hs;
@@ -2033,9 +2072,6 @@ void local_move(const DevGraph& g, const Buckets& b, const LMParams& prm, bool s
     fill_i64(sg.ownv, 0, n, st);
   }
   state_sums_sw2(sg, bufs.W, n, slot, 0, -1, st);
-  if (b.count[7])
-    k_hub_clear<<<(unsigned)b.hub_chunks, HUB_BLOCK, 0, st>>>(L_hubs(b), b.hub_chunk_off, b.count[7], g.off,
-                                                             bufs.arena, nullptr, -1);
   // Counters the kernels leave in the stripes are folded by the next bookkeeping kernel of a single graph
   // (no launch of their own); a union folds them at once.
   int64_t* S = b.stripes;
@@ -2106,9 +2142,6 @@ void launch_apply_and_empty(const DevGraph& g, const Buckets& b, LMBuffers& bufs
 void launch_destinations_strict(const DevGraph& g, const Buckets& b, const ScoreSrc& ss, LMBuffers& bufs,
                                 LMSlot* slot, hipStream_t st) {
   const HubScratch hs = hub_scratch(b);
-  if (b.count[7])
-    k_hub_clear<<<(unsigned)b.hub_chunks, HUB_BLOCK, 0, st>>>(L_hubs(b), b.hub_chunk_off, b.count[7], g.off,
-                                                             bufs.arena, nullptr, -1);
   launch_destinations(g, b, ss, 0, 1, 1, false, bufs, slot, 0, nullptr, hs, st);
 }
 
