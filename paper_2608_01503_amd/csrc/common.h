@@ -484,9 +484,11 @@ struct TeamHost {
   uint32_t turn = 0;
 };
 // Levels of up to this many entries (and a fourth as many vertices) take the team: an eighth of the chip, but no
-// launches between phases.  A local move on 27,000 entries takes 0.11 ms in the team and 0.33 ms in launches; on
-// 470,000 entries (kNN, 20,000 vertices) 0.72 against 0.35 ms.
-constexpr int64_t TEAM_ENTRIES = (int64_t)1 << 18;
+// launches between phases.  Whole calls at 2^18, 2^19 and 2^20: kNN graph of 20,000 vertices (470,000 entries),
+// Louvain+, 1.64, 1.36 and 1.36 ms; SBM of 70,000, pLeiden, 6.75, 5.42 and 6.07 ms; SBM of 300,000 14.5, 13.6 and 13.5
+// ms; R-MAT of 2^14 9.9, 9.1 and 9.1 ms; a lattice of 16.8 M, whose small levels have few entries per vertex, 105, 105
+// and 129 ms.
+constexpr int64_t TEAM_ENTRIES = (int64_t)1 << 19;
 inline bool team_level(int64_t n, int64_t nnz) { return nnz <= TEAM_ENTRIES && n <= TEAM_ENTRIES / 4; }
 struct TeamArgs;
 void team_launch(TeamArgs& a, TeamHost& h, hipStream_t st);

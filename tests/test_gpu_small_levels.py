@@ -29,8 +29,8 @@ GRAPHS = {
     "long rows": lambda: _rows([4096, 4097, 8191, 8192, 8193, 9500], 40000, 2),
     "pair": lambda: gg.from_pairs(2, [(0, 1)]),
     "star": lambda: gg.from_pairs(1026, [(0, i) for i in range(1, 1026)]),
-    "limit": lambda: gg.random_gnp(1500, 0.1165, 3, w_max=3),  # about 2^18 entries
-    "above limit": lambda: gg.random_gnp(1500, 0.119, 3, w_max=3),
+    "limit": lambda: gg.random_gnp(2200, 0.1075, 3, w_max=3),  # about 2^19 entries
+    "above limit": lambda: gg.random_gnp(2200, 0.1095, 3, w_max=3),
 }
 
 
