@@ -11,6 +11,7 @@
 //          (w(X_i, B \ X_i) = sum_{j <= i} a(v_j, B \ v_j) - 2 a(v_j, X_{j-1})); the longest all-valid prefix
 //          takes the root's id, every other vertex keeps its own id.
 #include "common.h"
+#include "rows.h"
 
 namespace lcc {
 
@@ -43,11 +44,7 @@ __device__ __forceinline__ int find_chunk_owner(const int32_t* chunk_off, int64_
 }
 
 template <int G>
-__device__ __forceinline__ int64_t gsum(int64_t x) {
-#pragma unroll
-  for (int o = G / 2; o > 0; o >>= 1) x += __shfl_xor(x, o, G);
-  return x;
-}
+__device__ __forceinline__ int64_t gsum(int64_t x) { return sum_steps<G>(x); }
 
 __device__ __forceinline__ uint64_t fkey(int32_t v, const RefSrc& rs, const uint8_t* flip) {
   uint64_t f = fmix32(rs.loc(v) ^ rs.fseed(v));

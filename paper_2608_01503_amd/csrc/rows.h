@@ -20,23 +20,29 @@ __device__ __forceinline__ bool better(int64_t s2, int32_t c2, int64_t s, int32_
 // mirror (lane i of an 8-lane half-row <-> lane 7 - i) and the row mirror (i <-> 15 - i).  The mirror partners
 // are not xor partners, but each step pairs every lane with one in the other half of its 2^(K+1)-lane block,
 // whose lanes all hold the same value after the earlier steps: an all-reduction of a commutative and
-// associative operation gets the same result.  Wider groups use shuffles.
+// associative operation gets the same result.  The steps between rows of 16 swap rows (permlane16_swap: the odd rows
+// of its first operand with the even rows of its second, permlane32_swap the same with halves), also without LDS:
+// with shuffles, two LDS permutes per step and 64-bit value, the chain of a 32-lane argmax was about 600 cycles.
 constexpr int DPP_GROUP_STEP[4] = {0xB1, 0x4E, 0x141, 0x140};
 
 template <int G, int K>
 __device__ __forceinline__ int32_t gx32(int32_t x) {
-  if constexpr (G <= 16) return __builtin_amdgcn_update_dpp(0, x, DPP_GROUP_STEP[K], 0xf, 0xf, false);
-  else return __shfl_xor(x, 1 << K, G);
+  static_assert((1 << K) < G && G <= WAVE, "a step inside the group");
+  if constexpr (K < 4) {
+    return __builtin_amdgcn_update_dpp(0, x, DPP_GROUP_STEP[K], 0xf, 0xf, false);
+  } else if constexpr (K == 4) {
+    const auto r = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
+    return (int32_t)((threadIdx.x & 16) ? r[0] : r[1]);
+  } else {
+    const auto r = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
+    return (int32_t)((threadIdx.x & 32) ? r[0] : r[1]);
+  }
 }
 template <int G, int K>
 __device__ __forceinline__ int64_t gx64(int64_t x) {
-  if constexpr (G <= 16) {
-    const int32_t lo = gx32<G, K>((int32_t)(uint32_t)(uint64_t)x);
-    const int32_t hi = gx32<G, K>((int32_t)((uint64_t)x >> 32));
-    return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo);
-  } else {
-    return __shfl_xor(x, 1 << K, G);
-  }
+  const int32_t lo = gx32<G, K>((int32_t)(uint32_t)(uint64_t)x);
+  const int32_t hi = gx32<G, K>((int32_t)((uint64_t)x >> 32));
+  return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint64_t)(uint32_t)lo);
 }
 
 // Lane K of every aligned group of G lanes (G = 4: quad permutation; 8 and 16: row broadcasts; else shuffle).
