@@ -97,7 +97,11 @@ struct TeamOut {
   int64_t Nbest, N0, nlab;                // as in the slot
   int64_t alt, alt_k, alt_best_k, alt_N;  // the alternate local move's movers, committed prefix and objective
   int64_t refined, refine_n, refine_U, refine_m, cycle;
-  int64_t coarse, coarse_nnz, coarse_w2, coarse_boff[NBUCKET + 1];
+  int64_t coarse, coarse_nnz, coarse_w2, coarse_boff[NBUCKET + 1];  // coarse_boff: of the input after the setup
+  int64_t obj_I, obj_SW2;                 // the result's objective
+  // setup: ERRB bits, entries towards lower-ranked minus towards higher-ranked vertices, total weights
+  uint32_t err, bad_offsets;
+  int64_t balance, sum_we, sum_w, sum_w2;
 };
 
 // Scalars shared by the driver and the kernels.
@@ -492,6 +496,7 @@ constexpr int64_t TEAM_ENTRIES = (int64_t)1 << 19;
 inline bool team_level(int64_t n, int64_t nnz) { return nnz <= TEAM_ENTRIES && n <= TEAM_ENTRIES / 4; }
 struct TeamArgs;
 void team_launch(TeamArgs& a, TeamHost& h, hipStream_t st);
+void team_setup_launch(TeamArgs& a, TeamHost& h, hipStream_t st);
 
 // contract.hip
 // used flags of labels -> rank (compact map) : rank[c] for c in [0, n), count at rank[n].

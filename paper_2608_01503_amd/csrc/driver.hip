@@ -47,7 +47,7 @@ constexpr int NSLOT = 4 * 1024 + 16;
 // The slots' part of a workspace, also holding the team launches' blocks.  Its size belongs to the figure that
 // lcc_workspace_bytes reports and no-allocation calls are admitted by.
 constexpr size_t SLOT_BYTES = (size_t)NSLOT * 1232;
-static_assert(NSLOT * sizeof(LMSlot) + 256 + TEAM_SLOTS * sizeof(TeamCtl) + sizeof(TeamOut) + 16 * TEAM_MAX <= SLOT_BYTES,
+static_assert((NSLOT + 1) * sizeof(LMSlot) + 256 + TEAM_SLOTS * sizeof(TeamCtl) + sizeof(TeamOut) + 16 * TEAM_MAX <= SLOT_BYTES,
               "the slots and the team's blocks share their part");
 
 inline size_t align_up(size_t x) { return (x + ALIGN - 1) & ~(ALIGN - 1); }
@@ -101,7 +101,7 @@ size_t carve(WS& w, char* base, int64_t n, int64_t nnz) {
   w.slots = (LMSlot*)slots;
   w.team = TeamHost{};
   if (slots) {
-    w.team.ctl = (TeamCtl*)(slots + align_up(NSLOT * sizeof(LMSlot)));
+    w.team.ctl = (TeamCtl*)(slots + align_up((NSLOT + 1) * sizeof(LMSlot)));  // slot NSLOT: of launches without a local move
     w.team_out = (TeamOut*)(w.team.ctl + TEAM_SLOTS);
     w.team_best = (int64_t*)(w.team_out + 1);
   }
@@ -449,6 +449,8 @@ struct Run {
   uint32_t flags = 0;
   uint64_t W = 0;
   uint64_t refine_calls = 0;
+  int32_t* labels = nullptr;  // where the compact labels go (device)
+  bool finished = false;      // a team launch has put them there, and the objective in its block
   // union of G graphs (G > 0): per-graph scoring parameters and local-move statistics on the device
   int64_t G = 0;
   Score* d_score = nullptr;
@@ -577,6 +579,33 @@ struct Run {
   // a level small enough for the team launches (single graphs; kernel timing measures the bucket kernels)
   bool small(const Level& L) const { return !G && team_level(L.g.n, L.g.nnz) && !prof_on(); }
 
+  // The input of a call whose level 0 takes the team, up to the point where the host checks the sums.
+  void team_setup(const lcc_graph* g, const Level& L, const int32_t* off32, bool ones, const int64_t* vw_given, const int32_t* init) {
+    TeamArgs a{};
+    a.n = (int32_t)L.g.n;
+    a.nnz = (int32_t)L.g.nnz;
+    a.off = const_cast<int64_t*>(L.g.off); a.idx = const_cast<int32_t*>(L.g.idx); a.w = const_cast<int32_t*>(L.g.w);
+    a.vw = w.vw0;
+    a.list = w.list0;
+    a.rows = (uint64_t*)w.hub_ps;
+    a.bounds = ctx->bounds();
+    a.out = w.team_out;
+    a.st.off = w.ux;
+    a.off32 = off32;
+    a.ones = ones;
+    a.search = o.validate;
+    a.vw_mode = (int32_t)g->vw_mode;
+    a.vw_given = vw_given;
+    a.init = init;
+    team_setup_launch(a, w.team, st);
+  }
+  TeamOut read_team(const char* what) {
+    TeamOut* h = (TeamOut*)ctx->h_slots;  // the mirror's slots are read at the end of the call
+    hip_check(hipMemcpyAsync(h, w.team_out, sizeof(TeamOut), hipMemcpyDeviceToHost, st), what);
+    sync(what);
+    return *h;
+  }
+
   // A team launch on level l.  With TEAM_CONTRACT it leaves the next level in the stage (arrays of the workspace that
   // no later phase before the next launch uses) and the sizes in the slot, for adopt().
   void team(int l, int32_t steps, bool singleton, bool constrained, int s) {
@@ -606,6 +635,7 @@ struct Run {
     a.out = w.team_out;
     a.used = w.used; a.rank = w.rank;
     if (steps & TEAM_PROJECT) a.up_C = lv[l + 1].C;
+    a.labels = labels;
     a.map = L.map;
     a.B = L.B;
     a.st.raw = w.k0; a.st.seg = w.k1; a.st.end = w.cnt; a.st.start = (int32_t*)w.v0; a.st.cnt = (int32_t*)w.v1;
@@ -674,10 +704,7 @@ struct Run {
     const int64_t n = lv[l].g.n;
     TeamOut r{};
     if (small(lv[l])) {
-      TeamOut* h = (TeamOut*)ctx->h_slots;  // the mirror's slots are read at the end of the call
-      hip_check(hipMemcpyAsync(h, w.team_out, sizeof(TeamOut), hipMemcpyDeviceToHost, st), "level");
-      sync("level");
-      r = *h;
+      r = read_team("level");
     } else {
       LMSlot* h = ctx->h_slots + s;
       hip_check(hipMemcpyAsync(h, w.slots + s, sizeof(LMSlot), hipMemcpyDeviceToHost, st), "slot");
@@ -841,11 +868,14 @@ struct Run {
   void uncoarsen(int top, bool plus) {
     for (int k = top - 1; k >= 0; --k) {
       Level& L = lv[k];
+      const int32_t more = TEAM_PROJECT | (k == 0 && small(L) ? TEAM_FINISH : 0);
+      finished = more & TEAM_FINISH;
       if (!plus) {
-        launch_project(lv[k + 1].C, L.map, L.g.n, L.C, st);
+        if (finished) team(k, more, false, false, NSLOT);
+        else launch_project(lv[k + 1].C, L.map, L.g.n, L.C, st);
         continue;
       }
-      const int s = local_move_level(k, false, 1, nullptr, TEAM_PROJECT);
+      const int s = local_move_level(k, false, 1, nullptr, more);
       rec(-2, k, 1, 0, L.g.n, L.g.nnz, s, 0);
     }
   }
@@ -1171,9 +1201,43 @@ uint64_t gcd64(uint64_t a, uint64_t b) {
   return a;
 }
 
+// The setup's checks and scoring parameters from its error bits and sums (unbalanced: the symmetry search met more
+// entries on one side than on the other).
+void finish_setup(Run& R, lcc_lambda lam, uint32_t e, bool unbalanced, uint64_t sum_we, uint64_t sum_w, uint64_t sum_w2) {
+  if (!R.o.validate) e &= ERRB_INVALID | ERRB_VW_TOO_BIG;  // structural faults that would break the kernels
+  if (e & ERRB_INVALID) fail(LCC_ERR_INVALID, "neighbour index out of range (or initial label outside [0, n))");
+  if (e & ERRB_SELF_LOOP) fail(LCC_ERR_SELF_LOOP, "a row contains its own vertex");
+  if (e & ERRB_UNSORTED) fail(LCC_ERR_UNSORTED, "a row is not strictly ascending");
+  if (e & ERRB_WEIGHT) fail(LCC_ERR_WEIGHT, "an edge weight <= 0 or a vertex weight < 0");
+  if ((e & ERRB_NOT_SYMMETRIC) || unbalanced) fail(LCC_ERR_NOT_SYMMETRIC, "the graph is not symmetric");
+  if (sum_we >= ((uint64_t)1 << 32)) fail(LCC_ERR_OVERFLOW, "total edge weight >= 2^32");
+  if (e & ERRB_VW_TOO_BIG) fail(LCC_ERR_OVERFLOW, "a vertex weight >= 2^31");
+  R.lv[0].sum_w2 = (int64_t)sum_w2;
+  R.W = sum_w;
+  const unsigned __int128 W = sum_w, WE = sum_we;
+  if (lam.den == 0) fail(LCC_ERR_LAMBDA, "lambda denominator is zero");
+  unsigned __int128 P = lam.num, Q = (unsigned __int128)lam.den * (lam.over_total_weight ? W : 1);
+  if (Q == 0 || P > Q) fail(LCC_ERR_LAMBDA, "lambda outside [0, 1] or undefined");
+  if (Q >> 64) fail(LCC_ERR_OVERFLOW, "lambda denominator >= 2^64");
+  uint64_t p = (uint64_t)P, q = (uint64_t)Q;
+  if (p == 0) q = 1;
+  else { uint64_t d = gcd64(p, q); p /= d; q /= d; }
+  if ((unsigned __int128)q * WE + (unsigned __int128)p * W * W >= ((unsigned __int128)1 << 62))
+    fail(LCC_ERR_OVERFLOW, "q W_E + p W^2 >= 2^62");
+  R.p = (int64_t)p;
+  R.q = (int64_t)q;
+  R.sc.p = R.p;
+  R.sc.q = R.q;
+  // tie window: |delta_u - delta_v| <= floor((eps_num q - 1) / (2 eps_den)), at least 0
+  __int128 num = (__int128)R.o.eps_num * q - 1;
+  __int128 den = 2 * (__int128)R.o.eps_den;
+  __int128 t = num >= 0 ? num / den : -1;
+  R.sc.tie = t < 0 ? 0 : (int64_t)t;
+}
+
 // Setup (Sec. II): copy or adopt the input, validate it on the device, derive vertex weights, W, W_E,
 // lambda = p / q in lowest terms and the exactness bound.  Fills lv[0].
-void setup(Run& R, const lcc_graph* g, lcc_lambda lam, const int32_t* init_labels) {
+void setup(Run& R, const lcc_graph* g, lcc_lambda lam, const int32_t* init_labels, bool cluster) {
   lcc_ctx* ctx = R.ctx;
   WS& w = R.w;
   hipStream_t st = R.st;
@@ -1185,22 +1249,28 @@ void setup(Run& R, const lcc_graph* g, lcc_lambda lam, const int32_t* init_label
   auto cp = [&](void* dst, const void* src, size_t bytes) {
     if (bytes) hip_check(hipMemcpyAsync(dst, src, bytes, host ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, st), "input copy");
   };
+  const bool team = cluster && R.small(L0);
   // offsets
+  const int32_t* off32 = nullptr;
   if (g->offsets_bits == 64 && !host) {
     L0.g.off = (const int64_t*)g->offsets;
   } else if (g->offsets_bits == 64) {
     cp(w.in_off, g->offsets, (size_t)(n + 1) * 8);
     L0.g.off = w.in_off;
   } else {
-    int32_t* tmp = (int32_t*)w.k0;  // staging for 32-bit offsets
-    cp(tmp, g->offsets, (size_t)(n + 1) * 4);
-    offsets32_to_64(tmp, w.in_off, n + 1, st);
+    off32 = (const int32_t*)g->offsets;
+    if (!team || host) {
+      int32_t* tmp = (int32_t*)w.k0;  // staging for 32-bit offsets
+      cp(tmp, g->offsets, (size_t)(n + 1) * 4);
+      off32 = tmp;
+    }
+    if (!team) offsets32_to_64(off32, w.in_off, n + 1, st);
     L0.g.off = w.in_off;
   }
   if (host) { cp(w.in_idx, g->indices, (size_t)nnz * 4); L0.g.idx = w.in_idx; }
   else L0.g.idx = g->indices;
   if (!g->edge_w) {
-    k_ones<<<grid1(nnz), BLOCK, 0, st>>>(w.in_w, nnz);
+    if (!team) k_ones<<<grid1(nnz), BLOCK, 0, st>>>(w.in_w, nnz);
     L0.g.w = w.in_w;
   } else if (host) {
     cp(w.in_w, g->edge_w, (size_t)nnz * 4);
@@ -1215,6 +1285,18 @@ void setup(Run& R, const lcc_graph* g, lcc_lambda lam, const int32_t* init_label
   }
   L0.g.vw = w.vw0;
   L0.C = take<int32_t>(ctx, n);
+  if (team) {
+    R.team_setup(g, L0, off32, !g->edge_w, vwg, init_labels);
+    const TeamOut c = R.read_team("setup");
+    if (c.bad_offsets) fail(LCC_ERR_INVALID, "CSR offsets are not a valid row partition");
+    Buckets& b = L0.b;
+    b.list = w.list0;
+    for (int k = 0; k <= NBUCKET; ++k) b.off[k] = c.coarse_boff[k];
+    b.hash_shift = ctx->tune.hash_shift;
+    R.lv.push_back(L0);
+    finish_setup(R, lam, c.err, c.balance != 0, c.sum_we, c.sum_w, c.sum_w2);
+    return;
+  }
   zero_bytes(w.ctrl, sizeof(Ctrl), st);
   // offsets
   launch_validate_offsets(L0.g.off, n, nnz, w.ctrl, st);
@@ -1261,36 +1343,7 @@ void setup(Run& R, const lcc_graph* g, lcc_lambda lam, const int32_t* init_label
   R.read_ctrl("validate rows");
   ctx->pool_release(sym_mark);
   const Ctrl& c = *ctx->h_ctrl;
-  uint32_t e = c.err_bits;
-  if (!R.o.validate) e &= ERRB_INVALID | ERRB_VW_TOO_BIG;  // structural faults that would break the kernels
-  if (e & ERRB_INVALID) fail(LCC_ERR_INVALID, "neighbour index out of range (or initial label outside [0, n))");
-  if (e & ERRB_SELF_LOOP) fail(LCC_ERR_SELF_LOOP, "a row contains its own vertex");
-  if (e & ERRB_UNSORTED) fail(LCC_ERR_UNSORTED, "a row is not strictly ascending");
-  if (e & ERRB_WEIGHT) fail(LCC_ERR_WEIGHT, "an edge weight <= 0 or a vertex weight < 0");
-  if ((e & ERRB_NOT_SYMMETRIC) || (sb.search && c.count0 != 0)) fail(LCC_ERR_NOT_SYMMETRIC, "the graph is not symmetric");
-  if (c.sum_we >= ((uint64_t)1 << 32)) fail(LCC_ERR_OVERFLOW, "total edge weight >= 2^32");
-  if (e & ERRB_VW_TOO_BIG) fail(LCC_ERR_OVERFLOW, "a vertex weight >= 2^31");
-  L.sum_w2 = (int64_t)c.sum_w2;
-  R.W = c.sum_w;
-  const unsigned __int128 W = c.sum_w, WE = c.sum_we;
-  if (lam.den == 0) fail(LCC_ERR_LAMBDA, "lambda denominator is zero");
-  unsigned __int128 P = lam.num, Q = (unsigned __int128)lam.den * (lam.over_total_weight ? W : 1);
-  if (Q == 0 || P > Q) fail(LCC_ERR_LAMBDA, "lambda outside [0, 1] or undefined");
-  if (Q >> 64) fail(LCC_ERR_OVERFLOW, "lambda denominator >= 2^64");
-  uint64_t p = (uint64_t)P, q = (uint64_t)Q;
-  if (p == 0) q = 1;
-  else { uint64_t d = gcd64(p, q); p /= d; q /= d; }
-  if ((unsigned __int128)q * WE + (unsigned __int128)p * W * W >= ((unsigned __int128)1 << 62))
-    fail(LCC_ERR_OVERFLOW, "q W_E + p W^2 >= 2^62");
-  R.p = (int64_t)p;
-  R.q = (int64_t)q;
-  R.sc.p = R.p;
-  R.sc.q = R.q;
-  // tie window: |delta_u - delta_v| <= floor((eps_num q - 1) / (2 eps_den)), at least 0
-  __int128 num = (__int128)R.o.eps_num * q - 1;
-  __int128 den = 2 * (__int128)R.o.eps_den;
-  __int128 t = num >= 0 ? num / den : -1;
-  R.sc.tie = t < 0 ? 0 : (int64_t)t;
+  finish_setup(R, lam, c.err_bits, sb.search && c.count0 != 0, c.sum_we, c.sum_w, c.sum_w2);
 }
 
 // Scoring parameters of one graph (lambda = p / q in lowest terms, tie window), or a failure status.
@@ -1464,7 +1517,8 @@ lcc_status cluster_impl(lcc_ctx* ctx, const lcc_graph* g, lcc_lambda lam, lcc_va
     init_labels = up(init_labels);
     constraint = up(constraint);
   }
-  setup(R, g, lam, init_labels);
+  R.labels = (g->mem == LCC_MEM_DEVICE) ? labels_out : R.w.in_labels;
+  setup(R, g, lam, init_labels, true);
   R.lv[0].B = const_cast<int32_t*>(constraint);
   if (variant == LCC_LOUVAIN || variant == LCC_PLEIDEN) R.use_pingpong(n, g->nnz);
   int top = 0;
@@ -1472,14 +1526,22 @@ lcc_status cluster_impl(lcc_ctx* ctx, const lcc_graph* g, lcc_lambda lam, lcc_va
   else top = R.leiden(variant == LCC_PLEIDEN_PLUS, init_labels);
   // final compaction on level 0 and the exact objective (Eq. 1) of the result
   Level& L0 = R.lv[0];
-  int64_t nc = R.count_labels(L0.C, n);
-  int32_t* lab = (g->mem == LCC_MEM_DEVICE) ? labels_out : R.w.in_labels;
-  launch_map_labels(L0.C, R.w.rank, n, lab, st);
-  launch_cluster_weights(lab, L0.g.vw, n, R.w.W, st);
-  launch_objective(L0.g, L0.b, lab, R.w.W, R.w.ctrl, st);
-  R.read_ctrl("objective");
-  if (ctx->prof_mask) prof_resolve(ctx, ctx->h_ctrl);
-  __int128 N = (__int128)R.q * ctx->h_ctrl->obj_I - (__int128)R.p * (ctx->h_ctrl->obj_SW2 - L0.sum_w2);
+  int32_t* lab = R.labels;
+  int64_t nc, obj_I, obj_SW2;
+  if (R.small(L0)) {
+    if (!R.finished) R.team(0, TEAM_FINISH, false, false, NSLOT);
+    const TeamOut r = R.read_team("objective");
+    nc = r.nlab; obj_I = r.obj_I; obj_SW2 = r.obj_SW2;
+  } else {
+    nc = R.count_labels(L0.C, n);
+    launch_map_labels(L0.C, R.w.rank, n, lab, st);
+    launch_cluster_weights(lab, L0.g.vw, n, R.w.W, st);
+    launch_objective(L0.g, L0.b, lab, R.w.W, R.w.ctrl, st);
+    R.read_ctrl("objective");
+    obj_I = ctx->h_ctrl->obj_I; obj_SW2 = ctx->h_ctrl->obj_SW2;
+    if (ctx->prof_mask) prof_resolve(ctx, ctx->h_ctrl);
+  }
+  __int128 N = (__int128)R.q * obj_I - (__int128)R.p * (obj_SW2 - L0.sum_w2);
   if (g->mem == LCC_MEM_HOST) {
     hip_check(hipMemcpyAsync(labels_out, lab, (size_t)n * 4, hipMemcpyDeviceToHost, st), "labels");
     R.sync("labels");
@@ -2080,7 +2142,7 @@ lcc_status lcc_objective_device(lcc_ctx* ctx, const lcc_graph* g, lcc_lambda lam
       lab = R.w.in_labels;
     }
     R.lv.reserve(2);
-    setup(R, g, lam, lab);
+    setup(R, g, lam, lab, false);
     Level& L0 = R.lv[0];
     int64_t nc = R.count_labels(lab, g->n);
     launch_cluster_weights(lab, L0.g.vw, g->n, R.w.W, st);

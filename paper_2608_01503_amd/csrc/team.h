@@ -47,7 +47,8 @@ enum : int32_t {
   TEAM_MOVE = 4,      // LocalMovePasses
   TEAM_ALTERNATE = 8, // the alternate local move, if the objective is unchanged
   TEAM_REFINE = 16,   // refinement; the contraction goes by it
-  TEAM_CONTRACT = 32  // build the next level in the stage
+  TEAM_CONTRACT = 32, // build the next level in the stage
+  TEAM_FINISH = 64    // compact labels and objective of the level's clustering (of level 0)
 };
 
 // Arguments of a team launch on one level.
@@ -101,6 +102,13 @@ struct TeamArgs {
   uint8_t *inU, *flip, *has_child;
   int32_t *H, *par, *par2, *root, *rel, *tsz, *toff, *trees, *R, *rankR;
   uint64_t* keys;               // 2 n
+  // finish
+  int32_t* labels;
+  // setup: the input's offsets (32-bit ones are copied to off), entries, weights of vertices and initial labels
+  const int32_t* off32;
+  int32_t nnz, ones, search, vw_mode;
+  const int64_t* vw_given;
+  const int32_t* init;
   // alternate local move: movers in ascending order, the flow into a mover's own cluster and into its destination
   // before it, the adjacent part of its gain; every member's best prefix
   int32_t *pos, *relD;

@@ -12,7 +12,9 @@
 // With only the local move in one launch a level still took 35 launches and 4 host reads for the contraction and 40
 // and 2 for the refinement; now it takes one launch and one read.  SBM graph of 2,000 vertices, Louvain+: 1058 -> 640
 // us a call; kNN graph of 3,000, pLeiden+: 5277 -> 2683 us; R-MAT graph of 2^14, pLeiden: 27.3 -> 14.6 ms.  The
-// alternate local move, about 30 launches and 2 reads where it is taken, joined them: 2683 -> 1594 us and 14.6 -> 11.5 ms.
+// alternate local move, about 30 launches and 2 reads where it is taken, joined them: 2683 -> 1594 us and 14.6 -> 11.5
+// ms.  The checks of a small input and the compaction and objective of its result, 28 launches and 5 reads, are a
+// launch of their own and a part of the last one: 567 -> 451 us and 1290 -> 1180 us.
 #include <algorithm>
 
 #include "team.h"
@@ -128,10 +130,8 @@ __device__ __forceinline__ void team_row_words(const Team& t, KP kp) {
 // per bucket a pass over 27,000 entries took 28 us, most of it six such chains one after the other).  The next task's
 // row words are loaded before a task is worked on.
 template <typename Op>
-__device__ __forceinline__ void team_tasks(const Team& t, KP kp, Op& op) {
-  TEAM_PHASE(kp);
+__device__ __forceinline__ void team_tasks_at(const Team& t, KP kp, Op& op, int e0, int e1, int e2, int e3, int e4) {
   const int tx = team_tx(), lane = tx & (WAVE - 1), wv = uniform32(tx / WAVE);
-  const int e0 = kp->boff[1], e1 = kp->boff[2], e2 = kp->boff[3], e3 = kp->boff[4], e4 = kp->boff[NBUCKET];
   const int n4 = e4 - e3, n3 = n4 + (e3 - e2 + 1) / 2, n2 = n3 + (e2 - e1 + 3) / 4, n1 = n2 + (e1 - e0 + 7) / 8,
             n0 = n1 + (e0 + 15) / 16;
   const auto word = [&](int k) __attribute__((always_inline)) {  // ~0: no row for this lane
@@ -161,13 +161,18 @@ __device__ __forceinline__ void team_tasks(const Team& t, KP kp, Op& op) {
   }
 }
 
+template <typename Op>
+__device__ __forceinline__ void team_tasks(const Team& t, KP kp, Op& op) {
+  TEAM_PHASE(kp);
+  team_tasks_at(t, kp, op, kp->boff[1], kp->boff[2], kp->boff[3], kp->boff[4], kp->boff[NBUCKET]);
+}
+
 // f(row) for this member's rows above `min` entries (min >= 128), by the whole workgroup.  Every wavefront looks at 64
 // of the member's rows at a time.
 template <typename F>
-__device__ __forceinline__ void team_long(const Team& t, KP kp, int min, F f) {
-  TEAM_PHASE(kp);
-  const int lane = team_tx() & (WAVE - 1), end = kp->boff[NBUCKET];
-  for (int i0 = kp->boff[5] + t.rank; i0 < end; i0 += t.n * WAVE) {  // uniform over the workgroup
+__device__ __forceinline__ void team_long_at(const Team& t, KP kp, int min, int begin, int end, F f) {
+  const int lane = team_tx() & (WAVE - 1);
+  for (int i0 = begin + t.rank; i0 < end; i0 += t.n * WAVE) {  // uniform over the workgroup
     const int i = i0 + lane * t.n;
     const uint64_t x = i < end ? ald(kp->rows + i) : 0;
     for (uint64_t m = __ballot(row_of(x).d > min); m; m &= m - 1) {
@@ -176,6 +181,12 @@ __device__ __forceinline__ void team_long(const Team& t, KP kp, int min, F f) {
       f(row_of((uint64_t)hi << 32 | lo));
     }
   }
+}
+
+template <typename F>
+__device__ __forceinline__ void team_long(const Team& t, KP kp, int min, F f) {
+  TEAM_PHASE(kp);
+  team_long_at(t, kp, min, kp->boff[5], kp->boff[NBUCKET], f);
 }
 
 // First pass from singletons: the clusters are the neighbours.
@@ -1647,6 +1658,168 @@ __device__ __forceinline__ void team_refine(Team& t, KP kp) {
   t.sync();
 }
 
+// --- the ends of a call whose level 0 is small
+
+// entries of a row inside its cluster
+struct FinishOp {
+  int64_t s = 0;
+  template <int U>
+  __device__ __forceinline__ void part(KP kp, const TeamRow& r, int x, int S) {
+    const int32_t cv = ald(kp->Cout + r.v);
+    s += team_row_sum<U>(kp, r, x, S, [&](int32_t u) __attribute__((always_inline)) { return ald(kp->Cout + u); },
+                         [&](int32_t c, int32_t, int32_t w) __attribute__((always_inline)) { return c == cv ? (int64_t)w : 0; });
+  }
+  template <int G>
+  __device__ __forceinline__ void group(KP kp, const TeamRow& r, int gl) { part<1>(kp, r, gl, G); }
+  __device__ __forceinline__ void wave(KP kp, const TeamRow& r, int lane) { part<4>(kp, r, lane, WAVE); }
+};
+
+// labels[v] = rank of C_out[v] among the ids in use; the clustering's objective
+__device__ __forceinline__ void team_finish_call(Team& t, KP kp) {
+  team_each(t, kp, kp->n, [](KP kp, int v) __attribute__((always_inline)) { ast(kp->WB + v, (int64_t)0); });
+  t.sync();
+  agg_clear();
+  team_each(t, kp, kp->n, [](KP kp, int v) __attribute__((always_inline)) {
+    const int32_t c = ald(kp->rank + ald(kp->Cout + v));
+    kp->labels[v] = c;
+    agg_add(kp->WB, kp->cnt, c, kp->vw[v], 0);
+  });
+  agg_flush(kp->WB, kp->cnt);
+  FinishOp op;
+  team_tasks(t, kp, op);
+  const int64_t I = t.sum(op.s).a;
+  int64_t sq = 0;
+  team_each(t, kp, kp->n, [&](KP kp, int c) __attribute__((always_inline)) { const int64_t w = ald(kp->WB + c); sq += w * w; });
+  sq = t.sum(sq).a;
+  if (t.rank == 0 && team_tx() == 0) { kp->out->obj_I = I; kp->out->obj_SW2 = sq; }
+}
+
+// The checks of a row's entries and the vertex's weight; the symmetry by search (lm.hip, EdgeCheck).
+struct CheckOp {
+  int64_t balance = 0, we = 0, sw = 0, sw2 = 0;
+  uint32_t err = 0;
+  // entries x, x + S, ...; returns their weight
+  __device__ __forceinline__ int64_t part(KP kp, const TeamRow& r, int x, int S) {
+    int64_t ws = 0;
+    const int32_t n = kp->n, v = r.v;
+    const bool search = kp->search;
+    for (int j = r.b + x; j < r.b + r.d; j += S) {
+      const int32_t u = kp->idx[j], w = kp->ones ? 1 : kp->w[j];
+      if (kp->ones) kp->w[j] = 1;
+      ws += w;
+      if (u < 0 || u >= n) { err |= ERRB_INVALID; continue; }
+      if (u == v) { err |= ERRB_SELF_LOOP; continue; }
+      if (j > r.b && kp->idx[j - 1] >= u) err |= ERRB_UNSORTED;
+      if (w <= 0) err |= ERRB_WEIGHT;
+      if (!search) continue;
+      int lo = (int)ald(kp->off + u);
+      const int end = (int)ald(kp->off + u + 1), du = end - lo;
+      if (du < r.d || (du == r.d && u < v)) {
+        ++balance;
+        int hi = end;
+        while (lo < hi) {  // first position holding an id >= v
+          const int mid = lo + ((hi - lo) >> 1);
+          if (kp->idx[mid] < v) lo = mid + 1; else hi = mid;
+        }
+        if (!(lo < end && kp->idx[lo] == v && (kp->ones || kp->w[lo] == w))) err |= ERRB_NOT_SYMMETRIC;
+      } else {
+        --balance;
+      }
+    }
+    return ws;
+  }
+  __device__ __forceinline__ void finish(KP kp, int32_t v, int64_t ws) {
+    int64_t x = ws;
+    if (kp->vw_mode == 2) x = 1;
+    else if (kp->vw_mode != 1) {
+      x = kp->vw_given[v];
+      if (x < 0) err |= ERRB_WEIGHT;
+      if (x >= ((int64_t)1 << 31)) err |= ERRB_VW_TOO_BIG;
+    }
+    kp->vw[v] = x;
+    we += ws;
+    sw += x;
+    sw2 = (int64_t)((uint64_t)sw2 + (uint64_t)x * (uint64_t)x);
+    if (kp->init) {
+      const int32_t c = kp->init[v];
+      if (c < 0 || c >= kp->n) err |= ERRB_INVALID;
+    }
+  }
+  template <int G>
+  __device__ __forceinline__ void group(KP kp, const TeamRow& r, int gl) {
+    const int64_t ws = sum_steps<G>(part(kp, r, gl, G));
+    if (gl == 0) finish(kp, r.v, ws);
+  }
+  __device__ __forceinline__ void wave(KP kp, const TeamRow& r, int lane) {
+    if (r.d > TW_ROW) return;  // the workgroup
+    const int64_t ws = wave_sum64(part(kp, r, lane, WAVE));
+    if (lane == 0) finish(kp, r.v, ws);
+  }
+};
+
+// Setup (Sec. II): offsets, degree buckets, the checks of the entries, vertex weights and their sums.  Offsets that are
+// no row partition end it before a row is read.
+__global__ __launch_bounds__(TEAM_BLOCK) void k_team_setup(TeamArgs args) {
+  KP kp = (KP)__builtin_amdgcn_kernarg_segment_ptr();
+  Team t;
+  if (!t.join(kp->ctl, kp->next)) return;
+  for (int k = team_tx(); t.rank == 0 && k < (int)(sizeof(TeamOut) / 8); k += TEAM_BLOCK) ast((int64_t*)kp->out + k, (int64_t)0);
+  int bad = 0;
+  team_each(t, kp, kp->n, [&](KP kp, int v) __attribute__((always_inline)) {
+    const int64_t a = kp->off32 ? (int64_t)kp->off32[v] : kp->off[v], b = kp->off32 ? (int64_t)kp->off32[v + 1] : kp->off[v + 1];
+    if (kp->off32) {
+      ast(kp->off + v, a);
+      if (v == kp->n - 1) ast(kp->off + v + 1, b);
+    }
+    bad += b < a || (v == 0 && a != 0) || (v == kp->n - 1 && b != kp->nnz);
+  });
+  if (t.sum(bad).a) {
+    if (t.rank == 0 && team_tx() == 0) kp->out->bad_offsets = 1;
+    return;
+  }
+  TEAM_PHASE(kp);
+  t.lists<NBUCKET>(kp->n, kp->st.off, kp->list, 0, [&](int v, int& cls, int& size) __attribute__((always_inline)) {
+    const int64_t d = ald(kp->off + v + 1) - ald(kp->off + v);
+    cls = 0;
+    for (int k = 0; k < NBUCKET - 1; ++k) cls += d > kp->bounds.max[k];
+  });
+  if (t.rank == 0 && team_tx() == 0)
+    for (int k = 0; k <= NBUCKET; ++k) kp->out->coarse_boff[k] = team_sh.first[k];
+  t.sync();
+  team_each(t, kp, kp->n, [](KP kp, int i) __attribute__((always_inline)) {
+    const int32_t v = ald(kp->list + i);
+    const int64_t b = ald(kp->off + v);
+    ast(kp->rows + i, row_word(v, (int)b, (int)(ald(kp->off + v + 1) - b)));
+  });
+  t.sync();
+  CheckOp op;
+  int boff[NBUCKET + 1];
+#pragma unroll
+  for (int k = 0; k <= NBUCKET; ++k) boff[k] = uniform32(team_sh.first[k]);
+  team_tasks_at(t, kp, op, boff[1], boff[2], boff[3], boff[4], boff[NBUCKET]);
+  team_long_at(t, kp, TW_ROW, boff[5], boff[NBUCKET], [&](const TeamRow& r) __attribute__((always_inline)) {
+    const int tx = team_tx(), lane = tx & (WAVE - 1);
+    int64_t ws = wave_sum64(op.part(kp, r, tx, TEAM_BLOCK));
+    __syncthreads();
+    if (lane == 0) team_best[tx / WAVE].own = ws;
+    __syncthreads();
+    if (tx == 0) {
+      for (int k = 1; k < TEAM_WAVES; ++k) ws += team_best[k].own;
+      op.finish(kp, r.v, ws);
+    }
+  });
+  if (op.err) atomicOr(&kp->out->err, op.err);
+  const Sum2 x = t.sum(op.balance, op.we);
+  const Sum2 y = t.sum(op.sw, op.sw2);
+  if (t.rank == 0 && team_tx() == 0) {
+    TeamOut* o = kp->out;
+    o->balance = x.a;
+    o->sum_we = x.b;
+    o->sum_w = y.a;
+    o->sum_w2 = y.b;
+  }
+}
+
 // One level: everything up to the point where the host has to decide or to allocate.
 __global__ __launch_bounds__(TEAM_BLOCK) void k_team_level(TeamArgs args) {
   KP kp = (KP)__builtin_amdgcn_kernarg_segment_ptr();
@@ -1660,6 +1833,9 @@ __global__ __launch_bounds__(TEAM_BLOCK) void k_team_level(TeamArgs args) {
   if (steps & TEAM_MOVE) {
     // C_out unchanged: the alternate local move
     if (!team_local_move(t, kp) && (steps & TEAM_ALTERNATE)) team_alternate(t, kp);
+  } else if (steps & TEAM_PROJECT) {
+    team_each(t, kp, n, [](KP kp, int v) __attribute__((always_inline)) { ast(kp->Cout + v, kp->up_C[kp->map[v]]); });
+    t.sync();
   }
   int nc = team_rank(t, kp, kp->Cout, kp->rank);
   if (t.rank == 0 && team_tx() == 0) kp->slot->nlab = kp->out->nlab = nc;
@@ -1673,16 +1849,26 @@ __global__ __launch_bounds__(TEAM_BLOCK) void k_team_level(TeamArgs args) {
   if (on) {
     team_contract(t, kp, nc);
   }
+  if (steps & TEAM_FINISH) team_finish_call(t, kp);
 }
 
 }  // namespace
 
 // --- host launchers
 
-void team_launch(TeamArgs& a, TeamHost& h, hipStream_t st) {
+static void team_blocks(TeamArgs& a, TeamHost& h) {
   a.ctl = h.ctl + h.turn % TEAM_SLOTS;
   a.next = h.ctl + (h.turn + 1) % TEAM_SLOTS;
   ++h.turn;
+}
+
+void team_setup_launch(TeamArgs& a, TeamHost& h, hipStream_t st) {
+  team_blocks(a, h);
+  k_team_setup<<<TEAM_GRID, TEAM_BLOCK, 0, st>>>(a);
+}
+
+void team_launch(TeamArgs& a, TeamHost& h, hipStream_t st) {
+  team_blocks(a, h);
   k_team_level<<<TEAM_GRID, TEAM_BLOCK, 0, st>>>(a);
 }
 

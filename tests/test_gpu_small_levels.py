@@ -107,3 +107,53 @@ def test_team_constrained_equals_launches(name):
     assert np.array_equal(a.trace, b.trace)
     buckets.close()
     team.close()
+
+
+def _set(a, i, v):
+    a[i] = v
+
+
+# (what, change of offsets, indices and weights): the smallest input for every check of the setup
+FAULTS = [
+    ("none", lambda o, i, w: None),
+    ("descending offsets", lambda o, i, w: _set(o, 5, o[6] + 1)),
+    ("first offset", lambda o, i, w: _set(o, 0, 1)),
+    ("last offset", lambda o, i, w: _set(o, -1, o[-1] + 2)),
+    ("index n", lambda o, i, w: _set(i, 9, len(o) - 1)),
+    ("index -1", lambda o, i, w: _set(i, 0, -1)),
+    ("self loop", lambda o, i, w: _set(i, o[3], 3)),
+    ("unsorted", lambda o, i, w: _set(i, slice(o[4], o[4] + 2), i[o[4]:o[4] + 2][::-1].copy())),
+    ("zero weight", lambda o, i, w: _set(w, 3, 0)),
+    ("one-sided weight", lambda o, i, w: _set(w, 3, w[3] + 1)),
+]
+
+
+@pytest.mark.parametrize("what,change", FAULTS, ids=[f[0] for f in FAULTS])
+@pytest.mark.parametrize("offsets32", [False, True])
+def test_team_setup_equals_launches(what, change, offsets32):
+    import torch
+    import paper_2608_01503_amd as L
+    g = gg.random_gnp(300, 0.03, 100, w_max=5)
+    off, idx, w = g.off.copy(), g.idx.copy(), g.w.copy()
+    change(off, idx, w)
+    h = gg.Graph(n=g.n, off=off, idx=idx, w=w)
+    buckets = L.Context(0)
+    buckets.profile_enable(["single"])
+    team = L.Context(0)
+    for lam, mode, kw in [(*MOD, {}), (*CPM, {}), (*CPM, dict(validate=0)), ((1, 3, False), O.VW_UNIT, dict(no_w=True))]:
+        kw = dict(kw)
+        with_w = not kw.pop("no_w", False)
+        if "validate" in kw and what not in ("none", "index n", "index -1", "first offset"):
+            continue  # without the checks only structural faults are the library's to find
+        dev = U.device_graph(h, mode, offsets32=offsets32, with_w=with_w)
+        got = []
+        for c in (buckets, team):
+            for init in (None, torch.full((g.n,), g.n, dtype=torch.int32, device="cuda:0")):
+                try:
+                    lab, r = c.cluster(dev, lam, O.PLOUVAIN, L.lcc_default_options(**kw), init=init)
+                    got.append((lab.cpu().numpy().tolist(), r.N, r.num_clusters, r.levels, r.flags))
+                except L.LccError as e:
+                    got.append(str(e))
+        assert got[:2] == got[2:], (what, lam, kw)
+    buckets.close()
+    team.close()
