@@ -845,16 +845,6 @@ __device__ __forceinline__ void ab_grp_blocks(const int32_t* list, int64_t cnt, 
   }
 }
 
-template <int G>
-__global__ __launch_bounds__(BLOCK) void k_ab_grp(const int32_t* list, int64_t cnt, DevGraph g, const VState* vs,
-                                                  ScoreSrc ss, uint8_t* keep, LMSlot* slot, int pass,
-                                                  int64_t* S) {
-  VtxAcc va;
-  if (slot->skip[pass]) return;
-  ab_grp_blocks<G>(list, cnt, blockIdx.x, gridDim.x, g, vs, ss, keep, va);
-  acc_flush<BLOCK>(va, S, CT_NM, -1);
-}
-
 // buckets 0-2 in one launch, as for the enumeration
 __global__ __launch_bounds__(BLOCK) void k_ab_grps(GrpSet q, DevGraph g, const VState* vs, ScoreSrc ss, uint8_t* keep,
                                                    LMSlot* slot, int pass, int64_t* S) {
@@ -868,28 +858,44 @@ __global__ __launch_bounds__(BLOCK) void k_ab_grps(GrpSet q, DevGraph g, const V
   acc_flush<BLOCK>(va, S, CT_NM, -1);
 }
 
-template <int BS>
-__global__ __launch_bounds__(BS) void k_ab_blk(const int32_t* list, int64_t cnt, DevGraph g, const VState* vs,
-                                               ScoreSrc ss, uint8_t* keep, LMSlot* slot, int pass,
-                                               int64_t* S) {
+// Rows of 17 to 8192 entries in one launch, the longest first: a workgroup per row of bucket 6, a wavefront per row of
+// bucket 5, half a wavefront per row of buckets 3 and 4 (a pass of U = 4 loads covers 128 entries).  Bound by the
+// gathers of the neighbours' states; as four launches, one after the other, most of a launch on a middle-sized level
+// was its start and its tail: on an R-MAT graph of 2^18 vertices a whole pLeiden
+// call went from 165 to 161 ms by it, a Louvain+ call on one of 500,000 from 12.1 to 11.5 ms.
+struct AbSet {
+  const int32_t* list[3];
+  int64_t cnt[3];
+  unsigned nb[3];  // workgroups of each kind
+};
+__global__ __launch_bounds__(BLOCK) void k_ab_rows(AbSet q, DevGraph g, const VState* vs, ScoreSrc ss, uint8_t* keep,
+                                                   LMSlot* slot, int pass, int64_t* S) {
+  static_assert(BLOCK == BIG_BLOCK, "one workgroup size");
   VtxAcc va;
   if (slot->skip[pass]) return;
-  for (int64_t vi = blockIdx.x; vi < cnt; vi += gridDim.x) {
-    const int32_t v = list[vi];
-    const VState me = vs[v];
-    if (me.d == D_NONE) {  // uniform over the block
-      if (threadIdx.x == 0) keep[v] = 0;
-      continue;
+  unsigned bid = blockIdx.x;  // the branches are uniform over the workgroup
+  if (bid < q.nb[0]) {
+    for (int64_t vi = bid; vi < q.cnt[0]; vi += q.nb[0]) {
+      const int32_t v = q.list[0][vi];
+      const VState me = vs[v];
+      if (me.d == D_NONE) {  // uniform over the block
+        if (threadIdx.x == 0) keep[v] = 0;
+        continue;
+      }
+      int64_t acc = ab_row(g, vs, ss.at(v), ss.base(v), g.off[v], g.off[v + 1], threadIdx.x, BLOCK, v, me, g.vw[v]);
+      acc = sum_reduce<BLOCK>(acc);
+      if (threadIdx.x == 0) {
+        bool k = (__int128)me.delta + acc >= 0;
+        keep[v] = k;
+        if (k) va.ncand += 1;
+      }
     }
-    int64_t acc = ab_row(g, vs, ss.at(v), ss.base(v), g.off[v], g.off[v + 1], threadIdx.x, BS, v, me, g.vw[v]);
-    acc = sum_reduce<BS>(acc);
-    if (threadIdx.x == 0) {
-      bool k = (__int128)me.delta + acc >= 0;
-      keep[v] = k;
-      if (k) va.ncand += 1;
-    }
+  } else if ((bid -= q.nb[0]) < q.nb[1]) {
+    ab_grp_blocks<64>(q.list[1], q.cnt[1], bid, q.nb[1], g, vs, ss, keep, va);
+  } else {
+    ab_grp_blocks<32>(q.list[2], q.cnt[2], bid - q.nb[1], q.nb[2], g, vs, ss, keep, va);
   }
-  acc_flush<BS>(va, S, CT_NM, -1);
+  acc_flush<BLOCK>(va, S, CT_NM, -1);
 }
 
 __global__ __launch_bounds__(HUB_BLOCK) void k_ab_hub(const int32_t* hubs, const int32_t* chunk_off, int64_t n7,
@@ -1020,8 +1026,9 @@ struct AggList {
 // slot->n_empty becomes nonzero when some kept move goes to a new singleton.
 __global__ __launch_bounds__(BLOCK) void k_apply(int64_t n, const uint8_t* keep, const VState* vs,
                                                  const int64_t* vw, int32_t* C, int64_t* W, uint8_t* empty,
-                                                 LMSlot* slot, int pass, int64_t* S, int track_sq) {
+                                                 LMSlot* slot, int pass, int64_t* S, int track_sq, int32_t* Cout) {
   if (slot && slot->skip[pass]) return;
+  const bool copy = Cout && slot->copy;  // C_out follows the state the pass started from
   uint64_t dsq = 0;  // modulo 2^64 (see AggList::flush)
   __shared__ int32_t ak[AGG_SLOTS];
   __shared__ unsigned long long av[AGG_SLOTS];
@@ -1057,6 +1064,7 @@ __global__ __launch_bounds__(BLOCK) void k_apply(int64_t n, const uint8_t* keep,
       claims += agg.add(kp[k], sv[k].c, -wv[k]);
       claims += agg.add(mv, sv[k].d, wv[k]);
       if (v < n) {
+        if (copy) Cout[v] = C[v];
         if (mv) C[v] = sv[k].d;
         if (kp[k] && !mv) atomicAdd(&ne, 1ull);
         empty[v] = (uint8_t)(kp[k] && !mv);
@@ -1974,11 +1982,15 @@ static void launch_afterburner(const DevGraph& g, const Buckets& b, const ScoreS
     }
     if (nb) k_ab_grps<<<nb, BLOCK, 0, st>>>(q, g, vs, sc, keep, slot, pass, b.stripes);
   }
-  if (b.count[3]) k_ab_grp<32><<<grp_blocks(b, b.count[3], 32), BLOCK, 0, st>>>(L + b.off[3], b.count[3], g, vs, sc, keep, slot, pass, b.stripes);
-  // degree 33-128 rows in half-wavefront groups (one pass of U = 4 loads covers them), longer ones per wavefront
-  if (b.count[4]) k_ab_grp<32><<<grp_blocks(b, b.count[4], 32), BLOCK, 0, st>>>(L + b.off[4], b.count[4], g, vs, sc, keep, slot, pass, b.stripes);
-  if (b.count[5]) k_ab_grp<64><<<grp_blocks(b, b.count[5], 64), BLOCK, 0, st>>>(L + b.off[5], b.count[5], g, vs, sc, keep, slot, pass, b.stripes);
-  if (b.count[6]) k_ab_blk<BIG_BLOCK><<<vtx_blocks(b, b.count[6]), BIG_BLOCK, 0, st>>>(L + b.off[6], b.count[6], g, vs, sc, keep, slot, pass, b.stripes);
+  {
+    AbSet q{};
+    const int64_t n34 = b.count[3] + b.count[4];  // adjacent in the list
+    q.list[0] = L + b.off[6]; q.cnt[0] = b.count[6]; q.nb[0] = b.count[6] ? vtx_blocks(b, b.count[6]) : 0;
+    q.list[1] = L + b.off[5]; q.cnt[1] = b.count[5]; q.nb[1] = b.count[5] ? grp_blocks(b, b.count[5], 64) : 0;
+    q.list[2] = L + b.off[3]; q.cnt[2] = n34; q.nb[2] = n34 ? grp_blocks(b, n34, 32) : 0;
+    const unsigned nb = q.nb[0] + q.nb[1] + q.nb[2];
+    if (nb) k_ab_rows<<<nb, BLOCK, 0, st>>>(q, g, vs, sc, keep, slot, pass, b.stripes);
+  }
   if (b.count[7]) {
     const int32_t* hubs = L + b.off[7];
     k_ab_hub<<<(unsigned)b.hub_chunks, HUB_BLOCK, 0, st>>>(hubs, b.hub_chunk_off, b.count[7], g, vs, sc, hs.hacc, slot, pass);
@@ -1989,12 +2001,13 @@ static void launch_afterburner(const DevGraph& g, const Buckets& b, const ScoreS
 // track_sq: keep slot->SW2[pass] (set to the previous state's value by k_pass_begin) up to date from the
 // moves instead of recomputing it from all cluster weights
 static void apply_and_empty(const DevGraph& g, const Buckets& b, LMBuffers& bufs, const SegLM& sg, LMSlot* slot,
-                            int pass, bool track_sq, hipStream_t st, FoldDst* pending = nullptr) {
+                            int pass, bool track_sq, hipStream_t st, FoldDst* pending = nullptr,
+                            int32_t* Cout = nullptr) {
   const int64_t n = g.n;
   int64_t* sq = track_sq ? &slot->SW2[pass] : nullptr;
   unsigned ga = (unsigned)std::max<int64_t>(1, std::min<int64_t>(cdiv(n, APPLY_TILE), AGG_BLOCKS));
   k_apply<<<ga, BLOCK, 0, st>>>(n, bufs.keep, bufs.vs, g.vw, bufs.C, bufs.W, bufs.empty, slot, pass, b.stripes,
-                                track_sq ? 1 : 0);
+                                track_sq ? 1 : 0, Cout);
   // the kept moves (afterburner or keep rule) and the sum-of-squares change
   fold(b.stripes, {{CT_NM, slot ? &slot->nM[pass] : nullptr}, {CT_SQ, sq}}, st, pending);
   // free ids and ranks of the movers to a new singleton; all no-ops unless some vertex moved to a new
@@ -2030,9 +2043,10 @@ static void state_sums_sw2(const SegLM& sg, const int64_t* W, int64_t n, LMSlot*
   }
 }
 
-// pend: counters still in the stripes that this check's sums need (folded here, then cleared)
+// pend: counters still in the stripes that this check's sums need (folded here, then cleared).  The copy to C_out of a
+// single graph's state before a pass is k_apply's (`copy` false here).
 static void best_so_far(const SegLM& sg, LMSlot* slot, const LMParams& prm, LMBuffers& bufs, int64_t n, int k,
-                        int skipk, hipStream_t st, int64_t* S, FoldDst& pend) {
+                        int skipk, hipStream_t st, int64_t* S, FoldDst& pend, bool copy) {
   if (sg.G) {
     bool any = false;
     for (int ct = 0; ct < CT_COUNT; ++ct) any = any || pend.d[ct];
@@ -2043,7 +2057,7 @@ static void best_so_far(const SegLM& sg, LMSlot* slot, const LMParams& prm, LMBu
   } else {
     k_best<<<1, 1024, 0, st>>>(slot, k, skipk, prm.sc.p, prm.sc.q, prm.sum_w2, S, pend);
     pend = FoldDst{};
-    if (k > 0) k_copy_if<<<grid_for(n), BLOCK, 0, st>>>(slot, bufs.C, bufs.Cout, n);
+    if (copy && k > 0) k_copy_if<<<grid_for(n), BLOCK, 0, st>>>(slot, bufs.C, bufs.Cout, n);
   }
 }
 
@@ -2091,7 +2105,7 @@ void local_move(const DevGraph& g, const Buckets& b, const LMParams& prm, bool s
       k_seg_sum<<<seg_blocks(G), BLOCK, 0, st>>>(sg.ownv, 0, sg.vbase, G, sg.I + (int64_t)(i - 1) * G,
                                                 i >= 2 ? sg.I + (int64_t)(i - 2) * G : nullptr, slot, i);
     // best-so-far check of the state this pass started from (state i-1)
-    best_so_far(sg, slot, prm, bufs, n, i - 1, i, st, S, pend);
+    best_so_far(sg, slot, prm, bufs, n, i - 1, i, st, S, pend, false);
     if (prm.symmetry == 0) {
       launch_afterburner(g, b, sc, bufs, slot, i, hs, st);
     } else {
@@ -2099,7 +2113,7 @@ void local_move(const DevGraph& g, const Buckets& b, const LMParams& prm, bool s
       k_keep_rule<<<red_blocks(nl), BLOCK, 0, st>>>(b.list, nl, bufs.vs, prm.symmetry, i, bufs.keep, slot,
                                                     b.stripes);
     }
-    apply_and_empty(g, b, bufs, sg, slot, i, G == 0, st, pp);
+    apply_and_empty(g, b, bufs, sg, slot, i, G == 0, st, pp, G == 0 && i > 1 ? bufs.Cout : nullptr);
     state_sums_sw2(sg, bufs.W, n, slot, i, i, st);
   }
   const int last = prm.pass_limit;
@@ -2113,9 +2127,9 @@ void local_move(const DevGraph& g, const Buckets& b, const LMParams& prm, bool s
     } else {
       launch_internal(g, b, bufs.C, &slot->I[last], &slot->skip[last], st, nullptr, &pend);
     }
-    best_so_far(sg, slot, prm, bufs, n, last, last, st, S, pend);
+    best_so_far(sg, slot, prm, bufs, n, last, last, st, S, pend, true);
   } else {
-    best_so_far(sg, slot, prm, bufs, n, 0, -1, st, S, pend);
+    best_so_far(sg, slot, prm, bufs, n, 0, -1, st, S, pend, true);
   }
 }
 
