@@ -2,6 +2,7 @@
 // LSD radix sort of (uint64 key, uint32 value) pairs with 8-bit digits (per-tile histograms, a scan of the
 // digit-major histogram, and a stable scatter whose in-tile ranks come from wavefront ballots).
 #include "common.h"
+#include "radix.h"
 
 namespace lcc {
 
@@ -9,7 +10,7 @@ namespace {
 
 constexpr int SCAN_ITEMS = 8;
 constexpr int SCAN_TILE = BLOCK * SCAN_ITEMS;  // 2048
-constexpr int RADIX_TILE = 4096;               // 16 rounds of 256 items
+constexpr int RADIX_TILE = RX_TILE;
 
 __host__ __device__ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -162,80 +163,19 @@ __global__ __launch_bounds__(BLOCK) void k_radix_hist(const uint64_t* keys, int6
   hist[(int64_t)threadIdx.x * ntiles + blockIdx.x] = cnt[threadIdx.x];
 }
 
-// Stable scatter.  Items of a tile are taken in rounds of 256 (one per thread, in index order); within a
-// round, a lane's rank among same-digit items is the number of lower lanes of its wavefront with the same
-// digit (ballot match over the 8 digit bits) plus the counts of the earlier wavefronts of the round.  Each
-// item first goes to its place in the tile sorted by digit, in LDS; the sorted tile is then written out with
-// consecutive threads on consecutive positions of each digit's run, so the stores coalesce instead of
-// scattering every round's items over 256 digit runs.
+// Stable scatter of a tile per workgroup.
 __global__ __launch_bounds__(BLOCK) void k_radix_scatter(const uint64_t* kin, const uint32_t* vin, int64_t m,
-                                                         int shift, const uint32_t* hist, const uint32_t* offs,
-                                                         int64_t ntiles, uint64_t* kout, uint32_t* vout) {
-  __shared__ uint64_t tk[RADIX_TILE];
-  __shared__ uint32_t tv[RADIX_TILE];
-  __shared__ uint32_t lbase[256];  // first position of each digit in the sorted tile
-  __shared__ uint32_t lrun[256];   // next free position of each digit in the sorted tile
-  __shared__ uint32_t gbase[256];  // first global position of this tile's items of each digit
-  __shared__ uint32_t wcnt[BLOCK / WAVE][256];
-  const int tid = threadIdx.x, wv = tid / WAVE, lane = tid & (WAVE - 1);
+                                                         int shift, const uint32_t* offs, int64_t ntiles,
+                                                         uint64_t* kout, uint32_t* vout) {
+  __shared__ RadixLds l;
   const int64_t t0 = (int64_t)blockIdx.x * RADIX_TILE;
-  gbase[tid] = offs[(int64_t)tid * ntiles + blockIdx.x];
-  {  // the tile's digit counts (from the histogram pass), exclusive-scanned over the digits
-    uint32_t tot = 0;
-    const uint32_t c = hist[(int64_t)tid * ntiles + blockIdx.x];
-    const uint32_t ex = block_excl_scan<uint32_t>(c, &tot);
-    lbase[tid] = ex;
-    lrun[tid] = ex;
-  }
-  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (WAVE - lane));
-  const int items = (int)min<int64_t>(RADIX_TILE, m - t0);
-  for (int r = 0; r * BLOCK < items; ++r) {  // block-uniform
-#pragma unroll
-    for (int k = 0; k < BLOCK / WAVE; ++k) wcnt[k][tid] = 0;
-    __syncthreads();
-    const int li = r * BLOCK + tid;
-    const bool valid = li < items;
-    const uint64_t key = valid ? kin[t0 + li] : 0;
-    const uint32_t val = valid ? vin[t0 + li] : 0;
-    const uint32_t d = (uint32_t)(key >> shift) & 255u;
-    uint64_t mask = __ballot(valid);
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      uint64_t bal = __ballot((d >> b) & 1u);
-      mask &= ((d >> b) & 1u) ? bal : ~bal;
-    }
-    const uint32_t prank = (uint32_t)__popcll(mask & lt);
-    if (valid && prank == 0) wcnt[wv][d] = (uint32_t)__popcll(mask);
-    __syncthreads();
-    {
-      uint32_t run = lrun[tid];
-#pragma unroll
-      for (int k = 0; k < BLOCK / WAVE; ++k) {
-        uint32_t c = wcnt[k][tid];
-        wcnt[k][tid] = run;
-        run += c;
-      }
-      lrun[tid] = run;
-    }
-    __syncthreads();
-    if (valid) {
-      const uint32_t pos = wcnt[wv][d] + prank;
-      tk[pos] = key;
-      tv[pos] = val;
-    }
-    __syncthreads();  // every wavefront has read its offsets before the next round clears them
-  }
-  for (int p = tid; p < items; p += BLOCK) {
-    const uint64_t key = tk[p];
-    const uint32_t d = (uint32_t)(key >> shift) & 255u;
-    const uint32_t dst = gbase[d] + ((uint32_t)p - lbase[d]);
-    kout[dst] = key;
-    vout[dst] = tv[p];
-  }
+  radix_tile(l, (int)min<int64_t>(RADIX_TILE, m - t0), shift, offs[(int64_t)threadIdx.x * ntiles + blockIdx.x],
+             [&](int i, uint64_t& k, uint32_t& v) { k = kin[t0 + i]; v = vin[t0 + i]; },
+             [&](uint32_t at, uint64_t k, uint32_t v) { kout[at] = k; vout[at] = v; });
 }
 
 // Whole sort of at most RADIX_TILE pairs by one workgroup in LDS: every pass is a histogram, a scan of the 256
-// digit counts and the stable ballot-ranked scatter above, between two LDS buffers.  The result is written to
+// digit counts and the stable ballot-ranked scatter in rounds of 256 items, between two LDS buffers.  The result is written to
 // (k0, v0).
 struct RadixShifts {
   int s[8];
@@ -374,7 +314,7 @@ int radix_sort_pairs(uint64_t* k0, uint32_t* v0, uint64_t* k1, uint32_t* v1, int
   for (int p = 0; p < npass; ++p) {
     k_radix_hist<<<(unsigned)nt, BLOCK, 0, st>>>(ki, m, shifts[p], hist, nt);
     scan_impl<uint32_t, uint32_t>(hist, offs, 256 * nt, stemp, nullptr, st);
-    k_radix_scatter<<<(unsigned)nt, BLOCK, 0, st>>>(ki, vi, m, shifts[p], hist, offs, nt, ko, vo);
+    k_radix_scatter<<<(unsigned)nt, BLOCK, 0, st>>>(ki, vi, m, shifts[p], offs, nt, ko, vo);
     uint64_t* tk = ki; ki = ko; ko = tk;
     uint32_t* tv = vi; vi = vo; vo = tv;
   }

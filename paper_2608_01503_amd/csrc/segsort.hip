@@ -14,6 +14,7 @@
 #include <functional>
 
 #include "common.h"
+#include "radix.h"
 
 namespace lcc {
 
@@ -317,7 +318,7 @@ __global__ __launch_bounds__(BLOCK) void k_seg_bitonic(const int32_t* list, cons
 // tiles of every long segment keep per-tile digit counts laid out as (segment rank, digit, tile), so one
 // exclusive scan over them gives each item's position in the concatenation of the long segments, which maps
 // back into its own segment's range.
-constexpr int SR_TILE = 4096;
+constexpr int SR_TILE = RX_TILE;
 
 __global__ void k_seg_long_sizes(const int32_t* list, int64_t nlong, const int64_t* off, int64_t* size,
                                  int64_t* ntile) {
@@ -360,57 +361,18 @@ __global__ __launch_bounds__(BLOCK) void k_segradix_hist(const uint64_t* keys, c
   hist[256 * toff[lt.r] + (int64_t)threadIdx.x * lt.nt + lt.t] = cnt[threadIdx.x];
 }
 
-// Stable scatter of one tile: items in rounds of 256 in index order; a lane's rank among same-digit items of
-// its round is the count of lower lanes of its wavefront with the same digit (ballot match) plus the counts of
-// the earlier wavefronts.
+// Stable scatter of one tile.
 __global__ __launch_bounds__(BLOCK) void k_segradix_scatter(const uint64_t* kin, const uint32_t* vin,
                                                             const int64_t* off, const int32_t* list,
                                                             const int64_t* toff, const int64_t* loff, int64_t nlong,
                                                             int shift, const uint32_t* offs, uint64_t* kout,
                                                             uint32_t* vout) {
-  __shared__ uint32_t base[256];
-  __shared__ uint32_t wcnt[BLOCK / WAVE][256];
-  const int tid = threadIdx.x, wv = tid / WAVE, lane = tid & (WAVE - 1);
+  __shared__ RadixLds l;
   const LongTile lt = long_tile(blockIdx.x, toff, nlong, list, off);
-  base[tid] = offs[256 * toff[lt.r] + (int64_t)tid * lt.nt + lt.t];
   const int64_t to_array = off[list[lt.r]] - loff[lt.r];  // position in the concatenation -> in the array
-  const uint64_t lm = (lane == 0) ? 0ull : (~0ull >> (WAVE - lane));
-  for (int64_t r0 = lt.b; r0 < lt.e; r0 += BLOCK) {  // block-uniform
-#pragma unroll
-    for (int k = 0; k < BLOCK / WAVE; ++k) wcnt[k][tid] = 0;
-    __syncthreads();
-    const int64_t i = r0 + tid;
-    const bool valid = i < lt.e;
-    const uint64_t key = valid ? kin[i] : 0;
-    const uint32_t val = valid ? vin[i] : 0;
-    const uint32_t d = (uint32_t)(key >> shift) & 255u;
-    uint64_t mask = __ballot(valid);
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const uint64_t bal = __ballot((d >> b) & 1u);
-      mask &= ((d >> b) & 1u) ? bal : ~bal;
-    }
-    const uint32_t prank = (uint32_t)__popcll(mask & lm);
-    if (valid && prank == 0) wcnt[wv][d] = (uint32_t)__popcll(mask);
-    __syncthreads();
-    {
-      uint32_t run = base[tid];
-#pragma unroll
-      for (int k = 0; k < BLOCK / WAVE; ++k) {
-        const uint32_t c = wcnt[k][tid];
-        wcnt[k][tid] = run;
-        run += c;
-      }
-      base[tid] = run;
-    }
-    __syncthreads();
-    if (valid) {
-      const int64_t dst = to_array + (int64_t)(wcnt[wv][d] + prank);
-      kout[dst] = key;
-      vout[dst] = val;
-    }
-    __syncthreads();
-  }
+  radix_tile(l, (int)(lt.e - lt.b), shift, offs[256 * toff[lt.r] + (int64_t)threadIdx.x * lt.nt + lt.t],
+             [&](int i, uint64_t& k, uint32_t& v) { k = kin[lt.b + i]; v = vin[lt.b + i]; },
+             [&](uint32_t at, uint64_t k, uint32_t v) { kout[to_array + at] = k; vout[to_array + at] = v; });
 }
 
 __global__ __launch_bounds__(BLOCK) void k_seg_long_copy(const uint64_t* kin, const uint32_t* vin, const int64_t* off,

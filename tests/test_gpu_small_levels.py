@@ -157,3 +157,22 @@ def test_team_setup_equals_launches(what, change, offsets32):
         assert got[:2] == got[2:], (what, lam, kw)
     buckets.close()
     team.close()
+
+
+@pytest.mark.parametrize("n", [1023, 1024, 1025, 1088, 2047, 2048, 2049, 5000])
+def test_alternate_move_by_radix_sort_equals_team(n):
+    """Four records per mover around the sort's tiles of 4096: from one cluster each by label, nearly every vertex moves."""
+    import torch
+    import paper_2608_01503_amd as L
+    g = gg.random_gnp(n, 8.0 / n, 7, w_max=4)
+    buckets = L.Context(0)
+    buckets.profile_enable(["single"])
+    team = L.Context(0)
+    init = torch.from_numpy(np.random.default_rng(2).permutation(n).astype(np.int32)).cuda()
+    dev = U.device_graph(g, CPM[1])
+    (la, a), (lb, b) = [c.cluster(dev, CPM[0], O.PLEIDEN, L.lcc_default_options(pass_limit=0), trace_capacity=1 << 14, init=init)
+                        for c in (buckets, team)]
+    assert np.array_equal(la.cpu().numpy(), lb.cpu().numpy()) and (a.N, a.levels, a.flags) == (b.N, b.levels, b.flags)
+    assert np.array_equal(a.trace, b.trace) and (a.trace[:, 0] == 3).any()
+    buckets.close()
+    team.close()
