@@ -1026,9 +1026,10 @@ struct AggList {
 // slot->n_empty becomes nonzero when some kept move goes to a new singleton.
 __global__ __launch_bounds__(BLOCK) void k_apply(int64_t n, const uint8_t* keep, const VState* vs,
                                                  const int64_t* vw, int32_t* C, int64_t* W, uint8_t* empty,
-                                                 LMSlot* slot, int pass, int64_t* S, int track_sq, int32_t* Cout) {
+                                                 LMSlot* slot, int pass, int64_t* S, int track_sq, int32_t* Cout,
+                                                 const int32_t* gcopy, const int32_t* gid) {
   if (slot && slot->skip[pass]) return;
-  const bool copy = Cout && slot->copy;  // C_out follows the state the pass started from
+  const bool copy = Cout && (gcopy || slot->copy);  // C_out follows the state the pass started from
   uint64_t dsq = 0;  // modulo 2^64 (see AggList::flush)
   __shared__ int32_t ak[AGG_SLOTS];
   __shared__ unsigned long long av[AGG_SLOTS];
@@ -1064,7 +1065,7 @@ __global__ __launch_bounds__(BLOCK) void k_apply(int64_t n, const uint8_t* keep,
       claims += agg.add(kp[k], sv[k].c, -wv[k]);
       claims += agg.add(mv, sv[k].d, wv[k]);
       if (v < n) {
-        if (copy) Cout[v] = C[v];
+        if (copy && (!gcopy || gcopy[gid[v]])) Cout[v] = C[v];
         if (mv) C[v] = sv[k].d;
         if (kp[k] && !mv) atomicAdd(&ne, 1ull);
         empty[v] = (uint8_t)(kp[k] && !mv);
@@ -1264,7 +1265,8 @@ __global__ void k_zero_listed(const int32_t* list, int64_t cnt, int64_t* per_v, 
 
 // out[k] = sum of x[i] (square: x[i]^2) over i in [vbase[k], vbase[k+1]); one workgroup per graph.  When pass
 // `pass` repeats the previous one (slot->skip), the previous state's sums are copied from prev instead.
-__global__ __launch_bounds__(BLOCK) void k_seg_sum(const int64_t* x, int square, const int32_t* vbase, int64_t G,
+constexpr int SEG_SUM_BLOCK = 1024;  // one round of loads for most graphs of a union: 8.7 us a launch with 256 threads, now 4.3
+__global__ __launch_bounds__(SEG_SUM_BLOCK) void k_seg_sum(const int64_t* x, int square, const int32_t* vbase, int64_t G,
                                                    int64_t* out, const int64_t* prev, const LMSlot* slot,
                                                    int pass) {
   const bool skip = slot && pass >= 0 && slot->skip[pass];
@@ -1274,11 +1276,15 @@ __global__ __launch_bounds__(BLOCK) void k_seg_sum(const int64_t* x, int square,
       continue;
     }
     int64_t s = 0;
-    for (int64_t i = (int64_t)vbase[k] + threadIdx.x; i < vbase[k + 1]; i += BLOCK) {
-      int64_t v = x[i];
-      s += square ? v * v : v;
+    const int64_t e = vbase[k + 1];
+    for (int64_t i = (int64_t)vbase[k] + threadIdx.x; i < e; i += 4 * SEG_SUM_BLOCK) {
+      int64_t v[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = i + j * SEG_SUM_BLOCK < e ? x[i + j * SEG_SUM_BLOCK] : 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) s += square ? v[j] * v[j] : v[j];
     }
-    s = sum_reduce<BLOCK>(s);
+    s = sum_reduce<SEG_SUM_BLOCK>(s);
     if (threadIdx.x == 0) out[k] = s;
   }
 }
@@ -1853,7 +1859,7 @@ void launch_internal_per_vertex(const DevGraph& g, const Buckets& b, const int32
 static unsigned seg_blocks(int64_t G) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(G, 4096)); }
 
 void launch_seg_sum(const int64_t* x, int square, const int32_t* vbase, int64_t G, int64_t* out, hipStream_t st) {
-  if (G > 0) k_seg_sum<<<seg_blocks(G), BLOCK, 0, st>>>(x, square, vbase, G, out, nullptr, nullptr, -1);
+  if (G > 0) k_seg_sum<<<seg_blocks(G), SEG_SUM_BLOCK, 0, st>>>(x, square, vbase, G, out, nullptr, nullptr, -1);
 }
 
 void launch_objective(const DevGraph& g, const Buckets& b, const int32_t* C, const int64_t* W, Ctrl* ctrl,
@@ -2007,7 +2013,7 @@ static void apply_and_empty(const DevGraph& g, const Buckets& b, LMBuffers& bufs
   int64_t* sq = track_sq ? &slot->SW2[pass] : nullptr;
   unsigned ga = (unsigned)std::max<int64_t>(1, std::min<int64_t>(cdiv(n, APPLY_TILE), AGG_BLOCKS));
   k_apply<<<ga, BLOCK, 0, st>>>(n, bufs.keep, bufs.vs, g.vw, bufs.C, bufs.W, bufs.empty, slot, pass, b.stripes,
-                                track_sq ? 1 : 0, Cout);
+                                track_sq ? 1 : 0, Cout, sg.G ? sg.copy : nullptr, sg.gid);
   // the kept moves (afterburner or keep rule) and the sum-of-squares change
   fold(b.stripes, {{CT_NM, slot ? &slot->nM[pass] : nullptr}, {CT_SQ, sq}}, st, pending);
   // free ids and ranks of the movers to a new singleton; all no-ops unless some vertex moved to a new
@@ -2036,24 +2042,20 @@ static void state_sums_sw2(const SegLM& sg, const int64_t* W, int64_t n, LMSlot*
                            hipStream_t st) {
   if (sg.G) {
     const int64_t G = sg.G;
-    k_seg_sum<<<seg_blocks(G), BLOCK, 0, st>>>(W, 1, sg.vbase, G, sg.SW2 + (int64_t)k * G,
+    k_seg_sum<<<seg_blocks(G), SEG_SUM_BLOCK, 0, st>>>(W, 1, sg.vbase, G, sg.SW2 + (int64_t)k * G,
                                               k ? sg.SW2 + (int64_t)(k - 1) * G : nullptr, pass >= 0 ? slot : nullptr, pass);
   } else if (pass < 0) {  // the starting state; later states follow from the moves (apply_and_empty)
     k_sw2<<<red_blocks(n), BLOCK, 0, st>>>(W, n, &slot->SW2[k], nullptr, pass);
   }
 }
 
-// pend: counters still in the stripes that this check's sums need (folded here, then cleared).  The copy to C_out of a
-// single graph's state before a pass is k_apply's (`copy` false here).
+// pend: counters still in the stripes that a single graph's check needs (folded here, then cleared).  The copy to C_out
+// of the state before a pass is k_apply's (`copy` false here).
 static void best_so_far(const SegLM& sg, LMSlot* slot, const LMParams& prm, LMBuffers& bufs, int64_t n, int k,
                         int skipk, hipStream_t st, int64_t* S, FoldDst& pend, bool copy) {
   if (sg.G) {
-    bool any = false;
-    for (int ct = 0; ct < CT_COUNT; ++ct) any = any || pend.d[ct];
-    if (any) k_fold<<<1, 1024, 0, st>>>(S, pend);
-    pend = FoldDst{};
     k_best_seg<<<grid_for(sg.G), BLOCK, 0, st>>>(sg, slot, k, skipk);
-    if (k > 0) k_copy_if_seg<<<grid_for(n), BLOCK, 0, st>>>(sg.copy, sg.gid, bufs.C, bufs.Cout, n);
+    if (copy && k > 0) k_copy_if_seg<<<grid_for(n), BLOCK, 0, st>>>(sg.copy, sg.gid, bufs.C, bufs.Cout, n);
   } else {
     k_best<<<1, 1024, 0, st>>>(slot, k, skipk, prm.sc.p, prm.sc.q, prm.sum_w2, S, pend);
     pend = FoldDst{};
@@ -2086,11 +2088,11 @@ void local_move(const DevGraph& g, const Buckets& b, const LMParams& prm, bool s
     fill_i64(sg.ownv, 0, n, st);
   }
   state_sums_sw2(sg, bufs.W, n, slot, 0, -1, st);
-  // Counters the kernels leave in the stripes are folded by the next bookkeeping kernel of a single graph
-  // (no launch of their own); a union folds them at once.
+  // Counters the kernels leave in the stripes are folded by the next bookkeeping kernel (no launch of their own); a
+  // union's checks need none of them, so they wait for the next pass's.
   int64_t* S = b.stripes;
   FoldDst pend{};
-  FoldDst* pp = G ? nullptr : &pend;
+  FoldDst* pp = &pend;
   for (int i = 1; i <= prm.pass_limit; ++i) {
     // a pass that kept no move repeats exactly when the next one has the same temperature (and, under the
     // minimum label heuristic, never: its rule alternates between passes)
@@ -2102,7 +2104,7 @@ void local_move(const DevGraph& g, const Buckets& b, const LMParams& prm, bool s
     launch_destinations(g, b, sc, prm.phi_num[i], prm.phi_den[i], 0, single_now, bufs, slot, i,
                         &slot->I[i - 1], hs, st, pp);
     if (G)  // internal weight of state i-1 per graph, from the own-cluster weights the pass just summed
-      k_seg_sum<<<seg_blocks(G), BLOCK, 0, st>>>(sg.ownv, 0, sg.vbase, G, sg.I + (int64_t)(i - 1) * G,
+      k_seg_sum<<<seg_blocks(G), SEG_SUM_BLOCK, 0, st>>>(sg.ownv, 0, sg.vbase, G, sg.I + (int64_t)(i - 1) * G,
                                                 i >= 2 ? sg.I + (int64_t)(i - 2) * G : nullptr, slot, i);
     // best-so-far check of the state this pass started from (state i-1)
     best_so_far(sg, slot, prm, bufs, n, i - 1, i, st, S, pend, false);
@@ -2113,7 +2115,7 @@ void local_move(const DevGraph& g, const Buckets& b, const LMParams& prm, bool s
       k_keep_rule<<<red_blocks(nl), BLOCK, 0, st>>>(b.list, nl, bufs.vs, prm.symmetry, i, bufs.keep, slot,
                                                     b.stripes);
     }
-    apply_and_empty(g, b, bufs, sg, slot, i, G == 0, st, pp, G == 0 && i > 1 ? bufs.Cout : nullptr);
+    apply_and_empty(g, b, bufs, sg, slot, i, G == 0, st, pp, i > 1 ? bufs.Cout : nullptr);
     state_sums_sw2(sg, bufs.W, n, slot, i, i, st);
   }
   const int last = prm.pass_limit;
@@ -2122,7 +2124,7 @@ void local_move(const DevGraph& g, const Buckets& b, const LMParams& prm, bool s
     pend = FoldDst{};
     if (G) {
       launch_internal(g, b, bufs.C, nullptr, &slot->skip[last], st, sg.ownv);
-      k_seg_sum<<<seg_blocks(G), BLOCK, 0, st>>>(sg.ownv, 0, sg.vbase, G, sg.I + (int64_t)last * G,
+      k_seg_sum<<<seg_blocks(G), SEG_SUM_BLOCK, 0, st>>>(sg.ownv, 0, sg.vbase, G, sg.I + (int64_t)last * G,
                                                 sg.I + (int64_t)(last - 1) * G, slot, last);
     } else {
       launch_internal(g, b, bufs.C, &slot->I[last], &slot->skip[last], st, nullptr, &pend);
