@@ -2,6 +2,8 @@
 // launchers each translation unit exports to the driver.  Not part of the public C-ABI (include/lcc.h).
 #pragma once
 
+#include <type_traits>
+
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -166,6 +168,48 @@ struct Buckets {
   int64_t* hub_acc = nullptr;
   int64_t* stripes = nullptr;  // NSTRIPE * STRIPE_W counter partials, all zero between folds
 };
+
+// Rows by the lanes that take them, for kernels that cover all of them in one launch: kind 0 a wavefront per row (buckets
+// `wave` to `last`), kinds 1 to 4 groups of 32, 16, 8 and 4 lanes (buckets 3 up to `wave`, 2, 1 and 0).  The workgroups are split into ranges,
+// one per kind, the longest rows first: the kinds run side by side instead of one launch after another, each with its
+// own start and tail.
+struct RowSet {
+  const int32_t* list[5];
+  int64_t cnt[5];
+  unsigned nb[5];
+};
+inline RowSet row_set(const Buckets& b, int last, unsigned* blocks, int wave = 4) {
+  RowSet q{};
+  *blocks = 0;
+  for (int k = 0; k < 5; ++k) {
+    const int lo = k ? 4 - k : wave, hi = k == 0 ? last : k == 1 ? wave - 1 : lo, lanes = 64 >> k;
+    q.list[k] = b.list + b.off[lo];
+    q.cnt[k] = b.off[hi + 1] - b.off[lo];
+    const int64_t n = (q.cnt[k] + 256 / lanes - 1) / (256 / lanes);
+    q.nb[k] = (unsigned)(n < b.grid_cap ? n : b.grid_cap);
+    *blocks += q.nb[k];
+  }
+  return q;
+}
+// the kind of this workgroup; bid: its number among them
+__device__ __forceinline__ int row_kind(const RowSet& q, unsigned& bid) {
+  bid = blockIdx.x;
+  int k = 0;
+  while (k < 4 && bid >= q.nb[k]) bid -= q.nb[k++];
+  return k;
+}
+// f(lanes, list, count, workgroup, workgroups) for this workgroup's kind, lanes as a compile-time constant
+template <typename F>
+__device__ __forceinline__ void for_row_kind(const RowSet& q, F f) {
+  unsigned bid;
+  switch (row_kind(q, bid)) {  // uniform over the workgroup
+    case 0: f(std::integral_constant<int, 64>{}, q.list[0], q.cnt[0], bid, q.nb[0]); break;
+    case 1: f(std::integral_constant<int, 32>{}, q.list[1], q.cnt[1], bid, q.nb[1]); break;
+    case 2: f(std::integral_constant<int, 16>{}, q.list[2], q.cnt[2], bid, q.nb[2]); break;
+    case 3: f(std::integral_constant<int, 8>{}, q.list[3], q.cnt[3], bid, q.nb[3]); break;
+    default: f(std::integral_constant<int, 4>{}, q.list[4], q.cnt[4], bid, q.nb[4]); break;
+  }
+}
 
 // Scoring parameters of a level: lambda = p / q; phi = phi_a / phi_b; tie window threshold on |delta_u -
 // delta_v| (see lm.hip).

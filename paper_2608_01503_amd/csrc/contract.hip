@@ -22,12 +22,6 @@ inline unsigned grid_for(int64_t n) {
   if (g > 65536) g = 65536;
   return (unsigned)g;
 }
-// persistent launches (at most 2048 workgroups looping over their share of the vertices)
-inline unsigned grp_blocks(const Buckets& bk, int64_t cnt, int G) {
-  int64_t b = cdiv(cnt, BLOCK / G);
-  return (unsigned)(b < 1 ? 1 : (b > bk.grid_cap ? bk.grid_cap : b));
-}
-
 __device__ __forceinline__ int find_chunk_owner(const int32_t* chunk_off, int64_t n7, int64_t blk) {
   int64_t lo = 0, hi = n7;
   while (hi - lo > 1) {
@@ -85,11 +79,11 @@ __global__ __launch_bounds__(BLOCK) void k_coarse_vw(const int32_t* map, const i
 // cross-cluster entries per fine vertex; G lanes per vertex (G = 64 also covers whole-block rows by
 // striding), hubs by chunks with atomics
 template <int G>
-__global__ __launch_bounds__(BLOCK) void k_cross_count_grp(const int32_t* list, int64_t cnt, DevGraph g,
-                                                           const int32_t* map, int32_t* out) {
+__device__ __forceinline__ void cross_count_rows(const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk, const DevGraph& g,
+                                                 const int32_t* map, int32_t* out) {
   const int gl = threadIdx.x % G;
-  for (int64_t gid = (int64_t)blockIdx.x * (BLOCK / G) + threadIdx.x / G; gid < cnt;
-       gid += (int64_t)gridDim.x * (BLOCK / G)) {
+  for (int64_t gid = (int64_t)bid * (BLOCK / G) + threadIdx.x / G; gid < cnt;
+       gid += (int64_t)nblk * (BLOCK / G)) {
     const int32_t v = list[gid];
     const int32_t x = map[v];
     int c = 0;
@@ -98,6 +92,11 @@ __global__ __launch_bounds__(BLOCK) void k_cross_count_grp(const int32_t* list, 
     for (int o = G / 2; o > 0; o >>= 1) c += __shfl_xor(c, o, G);
     if (gl == 0) out[v] = c;
   }
+}
+__global__ __launch_bounds__(BLOCK) void k_cross_count_rows(RowSet q, DevGraph g, const int32_t* map, int32_t* out) {
+  for_row_kind(q, [&](auto lanes, const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk) {
+    cross_count_rows<decltype(lanes)::value>(list, cnt, bid, nblk, g, map, out);
+  });
 }
 
 __global__ __launch_bounds__(HUB_BLOCK) void k_cross_count_chunk(const int32_t* hubs, const int32_t* chunk_off,
@@ -118,12 +117,11 @@ __global__ __launch_bounds__(HUB_BLOCK) void k_cross_count_chunk(const int32_t* 
 // Emit (x << 32 | y, w); positions claimed per group with one atomic on the vertex cursor (the cursor
 // starts at the vertex's exclusive prefix of cross entries).
 template <int G>
-__global__ __launch_bounds__(BLOCK) void k_cross_emit_grp(const int32_t* list, int64_t cnt, DevGraph g,
-                                                          const int32_t* map, int64_t* cursor, uint64_t* keys,
-                                                          uint32_t* vals) {
+__device__ __forceinline__ void cross_emit_rows(const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk, const DevGraph& g,
+                                                const int32_t* map, int64_t* cursor, uint64_t* keys, uint32_t* vals) {
   const int gl = threadIdx.x % G;
   // the loop bound is the same for every lane of the workgroup: the ballots below see whole wavefronts
-  for (int64_t gb0 = (int64_t)blockIdx.x * (BLOCK / G); gb0 < cnt; gb0 += (int64_t)gridDim.x * (BLOCK / G)) {
+  for (int64_t gb0 = (int64_t)bid * (BLOCK / G); gb0 < cnt; gb0 += (int64_t)nblk * (BLOCK / G)) {
   const int64_t gid = gb0 + threadIdx.x / G;
   // groups past the end still execute the ballots (uniform control flow inside the wavefront)
   const bool active = gid < cnt;
@@ -157,6 +155,12 @@ __global__ __launch_bounds__(BLOCK) void k_cross_emit_grp(const int32_t* list, i
     }
   }
   }
+}
+__global__ __launch_bounds__(BLOCK) void k_cross_emit_rows(RowSet q, DevGraph g, const int32_t* map, int64_t* cursor, uint64_t* keys,
+                                                           uint32_t* vals) {
+  for_row_kind(q, [&](auto lanes, const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk) {
+    cross_emit_rows<decltype(lanes)::value>(list, cnt, bid, nblk, g, map, cursor, keys, vals);
+  });
 }
 
 // rows handled by whole workgroups (bucket 6) or hub chunks: each wavefront claims its own positions
@@ -299,12 +303,9 @@ void launch_coarse_vw(const int32_t* map, const int64_t* vw, int64_t n, int64_t*
 
 void launch_cross_count(const DevGraph& g, const Buckets& b, const int32_t* map, int32_t* cnt, hipStream_t st) {
   const int32_t* L = b.list;
-  if (b.count[0]) k_cross_count_grp<4><<<grp_blocks(b, b.count[0], 4), BLOCK, 0, st>>>(L + b.off[0], b.count[0], g, map, cnt);
-  if (b.count[1]) k_cross_count_grp<8><<<grp_blocks(b, b.count[1], 8), BLOCK, 0, st>>>(L + b.off[1], b.count[1], g, map, cnt);
-  if (b.count[2]) k_cross_count_grp<16><<<grp_blocks(b, b.count[2], 16), BLOCK, 0, st>>>(L + b.off[2], b.count[2], g, map, cnt);
-  if (b.count[3]) k_cross_count_grp<32><<<grp_blocks(b, b.count[3], 32), BLOCK, 0, st>>>(L + b.off[3], b.count[3], g, map, cnt);
-  int64_t nw = b.count[4] + b.count[5] + b.count[6];
-  if (nw) k_cross_count_grp<64><<<grp_blocks(b, nw, 64), BLOCK, 0, st>>>(L + b.off[4], nw, g, map, cnt);
+  unsigned nrow;
+  const RowSet rows = row_set(b, 6, &nrow);
+  if (nrow) k_cross_count_rows<<<nrow, BLOCK, 0, st>>>(rows, g, map, cnt);
   if (b.count[7]) {
     const int32_t* hubs = L + b.off[7];
     k_zero_hub_counts<<<grid_for(b.count[7]), BLOCK, 0, st>>>(hubs, b.count[7], cnt);
@@ -316,12 +317,9 @@ void launch_cross_count(const DevGraph& g, const Buckets& b, const int32_t* map,
 void launch_cross_emit(const DevGraph& g, const Buckets& b, const int32_t* map, int64_t* cursor, uint64_t* keys,
                        uint32_t* vals, hipStream_t st) {
   const int32_t* L = b.list;
-  if (b.count[0]) k_cross_emit_grp<4><<<grp_blocks(b, b.count[0], 4), BLOCK, 0, st>>>(L + b.off[0], b.count[0], g, map, cursor, keys, vals);
-  if (b.count[1]) k_cross_emit_grp<8><<<grp_blocks(b, b.count[1], 8), BLOCK, 0, st>>>(L + b.off[1], b.count[1], g, map, cursor, keys, vals);
-  if (b.count[2]) k_cross_emit_grp<16><<<grp_blocks(b, b.count[2], 16), BLOCK, 0, st>>>(L + b.off[2], b.count[2], g, map, cursor, keys, vals);
-  if (b.count[3]) k_cross_emit_grp<32><<<grp_blocks(b, b.count[3], 32), BLOCK, 0, st>>>(L + b.off[3], b.count[3], g, map, cursor, keys, vals);
-  int64_t nw = b.count[4] + b.count[5];
-  if (nw) k_cross_emit_grp<64><<<grp_blocks(b, nw, 64), BLOCK, 0, st>>>(L + b.off[4], nw, g, map, cursor, keys, vals);
+  unsigned nrow;
+  const RowSet rows = row_set(b, 5, &nrow);
+  if (nrow) k_cross_emit_rows<<<nrow, BLOCK, 0, st>>>(rows, g, map, cursor, keys, vals);
   if (b.count[6]) k_cross_emit_chunk<<<(unsigned)b.count[6], HUB_BLOCK, 0, st>>>(L + b.off[6], nullptr, b.count[6], 0, g, map, cursor, keys, vals);
   if (b.count[7]) k_cross_emit_chunk<<<(unsigned)b.hub_chunks, HUB_BLOCK, 0, st>>>(L + b.off[7], b.hub_chunk_off, b.count[7], HUB_CHUNK_EDGES, g, map, cursor, keys, vals);
 }

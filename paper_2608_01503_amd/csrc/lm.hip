@@ -1195,15 +1195,13 @@ __global__ void k_sw2(const int64_t* W, int64_t n, int64_t* out, const LMSlot* s
 // Objective: ordered internal edge weight I(C) = sum over edges (u,v) with C[u] = C[v] of w(u,v)
 // ---------------------------------------------------------------------------------------------------------
 // one total over all rows (counter CT_INT of the stripes S), or per_v[v] per row when per_v is not null
+// returns this thread's share, unless every vertex gets its own (per_v)
 template <int G>
-__global__ __launch_bounds__(BLOCK) void k_internal_grp(const int32_t* list, int64_t cnt, DevGraph g,
-                                                        const int32_t* C, int64_t* S, const uint8_t* skip,
-                                                        int64_t* per_v) {
-  if (skip && *skip) return;
+__device__ __forceinline__ int64_t internal_rows(const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk, const DevGraph& g,
+                                                 const int32_t* C, int64_t* per_v) {
   const int gl = threadIdx.x % G;
   int64_t s = 0;
-  for (int64_t gid = (int64_t)blockIdx.x * (BLOCK / G) + threadIdx.x / G; gid < cnt;
-       gid += (int64_t)gridDim.x * (BLOCK / G)) {
+  for (int64_t gid = (int64_t)bid * (BLOCK / G) + threadIdx.x / G; gid < cnt; gid += (int64_t)nblk * (BLOCK / G)) {
     const int32_t v = list[gid];
     int64_t x = internal_row<G <= 16 ? 1 : U>(g, C, g.off[v], g.off[v + 1], gl, G, C[v]);
     if (per_v) {
@@ -1213,6 +1211,15 @@ __global__ __launch_bounds__(BLOCK) void k_internal_grp(const int32_t* list, int
       s += x;
     }
   }
+  return s;
+}
+__global__ __launch_bounds__(BLOCK) void k_internal_rows(RowSet q, DevGraph g, const int32_t* C, int64_t* S, const uint8_t* skip,
+                                                         int64_t* per_v) {
+  if (skip && *skip) return;
+  int64_t s = 0;
+  for_row_kind(q, [&](auto lanes, const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk) {
+    s = internal_rows<decltype(lanes)::value>(list, cnt, bid, nblk, g, C, per_v);
+  });
   if (per_v) return;
   s = sum_reduce<BLOCK>(s);
   if (threadIdx.x == 0 && s) atomicAdd(stripe(S, CT_INT), (unsigned long long)s);
@@ -1837,12 +1844,9 @@ static void launch_internal(const DevGraph& g, const Buckets& b, const int32_t* 
                             FoldDst* pending = nullptr) {
   const int32_t* L = b.list;
   int64_t* S = b.stripes;
-  if (b.count[0]) k_internal_grp<4><<<grp_blocks(b, b.count[0], 4), BLOCK, 0, st>>>(L + b.off[0], b.count[0], g, C, S, skip, per_v);
-  if (b.count[1]) k_internal_grp<8><<<grp_blocks(b, b.count[1], 8), BLOCK, 0, st>>>(L + b.off[1], b.count[1], g, C, S, skip, per_v);
-  if (b.count[2]) k_internal_grp<16><<<grp_blocks(b, b.count[2], 16), BLOCK, 0, st>>>(L + b.off[2], b.count[2], g, C, S, skip, per_v);
-  if (b.count[3]) k_internal_grp<32><<<grp_blocks(b, b.count[3], 32), BLOCK, 0, st>>>(L + b.off[3], b.count[3], g, C, S, skip, per_v);
-  if (b.count[4]) k_internal_grp<32><<<grp_blocks(b, b.count[4], 32), BLOCK, 0, st>>>(L + b.off[4], b.count[4], g, C, S, skip, per_v);
-  if (b.count[5]) k_internal_grp<64><<<grp_blocks(b, b.count[5], 64), BLOCK, 0, st>>>(L + b.off[5], b.count[5], g, C, S, skip, per_v);
+  unsigned nrow;
+  const RowSet rows = row_set(b, 5, &nrow, 5);  // rows of 33 to 128 entries by half wavefronts, 4 entries a lane
+  if (nrow) k_internal_rows<<<nrow, BLOCK, 0, st>>>(rows, g, C, S, skip, per_v);
   if (b.count[6]) k_internal_blk<BIG_BLOCK><<<vtx_blocks(b, b.count[6]), BIG_BLOCK, 0, st>>>(L + b.off[6], b.count[6], g, C, S, skip, per_v);
   if (b.count[7]) {
     if (per_v) k_zero_listed<<<grid_for(b.count[7]), BLOCK, 0, st>>>(L + b.off[7], b.count[7], per_v, skip);

@@ -27,13 +27,6 @@ inline unsigned grid_for(int64_t n) {
   if (g > 65536) g = 65536;
   return (unsigned)g;
 }
-// persistent launches (at most 2048 workgroups looping over their share): one short workgroup per few
-// vertices is bound by the workgroup dispatch rate
-inline unsigned grp_blocks(const Buckets& bk, int64_t cnt, int G) {
-  int64_t b = cdiv(cnt, BLOCK / G);
-  return (unsigned)(b < 1 ? 1 : (b > bk.grid_cap ? bk.grid_cap : b));
-}
-
 __device__ __forceinline__ int find_chunk_owner(const int32_t* chunk_off, int64_t n7, int64_t blk) {
   int64_t lo = 0, hi = n7;
   while (hi - lo > 1) {
@@ -53,15 +46,11 @@ __device__ __forceinline__ uint64_t fkey(int32_t v, const RefSrc& rs, const uint
 
 // a(v, B[v] \ v) and membership of U
 template <int G>
-__global__ __launch_bounds__(BLOCK) void k_aB_grp(const int32_t* list, int64_t cnt, DevGraph g, const int32_t* B,
-                                                  const int64_t* WB, RefSrc rs, int64_t* aB, uint8_t* inU,
-                                                  int64_t* nU) {
-  __shared__ unsigned long long cu;  // |U| of this workgroup, one global atomic at the end
-  if (threadIdx.x == 0) cu = 0;
-  __syncthreads();
+__device__ __forceinline__ void aB_rows(const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk, const DevGraph& g, const int32_t* B,
+                                        const int64_t* WB, const RefSrc& rs, int64_t* aB, uint8_t* inU, unsigned long long* cu) {
   const int gl = threadIdx.x % G;
-  for (int64_t gid = (int64_t)blockIdx.x * (BLOCK / G) + threadIdx.x / G; gid < cnt;
-       gid += (int64_t)gridDim.x * (BLOCK / G)) {
+  for (int64_t gid = (int64_t)bid * (BLOCK / G) + threadIdx.x / G; gid < cnt;
+       gid += (int64_t)nblk * (BLOCK / G)) {
     const int32_t v = list[gid];
     const int32_t bv = B[v];
     int64_t s = 0;
@@ -74,9 +63,18 @@ __global__ __launch_bounds__(BLOCK) void k_aB_grp(const int32_t* list, int64_t c
       const Score sc = rs.sc(v);
       bool u = rs.on(v) && sc.q * s - sc.p * wv * (WB[bv] - wv) >= 0;
       inU[v] = u;
-      if (u) atomicAdd(&cu, 1ull);
+      if (u) atomicAdd(cu, 1ull);
     }
   }
+}
+__global__ __launch_bounds__(BLOCK) void k_aB_rows(RowSet q, DevGraph g, const int32_t* B, const int64_t* WB, RefSrc rs, int64_t* aB,
+                                                   uint8_t* inU, int64_t* nU) {
+  __shared__ unsigned long long cu;  // |U| of this workgroup, one global atomic at the end
+  if (threadIdx.x == 0) cu = 0;
+  __syncthreads();
+  for_row_kind(q, [&](auto lanes, const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk) {
+    aB_rows<decltype(lanes)::value>(list, cnt, bid, nblk, g, B, WB, rs, aB, inU, &cu);
+  });
   __syncthreads();
   if (threadIdx.x == 0 && cu) atomicAdd((unsigned long long*)nU, cu);
 }
@@ -125,11 +123,11 @@ __device__ __forceinline__ bool qualifies(const DevGraph& g, const int32_t* B, c
 
 // Random candidate edge for rows of up to whole-wavefront groups: count, pick, locate (two sweeps).
 template <int G>
-__global__ __launch_bounds__(BLOCK) void k_choose_grp(const int32_t* list, int64_t cnt, DevGraph g, const int32_t* B,
-                                                      const uint8_t* inU, RefSrc rs, int32_t* H) {
+__device__ __forceinline__ void choose_rows(const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk, const DevGraph& g, const int32_t* B,
+                                            const uint8_t* inU, const RefSrc& rs, int32_t* H) {
   const int gl = threadIdx.x % G;
   // the loop bound is the same for every lane of the workgroup: the ballots below see whole wavefronts
-  for (int64_t gbase0 = (int64_t)blockIdx.x * (BLOCK / G); gbase0 < cnt; gbase0 += (int64_t)gridDim.x * (BLOCK / G)) {
+  for (int64_t gbase0 = (int64_t)bid * (BLOCK / G); gbase0 < cnt; gbase0 += (int64_t)nblk * (BLOCK / G)) {
   const int64_t gid = gbase0 + threadIdx.x / G;
   const bool active = gid < cnt;
   const int32_t v = active ? list[gid] : 0;
@@ -181,6 +179,11 @@ __global__ __launch_bounds__(BLOCK) void k_choose_grp(const int32_t* list, int64
     }
   }
   }
+}
+__global__ __launch_bounds__(BLOCK) void k_choose_rows(RowSet q, DevGraph g, const int32_t* B, const uint8_t* inU, RefSrc rs, int32_t* H) {
+  for_row_kind(q, [&](auto lanes, const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk) {
+    choose_rows<decltype(lanes)::value>(list, cnt, bid, nblk, g, B, inU, rs, H);
+  });
 }
 
 // hubs: per-chunk (qualifying count << 32 | qualifying count below v)
@@ -326,12 +329,11 @@ __global__ void k_tree_keys(int64_t n, const uint8_t* member, const int64_t* tpo
 
 // a(v, X_{<v}): edges to earlier vertices of the same tree
 template <int G>
-__global__ __launch_bounds__(BLOCK) void k_aX_grp(const int32_t* list, int64_t cnt, DevGraph g, const uint8_t* member,
-                                                  const int32_t* root, RefSrc rs, const uint8_t* flip,
-                                                  int64_t* aX) {
+__device__ __forceinline__ void aX_rows(const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk, const DevGraph& g, const uint8_t* member,
+                                        const int32_t* root, const RefSrc& rs, const uint8_t* flip, int64_t* aX) {
   const int gl = threadIdx.x % G;
-  for (int64_t gid = (int64_t)blockIdx.x * (BLOCK / G) + threadIdx.x / G; gid < cnt;
-       gid += (int64_t)gridDim.x * (BLOCK / G)) {
+  for (int64_t gid = (int64_t)bid * (BLOCK / G) + threadIdx.x / G; gid < cnt;
+       gid += (int64_t)nblk * (BLOCK / G)) {
     const int32_t v = list[gid];
     if (!member[v]) continue;  // uniform within the group
     const int32_t rv = root[v];
@@ -344,6 +346,12 @@ __global__ __launch_bounds__(BLOCK) void k_aX_grp(const int32_t* list, int64_t c
     s = gsum<G>(s);
     if (gl == 0) aX[v] = s;
   }
+}
+__global__ __launch_bounds__(BLOCK) void k_aX_rows(RowSet q, DevGraph g, const uint8_t* member, const int32_t* root, RefSrc rs,
+                                                   const uint8_t* flip, int64_t* aX) {
+  for_row_kind(q, [&](auto lanes, const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk) {
+    aX_rows<decltype(lanes)::value>(list, cnt, bid, nblk, g, member, root, rs, flip, aX);
+  });
 }
 
 __global__ __launch_bounds__(HUB_BLOCK) void k_aX_hub(const int32_t* hubs, const int32_t* chunk_off, int64_t n7,
@@ -412,12 +420,9 @@ void refine(const DevGraph& g, const Buckets& b, const RefSrc& rs, const int32_t
   // constraint-cluster weights and U
   launch_cluster_weights(B, g.vw, n, rb.WB, st);
   k_set_i64<<<1, 1, 0, st>>>(&ctrl->refine_U, 0);
-  if (b.count[0]) k_aB_grp<4><<<grp_blocks(b, b.count[0], 4), BLOCK, 0, st>>>(L + b.off[0], b.count[0], g, B, rb.WB, rs, rb.aB, rb.inU, &ctrl->refine_U);
-  if (b.count[1]) k_aB_grp<8><<<grp_blocks(b, b.count[1], 8), BLOCK, 0, st>>>(L + b.off[1], b.count[1], g, B, rb.WB, rs, rb.aB, rb.inU, &ctrl->refine_U);
-  if (b.count[2]) k_aB_grp<16><<<grp_blocks(b, b.count[2], 16), BLOCK, 0, st>>>(L + b.off[2], b.count[2], g, B, rb.WB, rs, rb.aB, rb.inU, &ctrl->refine_U);
-  if (b.count[3]) k_aB_grp<32><<<grp_blocks(b, b.count[3], 32), BLOCK, 0, st>>>(L + b.off[3], b.count[3], g, B, rb.WB, rs, rb.aB, rb.inU, &ctrl->refine_U);
-  int64_t nw = b.count[4] + b.count[5] + b.count[6];
-  if (nw) k_aB_grp<64><<<grp_blocks(b, nw, 64), BLOCK, 0, st>>>(L + b.off[4], nw, g, B, rb.WB, rs, rb.aB, rb.inU, &ctrl->refine_U);
+  unsigned nrow;
+  const RowSet rows = row_set(b, 6, &nrow);
+  if (nrow) k_aB_rows<<<nrow, BLOCK, 0, st>>>(rows, g, B, rb.WB, rs, rb.aB, rb.inU, &ctrl->refine_U);
   const int32_t* hubs = L + b.off[7];
   const int64_t n7 = b.count[7];
   if (n7) {
@@ -426,11 +431,7 @@ void refine(const DevGraph& g, const Buckets& b, const RefSrc& rs, const int32_t
     k_hub_inU<<<grid_for(n7), BLOCK, 0, st>>>(hubs, n7, g, B, rb.WB, rs, rb.aB, rb.inU, &ctrl->refine_U);
   }
   // random candidate edge
-  if (b.count[0]) k_choose_grp<4><<<grp_blocks(b, b.count[0], 4), BLOCK, 0, st>>>(L + b.off[0], b.count[0], g, B, rb.inU, rs, rb.H);
-  if (b.count[1]) k_choose_grp<8><<<grp_blocks(b, b.count[1], 8), BLOCK, 0, st>>>(L + b.off[1], b.count[1], g, B, rb.inU, rs, rb.H);
-  if (b.count[2]) k_choose_grp<16><<<grp_blocks(b, b.count[2], 16), BLOCK, 0, st>>>(L + b.off[2], b.count[2], g, B, rb.inU, rs, rb.H);
-  if (b.count[3]) k_choose_grp<32><<<grp_blocks(b, b.count[3], 32), BLOCK, 0, st>>>(L + b.off[3], b.count[3], g, B, rb.inU, rs, rb.H);
-  if (nw) k_choose_grp<64><<<grp_blocks(b, nw, 64), BLOCK, 0, st>>>(L + b.off[4], nw, g, B, rb.inU, rs, rb.H);
+  if (nrow) k_choose_rows<<<nrow, BLOCK, 0, st>>>(rows, g, B, rb.inU, rs, rb.H);
   if (n7) {
     k_choose_hub_count<<<(unsigned)b.hub_chunks, HUB_BLOCK, 0, st>>>(hubs, b.hub_chunk_off, n7, g, B, rb.inU, rs, b.hub_ps);
     k_choose_hub_pick<<<grid_for(n7), BLOCK, 0, st>>>(hubs, b.hub_chunk_off, n7, rb.inU, rs, b.hub_ps, b.hub_acc, rb.H);
@@ -465,11 +466,7 @@ void refine(const DevGraph& g, const Buckets& b, const RefSrc& rs, const int32_t
     const uint32_t* sv = rb.v1;
     // a(v, X_{<v}) for tree members
     fill_i64(rb.aX, 0, n, st);
-    if (b.count[0]) k_aX_grp<4><<<grp_blocks(b, b.count[0], 4), BLOCK, 0, st>>>(L + b.off[0], b.count[0], g, rb.member, rb.root, rs, rb.flip, rb.aX);
-    if (b.count[1]) k_aX_grp<8><<<grp_blocks(b, b.count[1], 8), BLOCK, 0, st>>>(L + b.off[1], b.count[1], g, rb.member, rb.root, rs, rb.flip, rb.aX);
-    if (b.count[2]) k_aX_grp<16><<<grp_blocks(b, b.count[2], 16), BLOCK, 0, st>>>(L + b.off[2], b.count[2], g, rb.member, rb.root, rs, rb.flip, rb.aX);
-    if (b.count[3]) k_aX_grp<32><<<grp_blocks(b, b.count[3], 32), BLOCK, 0, st>>>(L + b.off[3], b.count[3], g, rb.member, rb.root, rs, rb.flip, rb.aX);
-    if (nw) k_aX_grp<64><<<grp_blocks(b, nw, 64), BLOCK, 0, st>>>(L + b.off[4], nw, g, rb.member, rb.root, rs, rb.flip, rb.aX);
+    if (nrow) k_aX_rows<<<nrow, BLOCK, 0, st>>>(rows, g, rb.member, rb.root, rs, rb.flip, rb.aX);
     if (n7) k_aX_hub<<<(unsigned)b.hub_chunks, HUB_BLOCK, 0, st>>>(hubs, b.hub_chunk_off, n7, g, rb.member, rb.root, rs, rb.flip, rb.aX);
     k_sorted_terms<<<grid_for(m), BLOCK, 0, st>>>(m, sv, g.vw, rb.aB, rb.aX, rb.tmp64a, rb.tmp64b, rb.pos_of);
     scan_i64_i64(rb.tmp64a, rb.pw, m, rb.scan_temp, st);
