@@ -362,13 +362,11 @@ __global__ __launch_bounds__(1024) void k_final_state(LMSlot* s, int last, int64
 // Singleton pass (first coarsening pass, Sec. IV-A: clusters are the vertices, no enumeration)
 // ---------------------------------------------------------------------------------------------------------
 template <int G>
-__global__ __launch_bounds__(BLOCK) void k_single_grp(const int32_t* list, int64_t cnt, DevGraph g, ScoreSrc ss,
-                                                      uint32_t pa, uint32_t pb, VState* vs, LMSlot* slot,
-                                                      int pass, int64_t* S) {
-  VtxAcc va;
+__device__ __forceinline__ void single_rows(const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk, const DevGraph& g, const ScoreSrc& ss,
+                                            uint32_t pa, uint32_t pb, VState* vs, VtxAcc& va) {
   const int gl = threadIdx.x % G;
-  for (int64_t gid = (int64_t)blockIdx.x * (BLOCK / G) + threadIdx.x / G; gid < cnt;
-       gid += (int64_t)gridDim.x * (BLOCK / G)) {
+  for (int64_t gid = (int64_t)bid * (BLOCK / G) + threadIdx.x / G; gid < cnt;
+       gid += (int64_t)nblk * (BLOCK / G)) {
     const int32_t v = list[gid];
     const int64_t wv = g.vw[v];
     const Score sc = ss.at(v);
@@ -377,6 +375,13 @@ __global__ __launch_bounds__(BLOCK) void k_single_grp(const int32_t* list, int64
     best_reduce<G>(r);
     if (gl == 0) finish_vertex(v, v, wv, 0, r.s, r.c, sc, g.vw, pa, pb, 0, vs, va, ss.ownv);
   }
+}
+__global__ __launch_bounds__(BLOCK) void k_single_rows(RowSet q, DevGraph g, ScoreSrc ss, uint32_t pa, uint32_t pb, VState* vs,
+                                                       LMSlot* slot, int pass, int64_t* S) {
+  VtxAcc va;
+  for_row_kind(q, [&](auto lanes, const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk) {
+    single_rows<decltype(lanes)::value>(list, cnt, bid, nblk, g, ss, pa, pb, vs, va);
+  });
   acc_flush<BLOCK>(va, S, CT_NCAND, -1);
 }
 
@@ -1539,12 +1544,11 @@ __device__ __forceinline__ void check_edge(const DevGraph& g, int32_t v, int64_t
 // same weight, and there must be as many lower entries as upper ones (nnz / 2 each).  Positions map to distinct
 // lower entries, so equal counts make the pairing a bijection.
 template <int G>
-__global__ __launch_bounds__(BLOCK) void k_sym_emit_grp(const int32_t* list, int64_t cnt, DevGraph g,
-                                                        const int32_t* lo, const int64_t* lbase, uint64_t* keys,
-                                                        uint32_t* vals) {
+__device__ __forceinline__ void sym_emit_rows(const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk, const DevGraph& g,
+                                              const int32_t* lo, const int64_t* lbase, uint64_t* keys, uint32_t* vals) {
   const int gl = threadIdx.x % G;
-  for (int64_t gid = (int64_t)blockIdx.x * (BLOCK / G) + threadIdx.x / G; gid < cnt;
-       gid += (int64_t)gridDim.x * (BLOCK / G)) {
+  for (int64_t gid = (int64_t)bid * (BLOCK / G) + threadIdx.x / G; gid < cnt;
+       gid += (int64_t)nblk * (BLOCK / G)) {
     const int32_t v = list[gid];
     const int64_t rb = g.off[v], re = g.off[v + 1];
     const int64_t shift = lbase[v] + lo[v];
@@ -1553,6 +1557,12 @@ __global__ __launch_bounds__(BLOCK) void k_sym_emit_grp(const int32_t* list, int
       vals[j - shift] = (uint32_t)g.w[j];
     }
   }
+}
+__global__ __launch_bounds__(BLOCK) void k_sym_emit_rows(RowSet q, DevGraph g, const int32_t* lo, const int64_t* lbase, uint64_t* keys,
+                                                         uint32_t* vals) {
+  for_row_kind(q, [&](auto lanes, const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk) {
+    sym_emit_rows<decltype(lanes)::value>(list, cnt, bid, nblk, g, lo, lbase, keys, vals);
+  });
 }
 
 // hub rows: each chunk writes the upper entries of its own edge range
@@ -1619,14 +1629,11 @@ __device__ __forceinline__ void flush_check(EdgeCheck ec, int64_t wsum, Ctrl* ct
 }
 
 template <int G>
-__global__ __launch_bounds__(BLOCK) void k_validate_grp(const int32_t* list, int64_t cnt, DevGraph g, VwSrc vm,
-                                                        const int64_t* vw_given, int64_t* vw_out, Ctrl* ctrl,
-                                                        int32_t* lo, bool search) {
+__device__ __forceinline__ void validate_rows(const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk, const DevGraph& g, const VwSrc& vm,
+                                              const int64_t* vw_given, int64_t* vw_out, int32_t* lo, bool search, EdgeCheck& ec, int64_t& wsum) {
   const int gl = threadIdx.x % G;
-  EdgeCheck ec;
-  int64_t wsum = 0;
-  for (int64_t gid = (int64_t)blockIdx.x * (BLOCK / G) + threadIdx.x / G; gid < cnt;
-       gid += (int64_t)gridDim.x * (BLOCK / G)) {
+  for (int64_t gid = (int64_t)bid * (BLOCK / G) + threadIdx.x / G; gid < cnt;
+       gid += (int64_t)nblk * (BLOCK / G)) {
     const int32_t v = list[gid];
     const int64_t rb = g.off[v], re = g.off[v + 1];
     const int64_t ws0 = ec.ws, lo0 = ec.lower;
@@ -1640,6 +1647,14 @@ __global__ __launch_bounds__(BLOCK) void k_validate_grp(const int32_t* list, int
       wsum += ws;
     }
   }
+}
+__global__ __launch_bounds__(BLOCK) void k_validate_rows(RowSet q, DevGraph g, VwSrc vm, const int64_t* vw_given, int64_t* vw_out,
+                                                         Ctrl* ctrl, int32_t* lo, bool search) {
+  EdgeCheck ec;
+  int64_t wsum = 0;
+  for_row_kind(q, [&](auto lanes, const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk) {
+    validate_rows<decltype(lanes)::value>(list, cnt, bid, nblk, g, vm, vw_given, vw_out, lo, search, ec, wsum);
+  });
   flush_check(ec, wsum, ctrl);
 }
 
@@ -1784,11 +1799,9 @@ void launch_validate_rows(const DevGraph& g, const Buckets& b, int vw_mode, cons
   const int64_t nw = b.count[4] + b.count[5];
   const int32_t* hubs = L + b.off[7];
   if (tr && b.count[7]) fill_i32(lo, 0, g.n, st);  // hub rows add their chunks' counts
-  if (b.count[0]) k_validate_grp<4><<<grp_blocks(b, b.count[0], 4), BLOCK, 0, st>>>(L + b.off[0], b.count[0], g, vm, vw_given, vw_out, ctrl, lo, sb.search);
-  if (b.count[1]) k_validate_grp<8><<<grp_blocks(b, b.count[1], 8), BLOCK, 0, st>>>(L + b.off[1], b.count[1], g, vm, vw_given, vw_out, ctrl, lo, sb.search);
-  if (b.count[2]) k_validate_grp<16><<<grp_blocks(b, b.count[2], 16), BLOCK, 0, st>>>(L + b.off[2], b.count[2], g, vm, vw_given, vw_out, ctrl, lo, sb.search);
-  if (b.count[3]) k_validate_grp<32><<<grp_blocks(b, b.count[3], 32), BLOCK, 0, st>>>(L + b.off[3], b.count[3], g, vm, vw_given, vw_out, ctrl, lo, sb.search);
-  if (nw) k_validate_grp<64><<<grp_blocks(b, nw, 64), BLOCK, 0, st>>>(L + b.off[4], nw, g, vm, vw_given, vw_out, ctrl, lo, sb.search);
+  unsigned nrow;
+  const RowSet rows = row_set(b, 5, &nrow);
+  if (nrow) k_validate_rows<<<nrow, BLOCK, 0, st>>>(rows, g, vm, vw_given, vw_out, ctrl, lo, sb.search);
   if (b.count[6]) k_validate_blk<<<vtx_blocks(b, b.count[6]), BIG_BLOCK, 0, st>>>(L + b.off[6], b.count[6], g, vm, vw_given, vw_out, ctrl, lo, sb.search);
   if (b.count[7]) {
     fill_i64(b.hub_acc, 0, b.count[7], st);
@@ -1799,11 +1812,9 @@ void launch_validate_rows(const DevGraph& g, const Buckets& b, int vw_mode, cons
     scan_i32_i64(lo, sb.lbase, g.n, sb.scan_temp, st);
     const int64_t m = g.nnz / 2;
     const int32_t* lc = lo;
-    if (b.count[0]) k_sym_emit_grp<4><<<grp_blocks(b, b.count[0], 4), BLOCK, 0, st>>>(L + b.off[0], b.count[0], g, lc, sb.lbase, sb.k0, sb.v0);
-    if (b.count[1]) k_sym_emit_grp<8><<<grp_blocks(b, b.count[1], 8), BLOCK, 0, st>>>(L + b.off[1], b.count[1], g, lc, sb.lbase, sb.k0, sb.v0);
-    if (b.count[2]) k_sym_emit_grp<16><<<grp_blocks(b, b.count[2], 16), BLOCK, 0, st>>>(L + b.off[2], b.count[2], g, lc, sb.lbase, sb.k0, sb.v0);
-    if (b.count[3]) k_sym_emit_grp<32><<<grp_blocks(b, b.count[3], 32), BLOCK, 0, st>>>(L + b.off[3], b.count[3], g, lc, sb.lbase, sb.k0, sb.v0);
-    if (nw + b.count[6]) k_sym_emit_grp<64><<<grp_blocks(b, nw + b.count[6], 64), BLOCK, 0, st>>>(L + b.off[4], nw + b.count[6], g, lc, sb.lbase, sb.k0, sb.v0);
+    unsigned nem;
+    const RowSet em = row_set(b, 6, &nem);
+    if (nem) k_sym_emit_rows<<<nem, BLOCK, 0, st>>>(em, g, lc, sb.lbase, sb.k0, sb.v0);
     if (b.count[7]) k_sym_emit_hub<<<(unsigned)b.hub_chunks, HUB_BLOCK, 0, st>>>(hubs, b.hub_chunk_off, b.count[7], g, lc, sb.lbase, sb.k0, sb.v0);
     int bits = 1;
     while (((int64_t)1 << bits) < g.n) ++bits;
@@ -1892,12 +1903,9 @@ static void launch_destinations(const DevGraph& g, const Buckets& b, const Score
     double sb = 0;
     for (int k = 0; k < NBUCKET; ++k) sb += 16.0 * (double)b.edges[k] + 48.0 * (double)b.count[k];
     prof_begin(PF_SINGLE, st);
-    if (b.count[0]) k_single_grp<4><<<grp_blocks(b, b.count[0], 4), BLOCK, 0, st>>>(L + b.off[0], b.count[0], g, sc, pa, pb, vs, slot, pass, S);
-    if (b.count[1]) k_single_grp<8><<<grp_blocks(b, b.count[1], 8), BLOCK, 0, st>>>(L + b.off[1], b.count[1], g, sc, pa, pb, vs, slot, pass, S);
-    if (b.count[2]) k_single_grp<16><<<grp_blocks(b, b.count[2], 16), BLOCK, 0, st>>>(L + b.off[2], b.count[2], g, sc, pa, pb, vs, slot, pass, S);
-    if (b.count[3]) k_single_grp<32><<<grp_blocks(b, b.count[3], 32), BLOCK, 0, st>>>(L + b.off[3], b.count[3], g, sc, pa, pb, vs, slot, pass, S);
-    if (b.count[4]) k_single_grp<32><<<grp_blocks(b, b.count[4], 32), BLOCK, 0, st>>>(L + b.off[4], b.count[4], g, sc, pa, pb, vs, slot, pass, S);
-    if (b.count[5]) k_single_grp<64><<<grp_blocks(b, b.count[5], 64), BLOCK, 0, st>>>(L + b.off[5], b.count[5], g, sc, pa, pb, vs, slot, pass, S);
+    unsigned nrow;
+    const RowSet rows = row_set(b, 5, &nrow, 5);  // rows of 33 to 128 entries by half wavefronts
+    if (nrow) k_single_rows<<<nrow, BLOCK, 0, st>>>(rows, g, sc, pa, pb, vs, slot, pass, S);
     if (b.count[6]) k_single_blk<BIG_BLOCK><<<vtx_blocks(b, b.count[6]), BIG_BLOCK, 0, st>>>(L + b.off[6], b.count[6], g, sc, pa, pb, vs, slot, pass, S);
     if (n7) {
       k_single_hub<<<(unsigned)b.hub_chunks, HUB_BLOCK, 0, st>>>(hubs, b.hub_chunk_off, n7, g, sc, hs.ps, hs.pc);
