@@ -20,7 +20,8 @@ constexpr int MAX_PASSES = 32;
 // b adds instead into stripe b mod NSTRIPE of the counter (stripes 128 bytes apart), and one workgroup later
 // adds the stripes of each counter into its destination and clears them (a fold kernel, or the prologue of
 // the next single-workgroup bookkeeping kernel of the local move).
-constexpr int NSTRIPE = 1024;
+constexpr int NSTRIPE = 256;  // a fold of 1024 stripes read 128 KB through one workgroup, 2 us of its 5
+constexpr int STRIPE_ROOM = 1024;  // their part of a workspace (see SLOT_BYTES)
 constexpr int STRIPE_W = 16;  // int64 slots per stripe, one per counter id
 enum : int {
   CT_NCAND = 0,  // candidates of a pass

@@ -140,7 +140,7 @@ size_t carve(WS& w, char* base, int64_t n, int64_t nnz) {
   w.tg.status_cap = (M + 1) / LB_TILE + 2;
   w.tg.status = c.take<unsigned long long>(w.tg.status_cap);
   w.tg.ticket = c.take<uint32_t>(1);
-  w.stripes = c.take<int64_t>((int64_t)NSTRIPE * STRIPE_W);
+  w.stripes = c.take<int64_t>((int64_t)STRIPE_ROOM * STRIPE_W);
   w.scan_temp = c.take<char>((int64_t)scan_temp_bytes(M + 1));
   return c.off;
 }

@@ -66,12 +66,13 @@ struct FoldDst {
 };
 
 // Adds the stripes of every counter that has a destination into it and clears those stripes; run by one
-// workgroup of 1024 threads.  The stripes are read as 8192 pieces of 16 bytes, thread t taking pieces t,
-// t + 1024, ..., t + 7168: every load instruction of a wavefront covers 1 KB of consecutive bytes, and piece p
+// workgroup of 1024 threads.  The stripes are read as 2048 pieces of 16 bytes, thread t taking pieces t
+// and t + 1024: every load instruction of a wavefront covers 1 KB of consecutive bytes, and piece p
 // holds counters 2 (p mod 8) and 2 (p mod 8) + 1 of stripe p / 8, so a thread always sees the same two
 // counters.  Ends with a barrier: the destinations are final for every thread afterwards.
 __device__ __forceinline__ void fold_block(int64_t* S, const FoldDst& f) {
-  static_assert(NSTRIPE == 1024 && STRIPE_W == 16 && CT_COUNT <= STRIPE_W, "8 pieces per stripe, 8 per thread");
+  static_assert(STRIPE_W == 16 && CT_COUNT <= STRIPE_W, "8 pieces per stripe");
+  constexpr int PT = NSTRIPE * 8 / 1024;  // pieces per thread
   __shared__ int64_t part[1024 / WAVE][STRIPE_W];
   const int t = threadIdx.x, lane = t & (WAVE - 1), wv = t / WAVE;
   const int c0 = 2 * (t & 7), c1 = c0 + 1;
@@ -79,16 +80,16 @@ __device__ __forceinline__ void fold_block(int64_t* S, const FoldDst& f) {
   int64_t a0 = 0, a1 = 0;
   if (f0 || f1) {
     longlong2* P = (longlong2*)S;
-    longlong2 v[8];
+    longlong2 v[PT];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = P[t + 1024 * k];
+    for (int k = 0; k < PT; ++k) v[k] = P[t + 1024 * k];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
+    for (int k = 0; k < PT; ++k) {
       if (f0) a0 += v[k].x;
       if (f1) a1 += v[k].y;
     }
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
+    for (int k = 0; k < PT; ++k) {
       if ((f0 && v[k].x) || (f1 && v[k].y)) {
         longlong2 z = v[k];
         if (f0) z.x = 0;
