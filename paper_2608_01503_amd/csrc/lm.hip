@@ -1186,14 +1186,28 @@ __global__ __launch_bounds__(BLOCK) void k_assign_empty(int64_t n, const uint8_t
 }
 
 // sum over cluster ids of W_c^2
-__global__ void k_sw2(const int64_t* W, int64_t n, int64_t* out, const LMSlot* slot, int pass) {
+// Sums over an array, by few large workgroups: the adds of a workgroup to one address take about 12 ns each, one after
+// the other (with 1024 workgroups of 256 threads the two sums of vertex weights took 28 us on 2^20 vertices, now 10 us).
+constexpr int SUM_BLOCK = 1024, SUM_U = 4;
+inline unsigned sum_blocks(int64_t n) {
+  const int64_t g = (n + SUM_BLOCK * SUM_U - 1) / (SUM_BLOCK * SUM_U);
+  return (unsigned)(g < 1 ? 1 : (g > 256 ? 256 : g));
+}
+template <typename F>
+__device__ __forceinline__ void sum_each(const int64_t* x, int64_t n, F f) {
+  for (int64_t i = (int64_t)blockIdx.x * SUM_BLOCK * SUM_U + threadIdx.x; i < n; i += (int64_t)gridDim.x * SUM_BLOCK * SUM_U) {
+    int64_t v[SUM_U];
+#pragma unroll
+    for (int k = 0; k < SUM_U; ++k) v[k] = i + k * SUM_BLOCK < n ? x[i + k * SUM_BLOCK] : 0;
+#pragma unroll
+    for (int k = 0; k < SUM_U; ++k) f(v[k]);
+  }
+}
+__global__ __launch_bounds__(SUM_BLOCK) void k_sw2(const int64_t* W, int64_t n, int64_t* out, const LMSlot* slot, int pass) {
   if (slot && pass >= 0 && slot->skip[pass]) return;
   int64_t s = 0;
-  for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n; c += (int64_t)gridDim.x * blockDim.x) {
-    int64_t x = W[c];
-    s += x * x;
-  }
-  s = sum_reduce<BLOCK>(s);
+  sum_each(W, n, [&](int64_t x) { s += x * x; });
+  s = sum_reduce<SUM_BLOCK>(s);
   if (threadIdx.x == 0 && s) atomicAdd((unsigned long long*)out, (unsigned long long)s);
 }
 
@@ -1713,15 +1727,11 @@ __global__ void k_validate_hub_final(const int32_t* hubs, int64_t n7, VwSrc vm, 
   if (err) atomicOr(&ctrl->err_bits, err);
 }
 
-__global__ void k_vertex_sums(const int64_t* vw, int64_t n, Ctrl* ctrl) {
+__global__ __launch_bounds__(SUM_BLOCK) void k_vertex_sums(const int64_t* vw, int64_t n, Ctrl* ctrl) {
   int64_t s = 0, s2 = 0;
-  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
-    int64_t x = vw[v];
-    s += x;
-    s2 += x * x;
-  }
-  s = sum_reduce<BLOCK>(s);
-  s2 = sum_reduce<BLOCK>(s2);
+  sum_each(vw, n, [&](int64_t x) { s += x; s2 += x * x; });
+  s = sum_reduce<SUM_BLOCK>(s);
+  s2 = sum_reduce<SUM_BLOCK>(s2);
   if (threadIdx.x == 0) {
     if (s) atomicAdd((unsigned long long*)&ctrl->sum_w, (unsigned long long)s);
     if (s2) atomicAdd((unsigned long long*)&ctrl->sum_w2, (unsigned long long)s2);
@@ -1843,7 +1853,7 @@ void launch_hub_chunks(const int32_t* hubs, int64_t n7, const int64_t* off, int3
 }
 
 void launch_vertex_sums(const int64_t* vw, int64_t n, Ctrl* ctrl, hipStream_t st) {
-  k_vertex_sums<<<red_blocks(n), BLOCK, 0, st>>>(vw, n, ctrl);
+  k_vertex_sums<<<sum_blocks(n), SUM_BLOCK, 0, st>>>(vw, n, ctrl);
 }
 
 void launch_cluster_weights(const int32_t* C, const int64_t* vw, int64_t n, int64_t* W, hipStream_t st) {
@@ -1883,7 +1893,7 @@ void launch_objective(const DevGraph& g, const Buckets& b, const int32_t* C, con
   k_zero_i64<<<1, 1, 0, st>>>(&ctrl->obj_I);
   k_zero_i64<<<1, 1, 0, st>>>(&ctrl->obj_SW2);
   launch_internal(g, b, C, &ctrl->obj_I, nullptr, st);
-  k_sw2<<<red_blocks(g.n), BLOCK, 0, st>>>(W, g.n, &ctrl->obj_SW2, nullptr, -1);
+  k_sw2<<<sum_blocks(g.n), SUM_BLOCK, 0, st>>>(W, g.n, &ctrl->obj_SW2, nullptr, -1);
 }
 
 static HubScratch hub_scratch(const Buckets& b);
@@ -2058,7 +2068,7 @@ static void state_sums_sw2(const SegLM& sg, const int64_t* W, int64_t n, LMSlot*
     k_seg_sum<<<seg_blocks(G), SEG_SUM_BLOCK, 0, st>>>(W, 1, sg.vbase, G, sg.SW2 + (int64_t)k * G,
                                               k ? sg.SW2 + (int64_t)(k - 1) * G : nullptr, pass >= 0 ? slot : nullptr, pass);
   } else if (pass < 0) {  // the starting state; later states follow from the moves (apply_and_empty)
-    k_sw2<<<red_blocks(n), BLOCK, 0, st>>>(W, n, &slot->SW2[k], nullptr, pass);
+    k_sw2<<<sum_blocks(n), SUM_BLOCK, 0, st>>>(W, n, &slot->SW2[k], nullptr, pass);
   }
 }
 
