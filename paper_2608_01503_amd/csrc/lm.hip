@@ -627,7 +627,7 @@ __global__ __launch_bounds__(BS) void k_enum_blk(const int32_t* list, int64_t cn
 // now about 95 us.
 constexpr int HUB_PARTS = HUB_BLOCK;
 constexpr int HUB_SLOTS = 1 << HUB_LDS_BITS;
-static_assert(HUB_SLOTS == 2 * HUB_CHUNK, "the LDS table holds 2 slots per chunk edge");
+static_assert(HUB_SLOTS == 2 * HUB_CHUNK && HUB_SLOTS % (2 * U * HUB_BLOCK) == 0, "the LDS table holds 2 slots per chunk edge");
 
 struct HubRow {
   int32_t v;
@@ -718,18 +718,23 @@ __global__ __launch_bounds__(HUB_BLOCK) void k_hub_best(const int32_t* hubs, con
       const int64_t e = (int64_t)ch * (r.parts + 1) + r.ch;
       const uint64_t* p = rec + (int64_t)ch * HUB_CHUNK;
       const int j1 = ends[e + 1];
-      for (int j = ends[e] + gl; j < j1; j += 1 << ls) {
-        const uint64_t x = p[j];
-        const int32_t c = (int32_t)(x >> 32);
-        if (sub > 1 && ((hub_hash(c, r.parts) & 0xFFFFFFFFu) * sub) >> 32 != q) continue;
-        uint32_t h = hslot(c, HUB_LDS_BITS);
-        int probe = 0;
-        for (; probe < HUB_SLOTS; ++probe) {
-          const int32_t prev = atomicCAS(&lk[h], -1, c);
-          if (prev == -1 || prev == c) { atomicAdd(&lv[h], (uint32_t)x); break; }
-          h = (h + 1) & (HUB_SLOTS - 1);
+      for (int j = ends[e] + gl; j < j1; j += U << ls) {
+        uint64_t xs[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) xs[k] = j + (k << ls) < j1 ? p[j + (k << ls)] : ~0ull;  // no cluster has id -1
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+          const int32_t c = (int32_t)(xs[k] >> 32);
+          if (c < 0 || (sub > 1 && ((hub_hash(c, r.parts) & 0xFFFFFFFFu) * sub) >> 32 != q)) continue;
+          uint32_t h = hslot(c, HUB_LDS_BITS);
+          int probe = 0;
+          for (; probe < HUB_SLOTS; ++probe) {
+            const int32_t prev = atomicCAS(&lk[h], -1, c);
+            if (prev == -1 || prev == c) { atomicAdd(&lv[h], (uint32_t)xs[k]); break; }
+            h = (h + 1) & (HUB_SLOTS - 1);
+          }
+          if (probe == HUB_SLOTS) full = 1;
         }
-        if (probe == HUB_SLOTS) full = 1;
       }
     }
     __syncthreads();
@@ -740,12 +745,20 @@ __global__ __launch_bounds__(HUB_BLOCK) void k_hub_best(const int32_t* hubs, con
       __syncthreads();
       continue;
     }
-    for (int s = t; s < HUB_SLOTS; s += HUB_BLOCK) {
-      const int32_t c = lk[s];
-      if (c < 0) continue;
-      ++best.np;
-      const int64_t x = sc.q * (int64_t)lv[s] - sc.p * wvt * W[c];
-      if (better(x, c, best.s, best.c)) { best.s = x; best.c = c; }
+    for (int s0 = t; s0 < HUB_SLOTS; s0 += 2 * U * HUB_BLOCK) {
+      int32_t cs[2 * U];
+      int64_t Ws[2 * U];
+#pragma unroll
+      for (int k = 0; k < 2 * U; ++k) cs[k] = lk[s0 + k * HUB_BLOCK];
+#pragma unroll
+      for (int k = 0; k < 2 * U; ++k) Ws[k] = cs[k] >= 0 ? W[cs[k]] : 0;
+#pragma unroll
+      for (int k = 0; k < 2 * U; ++k) {
+        if (cs[k] < 0) continue;
+        ++best.np;
+        const int64_t x = sc.q * (int64_t)lv[s0 + k * HUB_BLOCK] - sc.p * wvt * Ws[k];
+        if (better(x, cs[k], best.s, best.c)) { best.s = x; best.c = cs[k]; }
+      }
     }
     ++q;
     __syncthreads();
