@@ -10,6 +10,8 @@
 //          is the earlier part of the tree; w(X) and w(X, B \ X) come from prefix sums over the sorted order
 //          (w(X_i, B \ X_i) = sum_{j <= i} a(v_j, B \ v_j) - 2 a(v_j, X_{j-1})); the longest all-valid prefix
 //          takes the root's id, every other vertex keeps its own id.
+#include <algorithm>
+
 #include "common.h"
 #include "rows.h"
 
@@ -47,7 +49,7 @@ __device__ __forceinline__ uint64_t fkey(int32_t v, const RefSrc& rs, const uint
 // a(v, B[v] \ v) and membership of U
 template <int G>
 __device__ __forceinline__ void aB_rows(const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk, const DevGraph& g, const int32_t* B,
-                                        const int64_t* WB, const RefSrc& rs, int64_t* aB, uint8_t* inU, unsigned long long* cu) {
+                                        const int64_t* WB, const RefSrc& rs, int64_t* aB, uint8_t* inU) {
   const int gl = threadIdx.x % G;
   for (int64_t gid = (int64_t)bid * (BLOCK / G) + threadIdx.x / G; gid < cnt;
        gid += (int64_t)nblk * (BLOCK / G)) {
@@ -63,20 +65,14 @@ __device__ __forceinline__ void aB_rows(const int32_t* list, int64_t cnt, unsign
       const Score sc = rs.sc(v);
       bool u = rs.on(v) && sc.q * s - sc.p * wv * (WB[bv] - wv) >= 0;
       inU[v] = u;
-      if (u) atomicAdd(cu, 1ull);
     }
   }
 }
 __global__ __launch_bounds__(BLOCK) void k_aB_rows(RowSet q, DevGraph g, const int32_t* B, const int64_t* WB, RefSrc rs, int64_t* aB,
-                                                   uint8_t* inU, int64_t* nU) {
-  __shared__ unsigned long long cu;  // |U| of this workgroup, one global atomic at the end
-  if (threadIdx.x == 0) cu = 0;
-  __syncthreads();
+                                                   uint8_t* inU) {
   for_row_kind(q, [&](auto lanes, const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk) {
-    aB_rows<decltype(lanes)::value>(list, cnt, bid, nblk, g, B, WB, rs, aB, inU, &cu);
+    aB_rows<decltype(lanes)::value>(list, cnt, bid, nblk, g, B, WB, rs, aB, inU);
   });
-  __syncthreads();
-  if (threadIdx.x == 0 && cu) atomicAdd((unsigned long long*)nU, cu);
 }
 
 __global__ __launch_bounds__(HUB_BLOCK) void k_aB_hub(const int32_t* hubs, const int32_t* chunk_off, int64_t n7,
@@ -99,20 +95,28 @@ __global__ void k_hub_zero64(const int32_t* hubs, int64_t n7, int64_t* a) {
 }
 
 __global__ void k_hub_inU(const int32_t* hubs, int64_t n7, DevGraph g, const int32_t* B, const int64_t* WB,
-                          RefSrc rs, const int64_t* aB, uint8_t* inU, int64_t* nU) {
-  __shared__ unsigned long long cu;
-  if (threadIdx.x == 0) cu = 0;
-  __syncthreads();
+                          RefSrc rs, const int64_t* aB, uint8_t* inU) {
   for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n7; k += (int64_t)gridDim.x * blockDim.x) {
     int32_t v = hubs[k];
     int64_t wv = g.vw[v];
     const Score sc = rs.sc(v);
     bool u = rs.on(v) && sc.q * aB[v] - sc.p * wv * (WB[B[v]] - wv) >= 0;
     inU[v] = u;
-    if (u) atomicAdd(&cu, 1ull);
   }
-  __syncthreads();
-  if (threadIdx.x == 0 && cu) atomicAdd((unsigned long long*)nU, cu);
+}
+
+// number of set flags (0 or 1), by few large workgroups.  With one add per workgroup of the row kernel to one address,
+// about 12 ns each, that kernel took 62 us on an R-MAT graph of 2^18 vertices, now 19 us and 4 us here.
+constexpr int COUNT_BLOCK = 1024;
+__global__ __launch_bounds__(COUNT_BLOCK) void k_count_flags(const uint8_t* flag, int64_t n, int64_t* out) {
+  int64_t s = 0;
+  const int64_t n8 = n / 8;
+  for (int64_t i = (int64_t)blockIdx.x * COUNT_BLOCK + threadIdx.x; i < n8; i += (int64_t)gridDim.x * COUNT_BLOCK)
+    s += __popcll(((const uint64_t*)flag)[i]);  // the flags start on a multiple of 256 bytes
+  const int64_t t = 8 * n8 + threadIdx.x;
+  if (blockIdx.x == 0 && t < n) s += flag[t];
+  s = sum_reduce<COUNT_BLOCK>(s);
+  if (threadIdx.x == 0 && s) atomicAdd((unsigned long long*)out, (unsigned long long)s);
 }
 
 __device__ __forceinline__ bool qualifies(const DevGraph& g, const int32_t* B, const uint8_t* inU, const Score& sc,
@@ -422,14 +426,15 @@ void refine(const DevGraph& g, const Buckets& b, const RefSrc& rs, const int32_t
   k_set_i64<<<1, 1, 0, st>>>(&ctrl->refine_U, 0);
   unsigned nrow;
   const RowSet rows = row_set(b, 6, &nrow);
-  if (nrow) k_aB_rows<<<nrow, BLOCK, 0, st>>>(rows, g, B, rb.WB, rs, rb.aB, rb.inU, &ctrl->refine_U);
+  if (nrow) k_aB_rows<<<nrow, BLOCK, 0, st>>>(rows, g, B, rb.WB, rs, rb.aB, rb.inU);
   const int32_t* hubs = L + b.off[7];
   const int64_t n7 = b.count[7];
   if (n7) {
     k_hub_zero64<<<grid_for(n7), BLOCK, 0, st>>>(hubs, n7, rb.aB);
     k_aB_hub<<<(unsigned)b.hub_chunks, HUB_BLOCK, 0, st>>>(hubs, b.hub_chunk_off, n7, g, B, rb.aB);
-    k_hub_inU<<<grid_for(n7), BLOCK, 0, st>>>(hubs, n7, g, B, rb.WB, rs, rb.aB, rb.inU, &ctrl->refine_U);
+    k_hub_inU<<<grid_for(n7), BLOCK, 0, st>>>(hubs, n7, g, B, rb.WB, rs, rb.aB, rb.inU);
   }
+  k_count_flags<<<(unsigned)std::min<int64_t>(cdiv(n, 8 * COUNT_BLOCK) + 1, 256), COUNT_BLOCK, 0, st>>>(rb.inU, n, &ctrl->refine_U);
   // random candidate edge
   if (nrow) k_choose_rows<<<nrow, BLOCK, 0, st>>>(rows, g, B, rb.inU, rs, rb.H);
   if (n7) {
