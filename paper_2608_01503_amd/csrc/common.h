@@ -30,7 +30,9 @@ enum : int {
   CT_NM = 10,    // kept moves
   CT_SQ = 11,    // change of the sum of squared cluster weights
   CT_INT = 12,   // internal edge weight
-  CT_COUNT = 13
+  CT_BAL = 13,   // the row checks: entries towards lower-ranked minus towards higher-ranked vertices
+  CT_WE = 14,    // and the entries' weight
+  CT_COUNT = 15
 };
 constexpr int32_t D_NONE = -1;   // no destination
 constexpr int32_t D_EMPTY = -2;  // destination = a new singleton cluster

@@ -1645,14 +1645,14 @@ __device__ __forceinline__ int64_t vertex_weight(int vw_mode, int64_t ws, const 
   return x;
 }
 
-__device__ __forceinline__ void flush_check(EdgeCheck ec, int64_t wsum, Ctrl* ctrl) {
+__device__ __forceinline__ void flush_check(EdgeCheck ec, int64_t wsum, Ctrl* ctrl, int64_t* S) {
   // block-wide: every thread calls this
   const int64_t bal = sum_reduce<BLOCK>(ec.balance);
   wsum = sum_reduce<BLOCK>(wsum);
   if (ec.err) atomicOr(&ctrl->err_bits, ec.err);
   if (threadIdx.x == 0) {
-    if (bal) atomicAdd((unsigned long long*)&ctrl->count0, (unsigned long long)bal);
-    if (wsum) atomicAdd((unsigned long long*)&ctrl->sum_we, (unsigned long long)wsum);
+    if (bal) atomicAdd(stripe(S, CT_BAL), (unsigned long long)bal);
+    if (wsum) atomicAdd(stripe(S, CT_WE), (unsigned long long)wsum);
   }
 }
 
@@ -1677,18 +1677,18 @@ __device__ __forceinline__ void validate_rows(const int32_t* list, int64_t cnt, 
   }
 }
 __global__ __launch_bounds__(BLOCK) void k_validate_rows(RowSet q, DevGraph g, VwSrc vm, const int64_t* vw_given, int64_t* vw_out,
-                                                         Ctrl* ctrl, int32_t* lo, bool search) {
+                                                         Ctrl* ctrl, int32_t* lo, bool search, int64_t* S) {
   EdgeCheck ec;
   int64_t wsum = 0;
   for_row_kind(q, [&](auto lanes, const int32_t* list, int64_t cnt, unsigned bid, unsigned nblk) {
     validate_rows<decltype(lanes)::value>(list, cnt, bid, nblk, g, vm, vw_given, vw_out, lo, search, ec, wsum);
   });
-  flush_check(ec, wsum, ctrl);
+  flush_check(ec, wsum, ctrl, S);
 }
 
 __global__ __launch_bounds__(BIG_BLOCK) void k_validate_blk(const int32_t* list, int64_t cnt, DevGraph g, VwSrc vm,
                                                             const int64_t* vw_given, int64_t* vw_out, Ctrl* ctrl,
-                                                            int32_t* lo, bool search) {
+                                                            int32_t* lo, bool search, int64_t* S) {
   EdgeCheck ec;
   int64_t wsum = 0;
   for (int64_t vi = blockIdx.x; vi < cnt; vi += gridDim.x) {
@@ -1705,13 +1705,13 @@ __global__ __launch_bounds__(BIG_BLOCK) void k_validate_blk(const int32_t* list,
       wsum += ws;
     }
   }
-  flush_check(ec, wsum, ctrl);
+  flush_check(ec, wsum, ctrl, S);
 }
 
 // hubs: chunk sums of the weighted degree land in hsum[k] (zeroed beforehand)
 __global__ __launch_bounds__(HUB_BLOCK) void k_validate_hub(const int32_t* hubs, const int32_t* chunk_off,
                                                             int64_t n7, DevGraph g, int64_t* hsum, Ctrl* ctrl,
-                                                            int32_t* lo, bool search) {
+                                                            int32_t* lo, bool search, int64_t* S) {
   const int k = find_chunk_owner(chunk_off, n7, blockIdx.x);
   const int32_t v = hubs[k];
   const int64_t rb = g.off[v];
@@ -1725,7 +1725,7 @@ __global__ __launch_bounds__(HUB_BLOCK) void k_validate_hub(const int32_t* hubs,
     const int64_t nlo = sum_reduce<HUB_BLOCK>(ec.lower);
     if (threadIdx.x == 0 && nlo) atomicAdd(&lo[v], (int32_t)nlo);
   }
-  flush_check(ec, threadIdx.x == 0 ? ws : 0, ctrl);
+  flush_check(ec, threadIdx.x == 0 ? ws : 0, ctrl, S);
 }
 
 __global__ void k_validate_hub_final(const int32_t* hubs, int64_t n7, VwSrc vm, const int64_t* vw_given,
@@ -1825,13 +1825,14 @@ void launch_validate_rows(const DevGraph& g, const Buckets& b, int vw_mode, cons
   if (tr && b.count[7]) fill_i32(lo, 0, g.n, st);  // hub rows add their chunks' counts
   unsigned nrow;
   const RowSet rows = row_set(b, 5, &nrow);
-  if (nrow) k_validate_rows<<<nrow, BLOCK, 0, st>>>(rows, g, vm, vw_given, vw_out, ctrl, lo, sb.search);
-  if (b.count[6]) k_validate_blk<<<vtx_blocks(b, b.count[6]), BIG_BLOCK, 0, st>>>(L + b.off[6], b.count[6], g, vm, vw_given, vw_out, ctrl, lo, sb.search);
+  if (nrow) k_validate_rows<<<nrow, BLOCK, 0, st>>>(rows, g, vm, vw_given, vw_out, ctrl, lo, sb.search, b.stripes);
+  if (b.count[6]) k_validate_blk<<<vtx_blocks(b, b.count[6]), BIG_BLOCK, 0, st>>>(L + b.off[6], b.count[6], g, vm, vw_given, vw_out, ctrl, lo, sb.search, b.stripes);
   if (b.count[7]) {
     fill_i64(b.hub_acc, 0, b.count[7], st);
-    k_validate_hub<<<(unsigned)b.hub_chunks, HUB_BLOCK, 0, st>>>(hubs, b.hub_chunk_off, b.count[7], g, b.hub_acc, ctrl, lo, sb.search);
+    k_validate_hub<<<(unsigned)b.hub_chunks, HUB_BLOCK, 0, st>>>(hubs, b.hub_chunk_off, b.count[7], g, b.hub_acc, ctrl, lo, sb.search, b.stripes);
     k_validate_hub_final<<<grid_for(b.count[7]), BLOCK, 0, st>>>(hubs, b.count[7], vm, vw_given, b.hub_acc, vw_out, ctrl);
   }
+  fold(b.stripes, {{CT_BAL, &ctrl->count0}, {CT_WE, (int64_t*)&ctrl->sum_we}}, st);
   if (tr) {  // the upper entries packed, sorted by their target and compared with the rows' lower parts
     scan_i32_i64(lo, sb.lbase, g.n, sb.scan_temp, st);
     const int64_t m = g.nnz / 2;
