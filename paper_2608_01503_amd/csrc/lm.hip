@@ -616,9 +616,11 @@ __global__ __launch_bounds__(BS) void k_enum_blk(const int32_t* list, int64_t cn
 }
 
 // Hubs, in two steps.  Every chunk of a hub sums its entries by cluster in LDS (a hub's neighbours often share few
-// clusters) and writes the sums, one 8-byte record (cluster << 32 | weight) per cluster, grouped by P = min(chunks,
-// HUB_PARTS) ranges of the cluster's hash; then one workgroup per range sums the records that all chunks have for it,
-// again in LDS, and finds the best cluster of the range.  A range holds about as many clusters as a chunk.
+// clusters) and writes the sums, one 8-byte record (cluster << 32 | weight) per cluster, grouped by P <= HUB_PARTS ranges
+// of the cluster's hash; then one workgroup per range sums the records that all chunks have for it, again in LDS, and
+// finds the best cluster of the range.  Up to HUB_PARTS chunks there are as many ranges; with more, s workgroups read
+// each range, every one for its own s-th part of it, P s = about the chunks.  So a table holds about as many clusters as
+// a chunk has entries, at most half its slots, for a hub of any length.
 // Chunk k's records are at 2 off[v] + k HUB_CHUNK of the edge arena (64-bit slots), its ranges' ends as 16-bit numbers
 // from slot 2 off[v] + d on: P + 1 per chunk, less than 8 d bytes for any d.
 // Bound by the latency of the gathers C[u] in the first step.  Sums in a global-memory hash of 2 d slots, which these
@@ -632,7 +634,7 @@ static_assert(HUB_SLOTS == 2 * HUB_CHUNK && HUB_SLOTS % (2 * U * HUB_BLOCK) == 0
 struct HubRow {
   int32_t v;
   int64_t base, d;
-  int nch, ch, parts;  // chunks of the hub, this workgroup's, ranges
+  int nch, ch, parts, split;  // chunks of the hub, this workgroup's, ranges, sub-ranges of each
   __device__ __forceinline__ HubRow(const int32_t* hubs, const int32_t* chunk_off, int64_t n7, const int64_t* off) {
     const int k = find_chunk_owner(chunk_off, n7, blockIdx.x);
     v = hubs[k];
@@ -640,7 +642,8 @@ struct HubRow {
     d = off[v + 1] - base;
     nch = chunk_off[k + 1] - chunk_off[k];
     ch = (int)blockIdx.x - chunk_off[k];
-    parts = nch < HUB_PARTS ? nch : HUB_PARTS;
+    split = (nch + HUB_PARTS - 1) / HUB_PARTS;
+    parts = nch / split;
   }
   __device__ __forceinline__ uint64_t* records(uint32_t* arena) const { return (uint64_t*)arena + 2 * base; }
   __device__ __forceinline__ uint16_t* ends(uint32_t* arena) const { return (uint16_t*)(records(arena) + d); }
@@ -687,8 +690,12 @@ __global__ __launch_bounds__(HUB_BLOCK) void k_hub_part(const int32_t* hubs, con
 }
 
 // One range of a hub's clusters: partial best.  Chunks are read by groups of 8 to 64 lanes (a chunk's share of a range
-// is HUB_CHUNK / chunks records on average).  Should the range hold more clusters than the table, it is done again in
-// twice as many sub-ranges of the hash, which is a bijection of the cluster id: enough sub-ranges fit always.
+// is HUB_CHUNK / P records on average).  Should a table not place a cluster within HUB_PROBES slots, the part is done
+// again in twice as many sub-ranges of the hash, which is a bijection of the cluster id: enough sub-ranges fit always.
+// The probes are bounded because a full table would be walked by every further record: with one workgroup per range
+// also for longer hubs, and walks of the whole table, an R-MAT graph of 2^26 vertices took 230 ms a pass, now 6.8 ms (the
+// global-memory hash took 19 ms); a star of 4 M leaves from singletons takes 0.17 ms (0.43 ms), of 16 M 1.4 ms (1.8 ms).
+constexpr int HUB_PROBES = 128;
 __global__ __launch_bounds__(HUB_BLOCK) void k_hub_best(const int32_t* hubs, const int32_t* chunk_off, int64_t n7,
                                                         DevGraph g, const int32_t* C, const int64_t* W, ScoreSrc ss,
                                                         uint32_t* arena, int64_t* ps, int32_t* pc, const LMSlot* slot,
@@ -699,7 +706,7 @@ __global__ __launch_bounds__(HUB_BLOCK) void k_hub_best(const int32_t* hubs, con
   __shared__ int full;
   const HubRow r(hubs, chunk_off, n7, g.off);
   const int t = threadIdx.x;
-  if (r.ch >= r.parts) {
+  if (r.ch >= r.parts * r.split) {
     if (t == 0) { ps[blockIdx.x] = INT64_MIN; pc[blockIdx.x] = INT32_MAX; }
     return;
   }
@@ -709,13 +716,16 @@ __global__ __launch_bounds__(HUB_BLOCK) void k_hub_best(const int32_t* hubs, con
   const uint16_t* ends = r.ends(arena);
   const int ls = r.nch <= 4 ? 6 : r.nch <= 8 ? 5 : r.nch <= 16 ? 4 : 3;
   const int gl = t & ((1 << ls) - 1);
+  const int range = r.split == 1 ? r.ch : r.ch / r.split;
+  const uint64_t part = (uint64_t)(r.ch - range * r.split);
   Best best = best_init();
-  for (uint64_t sub = 1, q = 0; q < sub;) {  // uniform over the workgroup
+  for (uint64_t m = 1, i = 0; i < m;) {  // uniform over the workgroup
+    const uint64_t sub = (uint64_t)r.split * m, q = part * m + i;
     for (int s = t; s < HUB_SLOTS; s += HUB_BLOCK) { lk[s] = -1; lv[s] = 0; }
     if (t == 0) full = 0;
     __syncthreads();
-    for (int ch = t >> ls; ch < r.nch; ch += HUB_BLOCK >> ls) {
-      const int64_t e = (int64_t)ch * (r.parts + 1) + r.ch;
+    for (int ch = t >> ls; ch < r.nch && !*(volatile int*)&full; ch += HUB_BLOCK >> ls) {
+      const int64_t e = (int64_t)ch * (r.parts + 1) + range;
       const uint64_t* p = rec + (int64_t)ch * HUB_CHUNK;
       const int j1 = ends[e + 1];
       for (int j = ends[e] + gl; j < j1; j += U << ls) {
@@ -728,19 +738,19 @@ __global__ __launch_bounds__(HUB_BLOCK) void k_hub_best(const int32_t* hubs, con
           if (c < 0 || (sub > 1 && ((hub_hash(c, r.parts) & 0xFFFFFFFFu) * sub) >> 32 != q)) continue;
           uint32_t h = hslot(c, HUB_LDS_BITS);
           int probe = 0;
-          for (; probe < HUB_SLOTS; ++probe) {
+          for (; probe < HUB_PROBES; ++probe) {
             const int32_t prev = atomicCAS(&lk[h], -1, c);
             if (prev == -1 || prev == c) { atomicAdd(&lv[h], (uint32_t)xs[k]); break; }
             h = (h + 1) & (HUB_SLOTS - 1);
           }
-          if (probe == HUB_SLOTS) full = 1;
+          if (probe == HUB_PROBES) full = 1;
         }
       }
     }
     __syncthreads();
     if (full) {
-      sub *= 2;
-      q = 0;
+      m *= 2;
+      i = 0;
       best = best_init();
       __syncthreads();
       continue;
@@ -760,7 +770,7 @@ __global__ __launch_bounds__(HUB_BLOCK) void k_hub_best(const int32_t* hubs, con
         if (better(x, cs[k], best.s, best.c)) { best.s = x; best.c = cs[k]; }
       }
     }
-    ++q;
+    ++i;
     __syncthreads();
   }
   best_reduce<HUB_BLOCK>(best);

@@ -40,9 +40,33 @@ def test_hub_rows_around_the_chunks(variant, tuning):
 
 @pytest.mark.parametrize("leaves", [2048 * 256, 2048 * 256 + 1, 1400000])
 def test_hub_of_more_chunks_than_ranges(leaves):
-    """From singletons by labels, so that the first pass finds one cluster per leaf: with 1.4 M leaves a range has
-    about 5,500 clusters for a table of 4,096."""
+    """From singletons by labels, so that the first pass finds one cluster per leaf: 1.4 M leaves have 684 chunks, and
+    three workgroups share each range."""
     g = gg.from_pairs(leaves + 1, np.stack([np.zeros(leaves, np.int64), np.arange(1, leaves + 1)], axis=1))
     init = np.random.default_rng(1).permutation(leaves + 1).astype(np.int32)
+    for lam, mode in (MOD, CPM):
+        U.assert_parity(g, O.LOUVAIN, lam, mode, opts_kw=dict(pass_limit=2), init=init)
+
+
+def _fmix32(x):
+    x = x.astype(np.uint64)
+    for shift, mul in ((16, 0x85EBCA6B), (13, 0xC2B2AE35), (16, 1)):
+        x = ((x ^ (x >> np.uint64(shift))) * np.uint64(mul)) & np.uint64(0xFFFFFFFF)
+    return x
+
+
+def test_hub_with_its_clusters_in_one_range():
+    """A hub of 20 chunks whose 40,000 neighbours' labels all hash into one of the 20 ranges: the table of that range
+    is split again until its parts fit."""
+    n, d, chunks = 1 << 20, 40000, 20
+    rng = np.random.default_rng(5)
+    ranges = (_fmix32(np.arange(n)) * np.uint64(chunks)) >> np.uint64(32)
+    labels = np.flatnonzero(ranges == 7)[:d]
+    assert len(labels) == d
+    rest = rng.permutation(np.setdiff1d(np.arange(n), labels))
+    init = np.concatenate([rest[:1], labels, rest[1:]]).astype(np.int32)
+    P = np.concatenate([np.stack([np.zeros(d, np.int64), np.arange(1, d + 1)], axis=1),
+                        rng.integers(d + 1, n, size=(300000, 2))])
+    g = gg.from_pairs(n, P, rng.integers(1, 9, size=len(P)))
     for lam, mode in (MOD, CPM):
         U.assert_parity(g, O.LOUVAIN, lam, mode, opts_kw=dict(pass_limit=2), init=init)
