@@ -694,8 +694,11 @@ __global__ __launch_bounds__(HUB_BLOCK) void k_hub_part(const int32_t* hubs, con
 // again in twice as many sub-ranges of the hash, which is a bijection of the cluster id: enough sub-ranges fit always.
 // The probes are bounded because a full table would be walked by every further record: with one workgroup per range
 // also for longer hubs, and walks of the whole table, an R-MAT graph of 2^26 vertices took 230 ms a pass, now 6.8 ms (the
-// global-memory hash took 19 ms); a star of 4 M leaves from singletons takes 0.17 ms (0.43 ms), of 16 M 1.4 ms (1.8 ms).
+// global-memory hash took 19 ms); a star of 4 M leaves from singletons takes 0.14 ms (0.43 ms), of 16 M 1.0 ms (1.8 ms).
 constexpr int HUB_PROBES = 128;
+// Chunks whose ends and first records a lane group loads at once: the loads of one chunk after the other are a chain
+// (star of 16 M leaves: 1.4 ms with chunks one by one).
+constexpr int HC = 4;
 __global__ __launch_bounds__(HUB_BLOCK) void k_hub_best(const int32_t* hubs, const int32_t* chunk_off, int64_t n7,
                                                         DevGraph g, const int32_t* C, const int64_t* W, ScoreSrc ss,
                                                         uint32_t* arena, int64_t* ps, int32_t* pc, const LMSlot* slot,
@@ -724,26 +727,45 @@ __global__ __launch_bounds__(HUB_BLOCK) void k_hub_best(const int32_t* hubs, con
     for (int s = t; s < HUB_SLOTS; s += HUB_BLOCK) { lk[s] = -1; lv[s] = 0; }
     if (t == 0) full = 0;
     __syncthreads();
-    for (int ch = t >> ls; ch < r.nch && !*(volatile int*)&full; ch += HUB_BLOCK >> ls) {
-      const int64_t e = (int64_t)ch * (r.parts + 1) + range;
-      const uint64_t* p = rec + (int64_t)ch * HUB_CHUNK;
-      const int j1 = ends[e + 1];
-      for (int j = ends[e] + gl; j < j1; j += U << ls) {
-        uint64_t xs[U];
+    const auto insert = [&](uint64_t x) {
+      const int32_t c = (int32_t)(x >> 32);
+      if (c < 0 || (sub > 1 && ((hub_hash(c, r.parts) & 0xFFFFFFFFu) * sub) >> 32 != q)) return;
+      uint32_t h = hslot(c, HUB_LDS_BITS);
+      for (int probe = 0; probe < HUB_PROBES; ++probe) {
+        const int32_t prev = atomicCAS(&lk[h], -1, c);
+        if (prev == -1 || prev == c) { atomicAdd(&lv[h], (uint32_t)x); return; }
+        h = (h + 1) & (HUB_SLOTS - 1);
+      }
+      full = 1;
+    };
+    for (int ch = t >> ls; ch < r.nch && !*(volatile int*)&full; ch += HC * (HUB_BLOCK >> ls)) {
+      int j0[HC], j1[HC];
 #pragma unroll
-        for (int k = 0; k < U; ++k) xs[k] = j + (k << ls) < j1 ? p[j + (k << ls)] : ~0ull;  // no cluster has id -1
+      for (int k = 0; k < HC; ++k) {
+        const int chk = ch + k * (HUB_BLOCK >> ls);
+        const int64_t e = (int64_t)chk * (r.parts + 1) + range;
+        j0[k] = chk < r.nch ? ends[e] : 0;
+        j1[k] = chk < r.nch ? ends[e + 1] : 0;
+      }
+      uint64_t xs[HC][2];
 #pragma unroll
-        for (int k = 0; k < U; ++k) {
-          const int32_t c = (int32_t)(xs[k] >> 32);
-          if (c < 0 || (sub > 1 && ((hub_hash(c, r.parts) & 0xFFFFFFFFu) * sub) >> 32 != q)) continue;
-          uint32_t h = hslot(c, HUB_LDS_BITS);
-          int probe = 0;
-          for (; probe < HUB_PROBES; ++probe) {
-            const int32_t prev = atomicCAS(&lk[h], -1, c);
-            if (prev == -1 || prev == c) { atomicAdd(&lv[h], (uint32_t)xs[k]); break; }
-            h = (h + 1) & (HUB_SLOTS - 1);
-          }
-          if (probe == HUB_PROBES) full = 1;
+      for (int k = 0; k < HC; ++k) {
+        const uint64_t* p = rec + (int64_t)(ch + k * (HUB_BLOCK >> ls)) * HUB_CHUNK;
+        j0[k] += gl;
+#pragma unroll
+        for (int i2 = 0; i2 < 2; ++i2) xs[k][i2] = j0[k] + (i2 << ls) < j1[k] ? p[j0[k] + (i2 << ls)] : ~0ull;  // no cluster has id -1
+      }
+#pragma unroll
+      for (int k = 0; k < HC; ++k) {
+        insert(xs[k][0]);
+        insert(xs[k][1]);
+        const uint64_t* p = rec + (int64_t)(ch + k * (HUB_BLOCK >> ls)) * HUB_CHUNK;
+        for (int j = j0[k] + (2 << ls); j < j1[k]; j += U << ls) {
+          uint64_t ys[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) ys[u] = j + (u << ls) < j1[k] ? p[j + (u << ls)] : ~0ull;
+#pragma unroll
+          for (int u = 0; u < U; ++u) insert(ys[u]);
         }
       }
     }
