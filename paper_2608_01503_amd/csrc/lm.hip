@@ -627,7 +627,9 @@ __global__ __launch_bounds__(BS) void k_enum_blk(const int32_t* list, int64_t cn
 // steps replace, took a compare-and-swap or an add in memory per cluster of a chunk, and clearing the table as it was
 // scanned: 88 us a pass on an R-MAT graph of 2^18 vertices (8 M entries), now 39 us; on one of 2^22 vertices 385 us,
 // now about 95 us.
-constexpr int HUB_PARTS = HUB_BLOCK;
+// 1024 ranges: with 256 every record of a long hub is looked at by four times as many workgroups (star of 16 M leaves:
+// 1.0 ms a pass, now 0.7).
+constexpr int HUB_PARTS = 1024, HUB_PT = HUB_PARTS / HUB_BLOCK;  // ranges, and ranges scanned by a thread
 constexpr int HUB_SLOTS = 1 << HUB_LDS_BITS;
 static_assert(HUB_SLOTS == 2 * HUB_CHUNK && HUB_SLOTS % (2 * U * HUB_BLOCK) == 0, "the LDS table holds 2 slots per chunk edge");
 
@@ -661,7 +663,7 @@ __global__ __launch_bounds__(HUB_BLOCK) void k_hub_part(const int32_t* hubs, con
   const int64_t j0 = r.base + (int64_t)r.ch * HUB_CHUNK, j1 = min(r.base + r.d, j0 + HUB_CHUNK);
   const int t = threadIdx.x, lane = t & (WAVE - 1);
   for (int s = t; s < HUB_SLOTS; s += HUB_BLOCK) { lk[s] = -1; lv[s] = 0; }
-  at[t] = 0;
+  for (int i = t; i < HUB_PARTS; i += HUB_BLOCK) at[i] = 0;
   __syncthreads();
   const int64_t own = insert_row(g, C, j0, j1, t, HUB_BLOCK, C[r.v], lk, lv, HUB_LDS_BITS, cons, cons ? cons[r.v] : 0);
   __syncthreads();
@@ -669,7 +671,10 @@ __global__ __launch_bounds__(HUB_BLOCK) void k_hub_part(const int32_t* hubs, con
     if (lk[s] >= 0) atomicAdd(&at[hub_hash(lk[s], r.parts) >> 32], 1);
   const int64_t own_sum = sum_reduce<HUB_BLOCK>(own);  // with barriers
   if (t == 0) pown[blockIdx.x] = own_sum;
-  int inc = at[t];
+  int first[HUB_PT], inc = 0;
+#pragma unroll
+  for (int k = 0; k < HUB_PT; ++k) { first[k] = inc; inc += at[t * HUB_PT + k]; }
+  const int mine = inc;
 #pragma unroll
   for (int o = 1; o < WAVE; o <<= 1) {
     const int y = __shfl_up(inc, o, WAVE);
@@ -678,23 +683,28 @@ __global__ __launch_bounds__(HUB_BLOCK) void k_hub_part(const int32_t* hubs, con
   if (lane == WAVE - 1) wsum[t / WAVE] = inc;
   __syncthreads();
   for (int w = 0; w < t / WAVE; ++w) inc += wsum[w];
-  const int first = inc - at[t];
-  at[t] = first;
   uint16_t* ends = r.ends(arena) + (int64_t)r.ch * (r.parts + 1);
-  if (t < r.parts) ends[t] = (uint16_t)first;
-  if (t == r.parts - 1) ends[r.parts] = (uint16_t)inc;
+#pragma unroll
+  for (int k = 0; k < HUB_PT; ++k) {
+    const int i = t * HUB_PT + k;
+    first[k] += inc - mine;
+    at[i] = first[k];
+    if (i < r.parts) ends[i] = (uint16_t)first[k];
+  }
+  if (t == HUB_BLOCK - 1) ends[r.parts] = (uint16_t)inc;
   __syncthreads();
   uint64_t* rec = r.records(arena) + (int64_t)r.ch * HUB_CHUNK;
   for (int s = t; s < HUB_SLOTS; s += HUB_BLOCK)
     if (lk[s] >= 0) rec[atomicAdd(&at[hub_hash(lk[s], r.parts) >> 32], 1)] = (uint64_t)(uint32_t)lk[s] << 32 | lv[s];
 }
 
-// One range of a hub's clusters: partial best.  Chunks are read by groups of 8 to 64 lanes (a chunk's share of a range
+// One range of a hub's clusters: partial best.  Chunks are read by groups of 2 to 64 lanes (a chunk's share of a range
 // is HUB_CHUNK / P records on average).  Should a table not place a cluster within HUB_PROBES slots, the part is done
 // again in twice as many sub-ranges of the hash, which is a bijection of the cluster id: enough sub-ranges fit always.
 // The probes are bounded because a full table would be walked by every further record: with one workgroup per range
-// also for longer hubs, and walks of the whole table, an R-MAT graph of 2^26 vertices took 230 ms a pass, now 6.8 ms (the
-// global-memory hash took 19 ms); a star of 4 M leaves from singletons takes 0.14 ms (0.43 ms), of 16 M 1.0 ms (1.8 ms).
+// also for longer hubs, and walks of the whole table, an R-MAT graph of 2^26 vertices took 230 ms a pass, now 5.9 ms (the
+// global-memory hash took 19 ms); a star of 4 M leaves from singletons takes 0.11 ms (0.43 ms), of 16 M 0.7 ms (1.8 ms), of 60 M 8.3 ms (6.8 ms): every
+// range reads all chunks, so the cost grows with the square of the chunks beyond about 20 M entries of one row.
 constexpr int HUB_PROBES = 128;
 // Chunks whose ends and first records a lane group loads at once: the loads of one chunk after the other are a chain
 // (star of 16 M leaves: 1.4 ms with chunks one by one).
@@ -717,7 +727,7 @@ __global__ __launch_bounds__(HUB_BLOCK) void k_hub_best(const int32_t* hubs, con
   const int64_t wvt = g.vw[r.v];
   const uint64_t* rec = r.records(arena);
   const uint16_t* ends = r.ends(arena);
-  const int ls = r.nch <= 4 ? 6 : r.nch <= 8 ? 5 : r.nch <= 16 ? 4 : 3;
+  const int ls = r.nch <= 4 ? 6 : r.nch <= 8 ? 5 : r.nch <= 16 ? 4 : r.nch <= 256 ? 3 : r.nch <= 512 ? 2 : 1;
   const int gl = t & ((1 << ls) - 1);
   const int range = r.split == 1 ? r.ch : r.ch / r.split;
   const uint64_t part = (uint64_t)(r.ch - range * r.split);

@@ -38,10 +38,10 @@ def test_hub_rows_around_the_chunks(variant, tuning):
         ctx.set_tuning(old)
 
 
-@pytest.mark.parametrize("leaves", [2048 * 256, 2048 * 256 + 1, 1400000])
+@pytest.mark.parametrize("leaves", [2048 * 256, 2048 * 256 + 1, 1400000, 2048 * 1024 + 1])
 def test_hub_of_more_chunks_than_ranges(leaves):
-    """From singletons by labels, so that the first pass finds one cluster per leaf: 1.4 M leaves have 684 chunks, and
-    three workgroups share each range."""
+    """From singletons by labels, so that the first pass finds one cluster per leaf: 2048 * 1024
+    + 1 leaves have 1,025 chunks, and two workgroups share each of 512 ranges."""
     g = gg.from_pairs(leaves + 1, np.stack([np.zeros(leaves, np.int64), np.arange(1, leaves + 1)], axis=1))
     init = np.random.default_rng(1).permutation(leaves + 1).astype(np.int32)
     for lam, mode in (MOD, CPM):
