@@ -626,7 +626,7 @@ __global__ __launch_bounds__(BS) void k_enum_blk(const int32_t* list, int64_t cn
 // Bound by the latency of the gathers C[u] in the first step.  Sums in a global-memory hash of 2 d slots, which these
 // steps replace, took a compare-and-swap or an add in memory per cluster of a chunk, and clearing the table as it was
 // scanned: 88 us a pass on an R-MAT graph of 2^18 vertices (8 M entries), now 39 us; on one of 2^22 vertices 385 us,
-// now about 95 us.
+// now about 190 us.
 // 1024 ranges: with 256 every record of a long hub is looked at by four times as many workgroups (star of 16 M leaves:
 // 1.0 ms a pass, now 0.7).
 constexpr int HUB_PARTS = 1024, HUB_PT = HUB_PARTS / HUB_BLOCK;  // ranges, and ranges scanned by a thread
